@@ -69,11 +69,62 @@ template <int G> __device__ __forceinline__ double group_sum(double v)
     return v;
 }
 
-template <int G> __device__ __forceinline__ int group_min(int v)
+// v from the partner lane of butterfly step K. Steps 0 and 1 pair lane i with
+// i ^ 1 and i ^ 2 (quad_perm); from step 2 on, all lanes of an aligned block
+// of 2^K lanes already hold the same value, so any lane of the neighbouring
+// block will do: step 2 uses row_half_mirror (i -> 7 - i within 8), step 3
+// row_mirror (i -> 15 - i within 16), both DPP moves; steps 4 and 5 use lane
+// permutes across rows.
+template <int K> __device__ __forceinline__ int partner(int v)
 {
-#pragma unroll
-    for (int o = 1; o < G; o <<= 1)
-        v = min(v, __shfl_xor(v, o));
+    if constexpr (K == 0)
+        return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true); // quad_perm [1,0,3,2]
+    else if constexpr (K == 1)
+        return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true); // quad_perm [2,3,0,1]
+    else if constexpr (K == 2)
+        return __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true); // row_half_mirror
+    else if constexpr (K == 3)
+        return __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, true); // row_mirror
+    else
+        return __shfl_xor(v, 1 << K);
+}
+template <int K> __device__ __forceinline__ double partner(double v)
+{
+    int2 w = __builtin_bit_cast(int2, v);
+    w.x = partner<K>(w.x);
+    w.y = partner<K>(w.y);
+    return __builtin_bit_cast(double, w);
+}
+
+// Reductions over aligned groups of G lanes, G a wave-uniform run-time power
+// of two from 4 to 64.
+__device__ __forceinline__ double group_sum(double v, int G)
+{
+    v += partner<0>(v);
+    v += partner<1>(v);
+    if (G > 4)
+        v += partner<2>(v);
+    if (G > 8)
+        v += partner<3>(v);
+    if (G > 16)
+        v += partner<4>(v);
+    if (G > 32)
+        v += partner<5>(v);
+    return v;
+}
+
+__device__ __forceinline__ int group_min(int v, int G)
+{
+    v = min(v, partner<0>(v));
+    v = min(v, partner<1>(v));
+    if (G > 4)
+        v = min(v, partner<2>(v));
+    if (G > 8)
+        v = min(v, partner<3>(v));
+    if (G > 16)
+        v = min(v, partner<4>(v));
+    if (G > 32)
+        v = min(v, partner<5>(v));
     return v;
 }
 
@@ -108,7 +159,7 @@ template <bool LDS_ONLY> __device__ __forceinline__ void wg_barrier()
 // single-precision squared distance equals m1 and the first other position
 // whose distance equals m2 (the second order statistic): the minimum and the
 // second minimum with ties to the smaller index.
-template <int G> struct Argmins {
+struct Argmins {
     int f1 = INT_MAX, g1 = INT_MAX, g2 = INT_MAX;
     __device__ void see(int t, float s, float2 m)
     {
@@ -121,10 +172,10 @@ template <int G> struct Argmins {
                 g2 = t;
         }
     }
-    __device__ void resolve(int *q1, int *q2) const
+    __device__ void resolve(int *q1, int *q2, int G) const
     {
-        *q1 = group_min<G>(f1);
-        *q2 = group_min<G>(g1 != *q1 ? g1 : g2);
+        *q1 = group_min(f1, G);
+        *q2 = group_min(g1 != *q1 ? g1 : g2, G);
     }
 };
 

@@ -51,6 +51,40 @@ __host__ inline int softmax_lanes(int64_t owners, int64_t pairs)
 // Longer segments read the rest again in each step.
 constexpr int kSmCache = 8;
 
+// Calls f(lanes, owner, lane of the group) for the owner of each group of G
+// lanes, then, for the owners whose segment exceeds the groups' registers
+// (kSmCache pairs a lane), with the whole wave, one such owner after another.
+// A group strides through a long segment with two dependent loads a step
+// while the other groups of its wave wait: one point far from the rest keeps
+// hundreds of candidates (its gap sets its radius), and its row alone took
+// most of a launch. The lane count is a run-time value so that both uses
+// share one copy of f (two copies held 166 instead of 126 registers).
+// Forward + backward, before and after: 32 x 2048 points 357 -> 321 us, losses
+// of 100 x 1024 points 251 -> 201 us, 6 x 1900 x 1500 with rows that fall back
+// to all pairs 3.10 -> 2.53 ms. The forward kernels and the double-precision
+// row adjoint are held to four waves per SIMD: the bound costs them 40 and 16
+// bytes of scratch in the long-segment loops, without it three waves.
+template <int G, class F> __device__ __forceinline__ void each_owner(int o, int n_own, const int32_t *ptr, F f)
+{
+    const int n = o < n_own ? ptr[o + 1] - ptr[o] : 0;
+    const bool spread = n > G * kSmCache;
+    uint64_t left = __ballot(spread && threadIdx.x % G == 0);
+    bool mine = o < n_own && !spread;
+    int lanes = G, lane = (int)(threadIdx.x % G), owner = o;
+    for (;;) {
+        asm volatile("" : "+s"(lanes)); // one copy of f: the first pass is not peeled off
+        if (mine)
+            f(lanes, owner, lane);
+        if (left == 0)
+            break;
+        owner = __builtin_amdgcn_readlane(o, __builtin_ctzll(left));
+        left &= left - 1;
+        lanes = 64;
+        lane = lane_id();
+        mine = true;
+    }
+}
+
 // Pair t (row-major position; row i, column j of sample b, the k-th entry of
 // its column) with P0 into the per-sample Sinkhorn pieces of both orders.
 __device__ __forceinline__ void pack_pair(const DevPlan &d, int b, int j, int k, int i, int t, float p0)
@@ -80,8 +114,8 @@ __device__ __forceinline__ double dist3(float ax, float ay, float az, float bx, 
 // ROWS: owner r = b*N + i over row-major pairs t (the other index is the
 // column j); else owner gc = b*M + j over column-major entries q (the other
 // index is the row i, the row-major position t = csc_perm[q]).
-template <bool ROWS, int G>
-__device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p, int o, int lg)
+template <bool ROWS>
+__device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p, int o, int G, int lg)
 {
     const int n_own = ROWS ? d.N : d.M, n_oth = ROWS ? d.M : d.N;
     const int b = o / n_own;
@@ -123,7 +157,7 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
     };
 
     // minimum and second minimum among the stored pairs (single precision)
-    Argmins<G> am;
+    Argmins am;
 #pragma unroll
     for (int c = 0; c < kSmCache; ++c)
         if (lg + G * c < n)
@@ -134,7 +168,7 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
         am.see(s0 + k, sqdist_f32(a0, a1, a2, x, y, z), m);
     }
     int q1, q2;
-    am.resolve(&q1, &q2);
+    am.resolve(&q1, &q2, G);
     if (q1 == INT_MAX || q2 == INT_MAX) { // cannot happen: both minima are always emitted
         if (lg == 0) {
             atomicOr(&d.ctr->error, ROWS ? 1u : 2u);
@@ -172,7 +206,7 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
 #pragma unroll
             for (int c = 0; c < kSmCache; ++c)
                 v += lg + G * c == k ? dc[c] : 0.0;
-            return group_sum<G>(v);
+            return group_sum(v, G);
         }
         float x, y, z;
         other(k, x, y, z);
@@ -207,7 +241,7 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
         if (s >= p.tau)
             zsum += s;
     }
-    zsum = group_sum<G>(zsum);
+    zsum = group_sum(zsum, G);
 
     // P = s / Z on the kept pairs; rows store C, columns P0 = (P_row + P_col)/2
     auto write = [&](int k, int t, double c, double s, float pr, uint8_t f) {
@@ -249,20 +283,20 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
     }
 }
 
-template <int G> __global__ __launch_bounds__(kBlock) void k_row_softmax(DevPlan d, Params p)
+template <int G> __global__ __launch_bounds__(kBlock, 4) void k_row_softmax(DevPlan d, Params p)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    const int r = gid / G;
-    if (r < d.B * d.N)
-        owner_softmax<true, G>(d, p, r, gid % G);
+    each_owner<G>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+        owner_softmax<true>(d, p, r, lanes, lg);
+    });
 }
 
-template <int G> __global__ __launch_bounds__(kBlock) void k_col_softmax(DevPlan d, Params p)
+template <int G> __global__ __launch_bounds__(kBlock, 4) void k_col_softmax(DevPlan d, Params p)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    const int gc = gid / G;
-    if (gc < d.B * d.M)
-        owner_softmax<false, G>(d, p, gc, gid % G);
+    each_owner<G>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+        owner_softmax<false>(d, p, gc, lanes, lg);
+    });
 }
 
 // Column-major view of columns [j0, j1) of sample b in one workgroup: every
@@ -331,9 +365,9 @@ template <int G> __global__ __launch_bounds__(kCscT) void k_csc_rows(DevPlan d, 
         return;
     }
     const int gid = (blockIdx.x - d.B * parts) * kCscT + threadIdx.x;
-    const int r = gid / G;
-    if (r < d.B * d.N)
-        owner_softmax<true, G>(d, p, r, gid % G);
+    each_owner<G>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+        owner_softmax<true>(d, p, r, lanes, lg);
+    });
 }
 
 __host__ inline size_t csc_sample_lds(int M, int64_t max_pairs)
@@ -374,14 +408,11 @@ template <bool DP> struct BwdP {
     using T = std::conditional_t<DP, double, float>; // type of the cached P
 };
 
-template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_softmax(DevPlan d, Params p)
+template <bool DP>
+__device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p, int gc, int G, int lg)
 {
     constexpr int NC = BwdP<DP>::kCache;
     using PT = typename BwdP<DP>::T;
-    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    const int gc = gid / G, lg = gid % G;
-    if (gc >= d.B * d.M)
-        return;
     const int b = gc / d.M;
     const double gl = d.grad_loss[b];
     const int s0 = d.col_ptr[gc], n = d.col_ptr[gc + 1] - s0;
@@ -425,7 +456,7 @@ template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_so
             if (d.flags[t] & 2)
                 zsum += exp(-T * (d.cost[t] - c1));
         }
-        zsum = group_sum<G>(zsum);
+        zsum = group_sum(zsum, G);
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             pq[c] = kq[c] ? pq[c] / zsum : 0.0;
@@ -447,7 +478,7 @@ template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_so
         if (f & 2)
             sigma += p_at(s0 + k, t) * (sym_weight(p, f) * p0bar(d, t, gl));
     }
-    sigma = group_sum<G>(sigma);
+    sigma = group_sum(sigma, G);
     double tbar = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
@@ -458,7 +489,7 @@ template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_so
         if (f & 2)
             tbar -= p_at(s0 + k, t) * (sym_weight(p, f) * p0bar(d, t, gl) - sigma) * (d.cost[t] - c1);
     }
-    tbar = group_sum<G>(tbar);
+    tbar = group_sum(tbar, G);
     const double gapbar = gapbar_scale * tbar;
     auto gap_terms = [&](int q, double cb) {
         if (q == q2)
@@ -481,15 +512,19 @@ template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_so
     }
 }
 
-template <int G, bool DP>
-__global__ __launch_bounds__(kBlock) void k_bwd_row_softmax(DevPlan d, Params p, int keep_cbar)
+template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_softmax(DevPlan d, Params p)
+{
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
+    each_owner<G>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+        bwd_col_owner<DP>(d, p, gc, lanes, lg);
+    });
+}
+
+template <bool DP>
+__device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p, int keep_cbar, int r, int G, int lg)
 {
     constexpr int NC = BwdP<DP>::kCache;
     using PT = typename BwdP<DP>::T;
-    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    const int r = gid / G, lg = gid % G;
-    if (r >= d.B * d.N)
-        return;
     const int b = r / d.N;
     const size_t BN = (size_t)d.B * d.N, BM = (size_t)d.B * d.M;
     const float *xr = d.x + (size_t)r * 3;
@@ -533,7 +568,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_row_softmax(DevPlan d, Params p,
         for (int k = lg + G * NC; k < n; k += G)
             if (d.flags[t0 + k] & 1)
                 zsum += exp(-T * (d.cost[t0 + k] - c1));
-        zsum = group_sum<G>(zsum);
+        zsum = group_sum(zsum, G);
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             pq[c] = kq[c] ? pq[c] / zsum : 0.0;
@@ -555,7 +590,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_row_softmax(DevPlan d, Params p,
         if (f & 1)
             sigma += p_at(t) * (sym_weight(p, f) * p0bar(d, t, gl));
     }
-    sigma = group_sum<G>(sigma);
+    sigma = group_sum(sigma, G);
     double tbar = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
@@ -566,7 +601,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_row_softmax(DevPlan d, Params p,
         if (f & 1)
             tbar -= p_at(t) * (sym_weight(p, f) * p0bar(d, t, gl) - sigma) * (d.cost[t] - c1);
     }
-    tbar = group_sum<G>(tbar);
+    tbar = group_sum(tbar, G);
     const double gapbar = gscale * tbar;
     double gx = 0.0, gy = 0.0, gz = 0.0;
     // cbar of pair t (column part cb0, P_row, dL/dP0, cost, P0, column j) into grad_x (Eq. 5)
@@ -599,9 +634,9 @@ __global__ __launch_bounds__(kBlock) void k_bwd_row_softmax(DevPlan d, Params p,
         add(t, d.csr_col[t], d.cbar[t], kept, kept ? p_at(t) : 0.0, sym_weight(p, f) * p0bar(d, t, gl), d.cost[t],
             d.p0r[t]);
     }
-    gx = group_sum<G>(gx);
-    gy = group_sum<G>(gy);
-    gz = group_sum<G>(gz);
+    gx = group_sum(gx, G);
+    gy = group_sum(gy, G);
+    gz = group_sum(gz, G);
     if (lg == 0) {
         float *o = d.grad_x + (size_t)r * 3;
         o[0] = (float)gx;
@@ -610,12 +645,17 @@ __global__ __launch_bounds__(kBlock) void k_bwd_row_softmax(DevPlan d, Params p,
     }
 }
 
-template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_grad_y(DevPlan d, Params p)
+template <int G, bool DP>
+__global__ __launch_bounds__(kBlock, 4) void k_bwd_row_softmax(DevPlan d, Params p, int keep_cbar)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    const int gc = gid / G, lg = gid % G;
-    if (gc >= d.B * d.M)
-        return;
+    each_owner<G>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+        bwd_row_owner<DP>(d, p, keep_cbar, r, lanes, lg);
+    });
+}
+
+__device__ __forceinline__ void grad_y_owner(const DevPlan &d, const Params &p, int gc, int G, int lg)
+{
     const int b = gc / d.M;
     const float *yc = d.y + (size_t)gc * 3;
     const float *xb = d.x + (size_t)b * d.N * 3;
@@ -628,15 +668,23 @@ template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_grad_y(DevPlan 
         gy -= w * ((double)xi[1] - (double)yc[1]);
         gz -= w * ((double)xi[2] - (double)yc[2]);
     }
-    gx = group_sum<G>(gx);
-    gy = group_sum<G>(gy);
-    gz = group_sum<G>(gz);
+    gx = group_sum(gx, G);
+    gy = group_sum(gy, G);
+    gz = group_sum(gz, G);
     if (lg == 0) {
         float *o = d.grad_y + (size_t)gc * 3;
         o[0] = (float)gx;
         o[1] = (float)gy;
         o[2] = (float)gz;
     }
+}
+
+template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_grad_y(DevPlan d, Params p)
+{
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
+    each_owner<G>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+        grad_y_owner(d, p, gc, lanes, lg);
+    });
 }
 
 } // namespace
