@@ -1058,9 +1058,6 @@ apml_status run_backward(apml_plan *plan, const float *x, const float *y, const 
     dv.yr = dv.yc = nullptr;
     // the split streamed reverse kernel exchanges the owners' factors in memory
     const bool split = dv.L > 0 && plan->sink_wide && sinkhorn_split_factor(plan->B) > 1;
-    // On the per-iteration path the row-order sweep adjoint becomes the final
-    // adjoint in place (k_bwd_final reads and writes the same pair), and the
-    // cost adjoint reuses the column-order copy, dead once the sweeps end.
     auto lay = [&](Carve &c) {
         dv.adj = c.take<double>(plan->stored);
         if (dv.L > 0 && plan->sink_wide) {
@@ -1074,11 +1071,9 @@ apml_status run_backward(apml_plan *plan, const float *x, const float *y, const 
                 dv.yc = c.take<float>((size_t)dv.L * ((size_t)plan->B * plan->M + kSinkOwnersW));
             }
         } else if (dv.L > 0 && !plan->sink_bwd) {
-            dv.rz = dv.adj;
-            dv.kz = c.take<double>(plan->stored);
-            dv.cbar = dv.kz;
-            dv.xyr = c.take<double4>((size_t)plan->B * plan->N);
-            dv.xyc = c.take<double4>((size_t)plan->B * plan->M);
+            dv.cbar = c.take<double>(plan->stored);
+            dv.rbar = c.take<double>((size_t)plan->B * plan->N);
+            dv.cs = c.take<double2>((size_t)plan->B * plan->M);
         } else {
             dv.cbar = c.take<double>(plan->stored);
         }
@@ -1100,7 +1095,7 @@ apml_status run_backward(apml_plan *plan, const float *x, const float *y, const 
             } else if (plan->sink_wide) {
                 HIP_TRY(launch_sinkhorn_bwd_wide(dv, s));
             } else {
-                launch_sinkhorn_bwd_steps(dv, s);
+                launch_sinkhorn_bwd_steps(dv, plan->prm.eps_stab, s);
                 HIP_TRY(hipGetLastError());
             }
         }

@@ -326,10 +326,8 @@ struct DevPlan {
     float *grad_x, *grad_y;
     double *adj, *cbar;           // [nnz] row-major
     double *dvec;                 // [B*N] row losses of the per-iteration forward kernels
-    double4 *xyr, *xyc;           // [B*N], [B*M] per-owner values of the per-iteration reverse sweeps: X, Y and
-                                  // the reciprocal of the owner's scaling
-    double *rz, *kz;              // [nnz] reverse-sweep adjoints in row and in column order (per-iteration
-                                  // kernels; rz shares adj's memory and cbar kz's)
+    double *rbar;                 // [B*N] per-iteration reverse sweeps: adjoints of the row sums
+    double2 *cs;                  // [B*M] and per column its scaling and the adjoint of its sum
     PackedOrder pk_row, pk_col;   // per-sample Sinkhorn pieces (when that path is taken)
     WideOrder wk_row, wk_col;     // streamed per-sample pieces (larger samples)
     float *wr, *wc;               // backward of the streamed path: the plan adjoint in row and in column pieces
@@ -434,7 +432,7 @@ void launch_place(const DevPlan &d, int32_t *place, hipStream_t s);
 hipError_t launch_sinkhorn_fwd(const DevPlan &d, double eps, hipStream_t s);
 hipError_t launch_sinkhorn_bwd(const DevPlan &d, int64_t max_pairs, hipStream_t s);
 void launch_sinkhorn_fwd_steps(const DevPlan &d, double eps, hipStream_t s);
-void launch_sinkhorn_bwd_steps(const DevPlan &d, hipStream_t s);
+void launch_sinkhorn_bwd_steps(const DevPlan &d, double eps, hipStream_t s);
 
 // Kept pairs per sample, in count_support_chunks(largest sample) partial
 // counts per sample: out [B][chunks].

@@ -1616,12 +1616,11 @@ __global__ __launch_bounds__(kBlock) void k_zero_u32(uint32_t *a, int n)
 // per-iteration kernels (any N, M): one launch per sweep
 // ---------------------------------------------------------------------------
 //
-// G lanes per owner (row or column; steps_lanes); each lane issues the loads
-// of kSB of its pairs together before using them (kSBRev in the reverse
-// launches, whose pairs carry 12 registers each: with 8 they held 101
-// registers, four waves per SIMD; with 4, 61 and eight waves: reverse sweeps
-// 0.525 -> 0.474 ms on 16 x 4096 x 16384 points, 0.455 -> 0.444 ms on
-// 4 x 65536, measured side by side on one MI355X; 2 was slower than 4). Sums are per
+// G lanes per owner (row or column; steps_lanes), the whole wave for owners
+// of more than G kSB pairs (each_owner: 16 x 4096 x 16384 points, a column
+// launch 13 -> 10 us and a row launch 20 -> 12 us); each lane issues the loads
+// of kSB of its pairs together before using them (kSBRev in the reverse row
+// launches, whose pairs carry more registers: eight waves per SIMD). Sums are per
 // lane in pair order, then a butterfly over the group, so results do not
 // depend on scheduling.
 constexpr int kSG = 4;
@@ -1635,10 +1634,10 @@ __global__ __launch_bounds__(kBlock) void k_fill_ones(double *a, int n)
         a[k] = 1.0;
 }
 
-// Sum over owner o's pairs k = lg, lg + kSG, ... of f(k, position) with the
-// loads of kSB pairs in flight at once.
-template <int G = kSG, int SB = kSB, class Load, class Use>
-__device__ __forceinline__ double owner_sum(int n, int lg, Load load, Use use)
+// Sum over an owner's pairs k = lg, lg + G, ... of f(k, position) with the
+// loads of SB pairs in flight at once, added up over its G lanes.
+template <int SB = kSB, class Load, class Use>
+__device__ __forceinline__ double owner_sum(int n, int G, int lg, Load load, Use use)
 {
     double acc = 0.0;
     for (int k0 = lg; k0 < n; k0 += G * SB) {
@@ -1651,19 +1650,14 @@ __device__ __forceinline__ double owner_sum(int n, int lg, Load load, Use use)
             if (k0 + G * u < n)
                 acc += use(v[u]);
     }
-    return group_sum<G>(acc);
+    return group_sum(acc, G);
 }
 
 // Column step (Eq. 3, COL) or row step (Eq. 4) of iteration l for all owners.
-template <bool COL, int G> __global__ __launch_bounds__(kBlock) void k_sink_step(DevPlan d, int l, double eps)
+template <bool COL>
+__device__ __forceinline__ void sink_owner(const DevPlan &d, int l, double eps, int o, int G, int lg)
 {
-    // each XCD takes a contiguous range of owners: its L2 holds only the
-    // other side's scalings of those owners' samples
-    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-    const int o = gid / G, lg = gid % G;
     const int n_own = COL ? d.M : d.N, n_oth = COL ? d.N : d.M;
-    if (o >= d.B * n_own)
-        return;
     const int b = o / n_own;
     const size_t BN = (size_t)d.B * d.N, BM = (size_t)d.B * d.M;
     const int32_t *ptr = COL ? d.col_ptr : d.row_ptr;
@@ -1679,7 +1673,7 @@ template <bool COL, int G> __global__ __launch_bounds__(kBlock) void k_sink_step
         float p;
         double x;
     };
-    const double acc = owner_sum<G>(n, lg,
+    const double acc = owner_sum(n, G, lg,
                                  [&](int k) {
                                      V v{0.0f, 0.0};
                                      if (k >= 0) {
@@ -1695,12 +1689,17 @@ template <bool COL, int G> __global__ __launch_bounds__(kBlock) void k_sink_step
     }
 }
 
-template <int G> __global__ __launch_bounds__(kBlock) void k_loss_rows(DevPlan d, double *loss_rows)
+template <bool COL, int G> __global__ __launch_bounds__(kBlock) void k_sink_step(DevPlan d, int l, double eps)
 {
-    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
-    const int r = gid / G, lg = gid % G;
-    if (r >= d.B * d.N)
-        return;
+    // each XCD takes a contiguous range of owners: its L2 holds only the
+    // other side's scalings of those owners' samples
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    each_owner<G, kSB>(gid / G, d.B * (COL ? d.M : d.N), COL ? d.col_ptr : d.row_ptr,
+                       [&](int lanes, int o, int lg) { sink_owner<COL>(d, l, eps, o, lanes, lg); });
+}
+
+__device__ __forceinline__ void loss_row(const DevPlan &d, double *loss_rows, int r, int G, int lg)
+{
     const int b = r / d.N;
     const size_t BN = (size_t)d.B * d.N, BM = (size_t)d.B * d.M;
     const double *beta = d.beta + (size_t)d.L * BM + (size_t)b * d.M;
@@ -1709,7 +1708,7 @@ template <int G> __global__ __launch_bounds__(kBlock) void k_loss_rows(DevPlan d
         float p;
         double bc;
     };
-    const double acc = owner_sum<G>(n, lg,
+    const double acc = owner_sum(n, G, lg,
                                  [&](int k) {
                                      V v{0.0f, 0.0};
                                      if (k >= 0) {
@@ -1721,6 +1720,13 @@ template <int G> __global__ __launch_bounds__(kBlock) void k_loss_rows(DevPlan d
                                  [&](const V &v) { return (double)v.p * v.bc; });
     if (lg == 0)
         loss_rows[r] = d.alpha[(size_t)d.L * BN + r] * acc;
+}
+
+template <int G> __global__ __launch_bounds__(kBlock) void k_loss_rows(DevPlan d, double *loss_rows)
+{
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
+    each_owner<G, kSB>(gid / G, d.B * d.N, d.row_ptr,
+                       [&](int lanes, int r, int lg) { loss_row(d, loss_rows, r, lanes, lg); });
 }
 
 // Per sample: the sum of its row losses. 1024 threads, four partial sums per
@@ -1750,139 +1756,139 @@ __global__ __launch_bounds__(kLossT) void k_loss_reduce(DevPlan d, const double 
     }
 }
 
-// Reverse sweeps, one launch per half-step. The adjoint is kept twice in
-// double precision, in row order (rz) and in column order (kz), in the
-// scaled form of the per-sample kernel (adjoint * alpha^l before a row
-// phase, * beta^l before a column phase), and each copy is brought up to
-// date in its own order, so no launch reads or writes pairs out of order:
-//   row launch l:    rz <- column update of iteration l+1 (l < L), then the
-//                    row update of iteration l; row sums; row values
-//                    X_i = alpha^l_i, Y_i = d_i alpha^l_i and 1/alpha^l_i into xyr
-//   column launch l: kz <- row update of iteration l, then the column update
-//                    of iteration l; column sums; column values X_j =
-//                    beta^l_j, Y_j = e_j beta^l_j and 1/beta^l_j into xyc
-// where the row update of iteration l is z' = (z / alpha^l_i) X_j - Y_j with
-// the column values published last, and the column update z' = (z / beta^l_j)
-// X_i - Y_i with the row values of iteration l. The other side's values of a
-// pair arrive in one 32-byte gather; values, sums and updates are double
-// (single-precision factors left gradient errors of 1e-5 that moved with the
-// rounding of the sums).
-__global__ __launch_bounds__(kBlock) void k_bwd_init(DevPlan d)
+// Reverse sweeps, one launch per half-step, on the owners' scalings alone.
+// With f(c, s) = c / (c s + eps), df/dc = eps (f / c)^2 and df/ds = -f^2, so
+// the adjoints of the row and column sums of P0 against the other side's
+// scalings,
+//   Rbar^l_i = -(alpha^l_i)^2 alphabar^l_i   (of sum_j P0_ij beta^l_j),
+//   Sbar^l_j = -(beta^l_j)^2 betabar^l_j     (of sum_i alpha^(l-1)_i P0_ij),
+// follow one another without any per-pair state:
+//   Sbar^l_j     = eps Sbar^(l+1)_j - (beta^l_j)^2 sum_i P0_ij Rbar^l_i
+//   Rbar^(l-1)_i = eps Rbar^l_i - (alpha^(l-1)_i)^2 sum_j P0_ij Sbar^l_j
+// from the direct terms of the loss (sum alpha^L P0 beta^L C), and
+//   dLoss/dP0_ij = g alpha^L_i beta^L_j C_ij
+//                  + sum_l (Rbar^l_i beta^l_j + alpha^(l-1)_i Sbar^l_j),
+// which the row launches add up in row order, in double precision. A column
+// launch reads 16 bytes a pair (P0, index, Rbar), a row launch 40 (P0, index,
+// the pair's sum, and beta, Sbar in one gather). With the adjoint itself kept
+// per pair, once in each order, both launches moved 56: per launch 23 -> 11 us
+// (columns) and 33 -> 19 us (rows) at 16 x 4096 x 16384 points, 21 -> 12 and
+// 23 -> 14 us at 4 x 65536.
+//
+// Row launch L: the pairs' direct terms and Rbar^L.
+__device__ __forceinline__ void bwd_first_row(const DevPlan &d, int r, int G, int lg)
 {
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const size_t BN = (size_t)d.B * d.N, BM = (size_t)d.B * d.M;
-    if (g < d.nnz) { // row order: grad_loss * C, times alpha^L_i
-        const int r = d.csr_row[g], b = r / d.N;
-        d.rz[g] = d.grad_loss[b] * d.cost[g] * d.alpha[(size_t)d.L * BN + r];
-        // column order: the same pair through the permutation
-        const int t = d.csc_perm[g], rr = d.csr_row[t], bb = rr / d.N;
-        d.kz[g] = d.grad_loss[bb] * d.cost[t] * d.alpha[(size_t)d.L * BN + rr];
-    }
-    if (g < (int64_t)BM) { // no pending column update before the last iteration
-        const double bl = d.beta[(size_t)d.L * BM + g];
-        d.xyc[g] = make_double4(bl, 0.0, 1.0 / bl, 0.0);
-    }
-}
-
-template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_rows(DevPlan d, int l)
-{
-    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
-    const int r = gid / G, lg = gid % G;
-    if (r >= d.B * d.N)
-        return;
     const int b = r / d.N;
-    const size_t BN = (size_t)d.B * d.N;
-    const double4 *xyc = d.xyc + (size_t)b * d.M;
-    const bool pending = l < d.L;
-    const double4 mine = pending ? d.xyr[r] : make_double4(0.0, 0.0, 0.0, 0.0); // row values of iteration l+1
-    const double al = d.alpha[(size_t)l * BN + r];
-    const double inv_a = 1.0 / al;
+    const size_t BN = (size_t)d.B * d.N, BM = (size_t)d.B * d.M;
+    const double *beta = d.beta + (size_t)d.L * BM + (size_t)b * d.M;
+    const double al = d.alpha[(size_t)d.L * BN + r], gl = d.grad_loss[b];
     const int t0 = d.row_ptr[r], n = d.row_ptr[r + 1] - t0;
     struct V {
-        double z;
+        double bl, c;
         float p;
         int k;
-        double4 c;
     };
-    const double acc = owner_sum<G, kSBRev>(n, lg,
+    const double acc = owner_sum<kSBRev>(n, G, lg,
                                          [&](int k) {
-                                             V v{0.0, 0.0f, k, make_double4(0.0, 0.0, 1.0, 0.0)};
+                                             V v{0.0, 0.0, 0.0f, k};
                                              if (k >= 0) {
-                                                 const int j = d.csr_col[t0 + k];
-                                                 v.z = d.rz[t0 + k];
+                                                 v.bl = beta[d.csr_col[t0 + k]];
+                                                 v.c = d.cost[t0 + k];
                                                  v.p = d.p0r[t0 + k];
-                                                 v.c = xyc[j];
                                              }
                                              return v;
                                          },
                                          [&](const V &v) {
-                                             double z = v.z;
-                                             if (pending) // 1/beta^(l+1)_j
-                                                 z = __builtin_fma(z * v.c.z, mine.x, -mine.y);
-                                             z = __builtin_fma(z * inv_a, v.c.x, -v.c.y);
-                                             d.rz[t0 + v.k] = z;
-                                             return z * (double)v.p;
+                                             const double w = gl * v.bl * v.c;
+                                             d.adj[t0 + v.k] = al * w;
+                                             return w * (double)v.p;
                                          });
-    if (lg == 0) { // adjoint of Eq. 4: d_i = alpha^l_i * sum
-        const double dsum = al * acc;
-        d.xyr[r] = make_double4(al, dsum * al, inv_a, 0.0);
-    }
+    if (lg == 0)
+        d.rbar[r] = -(al * al) * acc;
 }
 
-template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_cols(DevPlan d, int l)
+template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_first(DevPlan d)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
-    const int gc = gid / G, lg = gid % G;
-    if (gc >= d.B * d.M)
-        return;
+    each_owner<G, kSB>(gid / G, d.B * d.N, d.row_ptr,
+                       [&](int lanes, int r, int lg) { bwd_first_row(d, r, lanes, lg); });
+}
+
+// Column launch l: Sbar^l. FIRST (l = L): with the direct term of the loss.
+template <bool FIRST>
+__device__ __forceinline__ void bwd_col(const DevPlan &d, int l, double eps, int gc, int G, int lg)
+{
     const int b = gc / d.M;
-    const size_t BM = (size_t)d.B * d.M;
-    const double4 *xyr = d.xyr + (size_t)b * d.N;
-    const double4 mine = d.xyc[gc]; // column values published last
-    const double bl = d.beta[(size_t)l * BM + gc];
-    const double inv_b = 1.0 / bl;
+    const size_t BN = (size_t)d.B * d.N, BM = (size_t)d.B * d.M;
+    const double *rbar = d.rbar + (size_t)b * d.N, *alpha = d.alpha + (size_t)l * BN + (size_t)b * d.N;
+    const double bl = d.beta[(size_t)l * BM + gc], gl = FIRST ? (double)d.grad_loss[b] : 0.0;
+    const double old = FIRST ? 0.0 : eps * d.cs[gc].y;
     const int s0 = d.col_ptr[gc], n = d.col_ptr[gc + 1] - s0;
     struct V {
+        float p;
+        double x;
+    };
+    const double acc = owner_sum(n, G, lg,
+                                 [&](int k) {
+                                     V v{0.0f, 0.0};
+                                     if (k >= 0) {
+                                         const int i = d.csc_row[s0 + k];
+                                         v.p = d.p0c[s0 + k];
+                                         v.x = rbar[i];
+                                         if (FIRST)
+                                             v.x += gl * alpha[i] * d.cost[d.csc_perm[s0 + k]];
+                                     }
+                                     return v;
+                                 },
+                                 [&](const V &v) { return (double)v.p * v.x; });
+    if (lg == 0)
+        d.cs[gc] = make_double2(bl, old - bl * bl * acc);
+}
+
+template <bool FIRST, int G> __global__ __launch_bounds__(kBlock) void k_bwd_cols(DevPlan d, int l, double eps)
+{
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
+    each_owner<G, kSB>(gid / G, d.B * d.M, d.col_ptr,
+                       [&](int lanes, int gc, int lg) { bwd_col<FIRST>(d, l, eps, gc, lanes, lg); });
+}
+
+// Row launch after column launch l: the pairs' terms of iteration l, Rbar^(l-1).
+__device__ __forceinline__ void bwd_row(const DevPlan &d, int l, double eps, int r, int G, int lg)
+{
+    const int b = r / d.N;
+    const double2 *cs = d.cs + (size_t)b * d.M;
+    const double rb = d.rbar[r], al = d.alpha[(size_t)(l - 1) * d.B * d.N + r];
+    const int t0 = d.row_ptr[r], n = d.row_ptr[r + 1] - t0;
+    struct V {
+        double2 c;
         double z;
         float p;
         int k;
-        double4 rw;
     };
-    const double acc = owner_sum<G, kSBRev>(n, lg,
+    const double acc = owner_sum<kSBRev>(n, G, lg,
                                          [&](int k) {
-                                             V v{0.0, 0.0f, k, make_double4(0.0, 0.0, 1.0, 0.0)};
+                                             V v{make_double2(0.0, 0.0), 0.0, 0.0f, k};
                                              if (k >= 0) {
-                                                 const int i = d.csc_row[s0 + k];
-                                                 v.z = d.kz[s0 + k];
-                                                 v.p = d.p0c[s0 + k];
-                                                 v.rw = xyr[i];
+                                                 v.c = cs[d.csr_col[t0 + k]];
+                                                 v.z = d.adj[t0 + k];
+                                                 v.p = d.p0r[t0 + k];
                                              }
                                              return v;
                                          },
-                                         [&](const V &v) { // v.rw.z = 1/alpha^l_i
-                                             double z = __builtin_fma(v.z * v.rw.z, mine.x, -mine.y);
-                                             z = __builtin_fma(z * inv_b, v.rw.x, -v.rw.y);
-                                             d.kz[s0 + v.k] = z;
-                                             return z * (double)v.p;
+                                         [&](const V &v) {
+                                             d.adj[t0 + v.k] =
+                                                 __builtin_fma(rb, v.c.x, __builtin_fma(al, v.c.y, v.z));
+                                             return v.c.y * (double)v.p;
                                          });
-    if (lg == 0) { // adjoint of Eq. 3: e_j = beta^l_j * sum
-        const double esum = bl * acc;
-        d.xyc[gc] = make_double4(bl, esum * bl, inv_b, 0.0);
-    }
+    if (lg == 0)
+        d.rbar[r] = eps * rb - al * al * acc;
 }
 
-// dLoss/dP0 in row order: the column update of iteration 1, then the row
-// update of iteration 0 (alpha^0 = 1).
-__global__ __launch_bounds__(kBlock) void k_bwd_final(DevPlan d)
+template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_rows(DevPlan d, int l, double eps)
 {
-    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (t >= d.nnz)
-        return;
-    const int r = d.csr_row[t], b = r / d.N, j = d.csr_col[t];
-    const double4 rw = d.xyr[r];
-    const double4 c = d.xyc[(size_t)b * d.M + j]; // c.z = 1/beta^1_j
-    double z = __builtin_fma(d.rz[t] * c.z, rw.x, -rw.y);
-    d.adj[t] = z * c.x - c.y;
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
+    each_owner<G, kSB>(gid / G, d.B * d.N, d.row_ptr,
+                       [&](int lanes, int r, int lg) { bwd_row(d, l, eps, r, lanes, lg); });
 }
 
 } // namespace
@@ -2122,8 +2128,10 @@ void launch_lanes(int g, int64_t owners, hipStream_t s, A... args)
 }
 template <int G> struct ColStep { static constexpr auto fn = k_sink_step<true, G>; };
 template <int G> struct RowStep { static constexpr auto fn = k_sink_step<false, G>; };
+template <int G> struct BwdFirst { static constexpr auto fn = k_bwd_first<G>; };
 template <int G> struct BwdRows { static constexpr auto fn = k_bwd_rows<G>; };
-template <int G> struct BwdCols { static constexpr auto fn = k_bwd_cols<G>; };
+template <int G> struct BwdColsFirst { static constexpr auto fn = k_bwd_cols<true, G>; };
+template <int G> struct BwdCols { static constexpr auto fn = k_bwd_cols<false, G>; };
 template <int G> struct LossRows { static constexpr auto fn = k_loss_rows<G>; };
 
 } // namespace
@@ -2143,16 +2151,18 @@ void launch_sinkhorn_fwd_steps(const DevPlan &d, double eps, hipStream_t s)
     hipLaunchKernelGGL(k_loss_reduce, dim3(d.B), dim3(kLossT), 0, s, d, (const double *)d.dvec);
 }
 
-void launch_sinkhorn_bwd_steps(const DevPlan &d, hipStream_t s)
+void launch_sinkhorn_bwd_steps(const DevPlan &d, double eps, hipStream_t s)
 {
     const int BN = d.B * d.N, BM = d.B * d.M;
     const int gr = steps_lanes(d.nnz, BN), gc = steps_lanes(d.nnz, BM);
-    hipLaunchKernelGGL(k_bwd_init, dim3(blocks_for(std::max<int64_t>(d.nnz, BM), kBlock)), dim3(kBlock), 0, s, d);
+    launch_lanes<BwdFirst>(gr, BN, s, d);
     for (int l = d.L; l >= 1; --l) {
-        launch_lanes<BwdRows>(gr, BN, s, d, l);
-        launch_lanes<BwdCols>(gc, BM, s, d, l);
+        if (l == d.L)
+            launch_lanes<BwdColsFirst>(gc, BM, s, d, l, eps);
+        else
+            launch_lanes<BwdCols>(gc, BM, s, d, l, eps);
+        launch_lanes<BwdRows>(gr, BN, s, d, l, eps);
     }
-    hipLaunchKernelGGL(k_bwd_final, dim3(blocks_for(d.nnz, kBlock)), dim3(kBlock), 0, s, d);
 }
 
 } // namespace apml

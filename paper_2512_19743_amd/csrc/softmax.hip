@@ -49,41 +49,13 @@ __host__ inline int softmax_lanes(int64_t owners, int64_t pairs)
 // coordinates and, for columns, P_row and the flags of the pair) and their
 // distances and similarities kept in registers, so the segment is read once.
 // Longer segments read the rest again in each step.
-constexpr int kSmCache = 8;
-
-// Calls f(lanes, owner, lane of the group) for the owner of each group of G
-// lanes, then, for the owners whose segment exceeds the groups' registers
-// (kSmCache pairs a lane), with the whole wave, one such owner after another.
-// A group strides through a long segment with two dependent loads a step
-// while the other groups of its wave wait: one point far from the rest keeps
-// hundreds of candidates (its gap sets its radius), and its row alone took
-// most of a launch. The lane count is a run-time value so that both uses
-// share one copy of f (two copies held 166 instead of 126 registers).
-// Forward + backward, before and after: 32 x 2048 points 357 -> 321 us, losses
+// Owners with more pairs than that take the whole wave (each_owner). Forward +
+// backward, before and after: 32 x 2048 points 357 -> 321 us, losses
 // of 100 x 1024 points 251 -> 201 us, 6 x 1900 x 1500 with rows that fall back
 // to all pairs 3.10 -> 2.53 ms. The forward kernels and the double-precision
 // row adjoint are held to four waves per SIMD: the bound costs them 40 and 16
 // bytes of scratch in the long-segment loops, without it three waves.
-template <int G, class F> __device__ __forceinline__ void each_owner(int o, int n_own, const int32_t *ptr, F f)
-{
-    const int n = o < n_own ? ptr[o + 1] - ptr[o] : 0;
-    const bool spread = n > G * kSmCache;
-    uint64_t left = __ballot(spread && threadIdx.x % G == 0);
-    bool mine = o < n_own && !spread;
-    int lanes = G, lane = (int)(threadIdx.x % G), owner = o;
-    for (;;) {
-        asm volatile("" : "+s"(lanes)); // one copy of f: the first pass is not peeled off
-        if (mine)
-            f(lanes, owner, lane);
-        if (left == 0)
-            break;
-        owner = __builtin_amdgcn_readlane(o, __builtin_ctzll(left));
-        left &= left - 1;
-        lanes = 64;
-        lane = lane_id();
-        mine = true;
-    }
-}
+constexpr int kSmCache = 8;
 
 // Pair t (row-major position; row i, column j of sample b, the k-th entry of
 // its column) with P0 into the per-sample Sinkhorn pieces of both orders.
@@ -286,7 +258,7 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
 template <int G> __global__ __launch_bounds__(kBlock, 4) void k_row_softmax(DevPlan d, Params p)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<G>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+    each_owner<G, kSmCache>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
         owner_softmax<true>(d, p, r, lanes, lg);
     });
 }
@@ -294,7 +266,7 @@ template <int G> __global__ __launch_bounds__(kBlock, 4) void k_row_softmax(DevP
 template <int G> __global__ __launch_bounds__(kBlock, 4) void k_col_softmax(DevPlan d, Params p)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<G>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+    each_owner<G, kSmCache>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
         owner_softmax<false>(d, p, gc, lanes, lg);
     });
 }
@@ -365,7 +337,7 @@ template <int G> __global__ __launch_bounds__(kCscT) void k_csc_rows(DevPlan d, 
         return;
     }
     const int gid = (blockIdx.x - d.B * parts) * kCscT + threadIdx.x;
-    each_owner<G>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+    each_owner<G, kSmCache>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
         owner_softmax<true>(d, p, r, lanes, lg);
     });
 }
@@ -515,7 +487,7 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
 template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_softmax(DevPlan d, Params p)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<G>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+    each_owner<G, kSmCache>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
         bwd_col_owner<DP>(d, p, gc, lanes, lg);
     });
 }
@@ -649,7 +621,7 @@ template <int G, bool DP>
 __global__ __launch_bounds__(kBlock, 4) void k_bwd_row_softmax(DevPlan d, Params p, int keep_cbar)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<G>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+    each_owner<G, kSmCache>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
         bwd_row_owner<DP>(d, p, keep_cbar, r, lanes, lg);
     });
 }
@@ -682,7 +654,7 @@ __device__ __forceinline__ void grad_y_owner(const DevPlan &d, const Params &p, 
 template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_grad_y(DevPlan d, Params p)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<G>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+    each_owner<G, kSmCache>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
         grad_y_owner(d, p, gc, lanes, lg);
     });
 }
