@@ -175,12 +175,14 @@ void pool_free(void *p, size_t size, hipStream_t s)
     m.free_blocks[{dev, s}].insert({size, p});
 }
 
-// A region that arenas carve from front to back, never giving memory back
-// within a call (the static scratch of apml_forward_backward_noalloc).
+// A region that arenas carve (the static scratch of
+// apml_forward_backward_noalloc): the plan's arrays from its front, the
+// temporaries of a pass from its end, which the next pass takes again.
 struct Bump {
     uint8_t *base = nullptr;
-    size_t cap = 0;
-    size_t used = 0;
+    size_t cap = 0;  // a multiple of 256
+    size_t used = 0; // from the front
+    size_t temp = 0; // from the end
     size_t need = 0; // bytes the call asked for when the region ran out
 };
 
@@ -189,6 +191,7 @@ struct Bump {
 struct Arena {
     hipStream_t stream = nullptr;
     Bump *bump = nullptr;
+    bool temporary = false; // of a bump region: from its end
     std::vector<std::pair<void *, size_t>> blocks;
     int64_t bytes = 0;
     bool failed = false;
@@ -199,15 +202,19 @@ struct Arena {
             return nullptr;
         const size_t want = std::max<size_t>(count * sizeof(T), 16);
         if (bump) {
-            const size_t at = (bump->used + 255) & ~size_t(255);
-            if (at > bump->cap || want > bump->cap - at) {
-                bump->need = std::max(bump->need, at + want);
+            const size_t size = (want + 255) & ~size_t(255);
+            if (size > bump->cap - bump->used - bump->temp) {
+                bump->need = std::max(bump->need, bump->used + bump->temp + size);
                 failed = true;
                 return nullptr;
             }
-            bump->used = at + want;
             bytes += (int64_t)want;
-            return reinterpret_cast<T *>(bump->base + at);
+            if (temporary) {
+                bump->temp += size;
+                return reinterpret_cast<T *>(bump->base + bump->cap - bump->temp);
+            }
+            bump->used += size;
+            return reinterpret_cast<T *>(bump->base + bump->used - size);
         }
         size_t got = 0;
         void *p = pool_alloc(want, stream, &got);
@@ -341,8 +348,7 @@ struct apml_plan {
     int64_t scanned[2] = {0, 0}; // pairs evaluated by the two dense scans
     bool skipping = false;  // the dense scans skipped pairs (large samples)
     int64_t max_sample = 0; // stored pairs of the largest sample
-    bool sink_fwd = false;  // per-sample Sinkhorn kernels take this plan (forward)
-    bool sink_bwd = false;  // and the reverse sweeps
+    bool sink_fwd = false;  // per-sample Sinkhorn kernels take this plan
     bool sink_wide = false; // streamed per-sample Sinkhorn kernels (larger samples)
     bool timed = true;  // phases recorded by the profiler (off for the no-alloc entry point)
     Arena keep;         // everything backward and export need
@@ -561,6 +567,7 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
     tmp.stream = s;
     dense_tmp.stream = s;
     tmp.bump = dense_tmp.bump = plan->keep.bump;
+    tmp.temporary = dense_tmp.temporary = true;
     const bool timed = plan->timed;
     Arena &keep = plan->keep;
     DevPlan &dv = plan->dv;
@@ -826,7 +833,6 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
     dv.nnz = nnz;
     const int slots = sinkhorn_slots(N, M, pieces, B);
     plan->sink_fwd = slots > 0;
-    plan->sink_bwd = sinkhorn_bwd_fits(slots, plan->max_sample);
     const int wslots = plan->sink_fwd ? 0 : sinkhorn_slots_wide(N, M, pieces, B);
     plan->sink_wide = wslots > 0;
 
@@ -851,7 +857,6 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
                 pk->p0 = c.take<float>(w);
                 pk->gi = c.take<uint32_t>(w / 2);
                 pk->info = c.take<uint32_t>(w / kSinkPiece);
-                pk->pos = pk == &dv.pk_col ? c.take<uint32_t>(w / 2) : nullptr;
                 pk->n_pos = c.take<int32_t>(B);
             }
         }
@@ -995,6 +1000,8 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
         pt.stop();
     }
     tmp.release();
+    if (bumped)
+        plan->keep.bump->temp = 0; // taken again by the backward pass, behind these kernels
     return APML_OK;
 }
 
@@ -1049,6 +1056,7 @@ apml_status run_backward(apml_plan *plan, const float *x, const float *y, const 
     Arena tmp;
     tmp.stream = s;
     tmp.bump = plan->keep.bump;
+    tmp.temporary = true;
     DevPlan dv = plan->dv;
     dv.x = x;
     dv.y = y;
@@ -1056,44 +1064,46 @@ apml_status run_backward(apml_plan *plan, const float *x, const float *y, const 
     dv.grad_x = grad_x;
     dv.grad_y = grad_y;
     dv.yr = dv.yc = nullptr;
-    // the split streamed reverse kernel exchanges the owners' factors in memory
-    const bool split = dv.L > 0 && plan->sink_wide && sinkhorn_split_factor(plan->B) > 1;
+    const size_t BN = (size_t)plan->B * plan->N, BM = (size_t)plan->B * plan->M;
+    // The kernels of larger samples exchange the owners' words of every phase
+    // in memory; where that does not fit, the per-iteration launches, which
+    // keep one word per owner, take the sweeps.
+    bool wide = plan->sink_wide && dv.L > 0;
     auto lay = [&](Carve &c) {
+        dv.cbar = c.take<double>(plan->stored);
+        if (dv.L == 0)
+            return;
         dv.adj = c.take<double>(plan->stored);
-        if (dv.L > 0 && plan->sink_wide) {
-            const size_t w = packed_order_words(plan->B, dv.wk_row.slots);
-            dv.wr = c.take<float>(w);
-            dv.wc = c.take<float>(w);
-            dv.cbar = c.take<double>(plan->stored);
-            if (split) {
-                // one region per phase, each padded by kSinkOwnersW words
-                dv.yr = c.take<float>((size_t)dv.L * ((size_t)plan->B * plan->N + kSinkOwnersW));
-                dv.yc = c.take<float>((size_t)dv.L * ((size_t)plan->B * plan->M + kSinkOwnersW));
-            }
-        } else if (dv.L > 0 && !plan->sink_bwd) {
-            dv.cbar = c.take<double>(plan->stored);
-            dv.rbar = c.take<double>((size_t)plan->B * plan->N);
-            dv.cs = c.take<double2>((size_t)plan->B * plan->M);
-        } else {
-            dv.cbar = c.take<double>(plan->stored);
+        dv.rbar = c.take<double>(BN);
+        dv.cs = c.take<double2>(BM);
+        if (wide) {
+            if (sinkhorn_bwd_streams(dv.wk_row.slots, plan->B))
+                dv.wz = c.take<double>(packed_order_words(plan->B, dv.wk_row.slots));
+            dv.yr = c.take<double>(sinkhorn_exchange_words(dv.L, BN));
+            dv.yc = c.take<double>(sinkhorn_exchange_words(dv.L, BM));
         }
     };
-    {
+    for (;;) {
         Carve size;
         lay(size);
         Carve c{tmp.get<uint8_t>(size.off)};
-        if (!tmp.failed)
+        if (!tmp.failed) {
             lay(c);
+            break;
+        }
+        if (!wide)
+            return fail(APML_ERR_OUT_OF_MEMORY, "device allocation failed (backward)");
+        wide = false;
+        tmp.failed = false;
     }
-    if (tmp.failed)
-        return fail(APML_ERR_OUT_OF_MEMORY, "device allocation failed (backward)");
     {
         PhaseTimer pt(PH_BWD_SINK, s, plan->timed);
         if (dv.L > 0) {
-            if (plan->sink_bwd) {
-                HIP_TRY(launch_sinkhorn_bwd(dv, plan->max_sample, s));
-            } else if (plan->sink_wide) {
-                HIP_TRY(launch_sinkhorn_bwd_wide(dv, s));
+            launch_bwd_direct(dv, s);
+            if (plan->sink_fwd) {
+                HIP_TRY(launch_sinkhorn_bwd(dv, plan->prm.eps_stab, s));
+            } else if (wide) {
+                HIP_TRY(launch_sinkhorn_bwd_wide(dv, plan->prm.eps_stab, s));
             } else {
                 launch_sinkhorn_bwd_steps(dv, plan->prm.eps_stab, s);
                 HIP_TRY(hipGetLastError());
@@ -1105,7 +1115,7 @@ apml_status run_backward(apml_plan *plan, const float *x, const float *y, const 
         PhaseTimer pt(PH_BWD_SOFTMAX, s, plan->timed);
         // double-precision P where the reverse sweeps keep the adjoint in
         // double too (per-iteration sweeps), or where there are none
-        const bool double_p = dv.L == 0 || (!plan->sink_bwd && !plan->sink_wide);
+        const bool double_p = dv.L == 0 || (!plan->sink_fwd && !plan->sink_wide);
         launch_bwd_softmax(dv, plan->kp, double_p, s);
         HIP_TRY(hipGetLastError());
         pt.stop();

@@ -281,7 +281,6 @@ struct PackedOrder {
     float *p0;      // [B][slots][kSinkPiece][lanes]: P0 (0 for padding)
     uint32_t *gi;   // [B][slots][kSinkPiece/2][lanes]: byte offsets of the gathered 8-byte values, two per word
     uint32_t *info; // [B][slots][lanes]: owner | log2(group) << 11 | head << 14 | valid << 15 | first position << 16 (rows)
-    uint32_t *pos;  // [B][slots][kSinkPiece/2][lanes]: row-major positions within the sample (columns only)
     int32_t *n_pos; // [B]: positions used
     int slots;      // positions per lane of this layout
 };
@@ -326,16 +325,16 @@ struct DevPlan {
     float *grad_x, *grad_y;
     double *adj, *cbar;           // [nnz] row-major
     double *dvec;                 // [B*N] row losses of the per-iteration forward kernels
-    double *rbar;                 // [B*N] per-iteration reverse sweeps: adjoints of the row sums
+    double *rbar;                 // [B*N] reverse sweeps: adjoints of the row sums
     double2 *cs;                  // [B*M] and per column its scaling and the adjoint of its sum
     PackedOrder pk_row, pk_col;   // per-sample Sinkhorn pieces (when that path is taken)
     WideOrder wk_row, wk_col;     // streamed per-sample pieces (larger samples)
-    float *wr, *wc;               // backward of the streamed path: the plan adjoint in row and in column pieces
+    double *wz;                   // streamed reverse sweeps: the pairs' sums of terms, in the row pieces' layout
     uint32_t *split_sync;         // [B][2][kSplitSyncStride]: meeting counter (word 0) and the workgroups' XCDs
                                   // (words 1..K) of the split streamed kernels
                                   // (forward, backward), cleared before each launch
-    float *yr, *yc;               // [L][B*N + kSinkOwnersW], [L][B*M + kSinkOwnersW]: owners' words published by
-                                  // the split reverse kernels, one padded region per phase
+    double *yr, *yc;              // sinkhorn_exchange_words each: owners' words published by the reverse kernels
+                                  // of larger samples, one region per phase
     const int32_t *sink_place;    // during the forward softmax of that path: the pieces' placement, so that the
                                   // column softmax writes every pair into its pieces; else NULL
 };
@@ -418,10 +417,12 @@ int sinkhorn_split_factor(int B);
 // Workgroups of a split launch: B rounded up to a multiple of the 8 XCDs, times K.
 inline int split_grid(int B, int K) { return (B + 7) / 8 * 8 * K; }
 // Streamed kernels, split over sinkhorn_split_factor(B) workgroups per sample
-// when that is above 1 (the reverse kernel then needs d.yr, d.yc), else one.
+// when that is above 1, else one. The reverse kernels need d.yr and d.yc, the
+// streamed ones (sinkhorn_bwd_streams) d.wz.
 hipError_t launch_sinkhorn_fwd_wide(const DevPlan &d, double eps, hipStream_t s);
-hipError_t launch_sinkhorn_bwd_wide(const DevPlan &d, hipStream_t s);
-bool sinkhorn_bwd_fits(int slots, int64_t max_pairs);
+hipError_t launch_sinkhorn_bwd_wide(const DevPlan &d, double eps, hipStream_t s);
+bool sinkhorn_bwd_streams(int slots, int B);
+size_t sinkhorn_exchange_words(int L, size_t owners);
 size_t packed_order_words(int B, int slots); // 32-bit words of one PackedOrder's p0 array
 // Lays out the pieces of both orders; place: [B][2][2048] int32 scratch.
 // placed: place[] and the info words are already written (with the compaction).
@@ -430,7 +431,10 @@ void launch_pack(const DevPlan &d, int32_t *place, bool placed, hipStream_t s);
 // packs the pairs.
 void launch_place(const DevPlan &d, int32_t *place, hipStream_t s);
 hipError_t launch_sinkhorn_fwd(const DevPlan &d, double eps, hipStream_t s);
-hipError_t launch_sinkhorn_bwd(const DevPlan &d, int64_t max_pairs, hipStream_t s);
+// The first adjoints of the row and column sums (rbar, cs) from the loss, then
+// the reverse sweeps, which leave each pair's sum of terms in adj.
+void launch_bwd_direct(const DevPlan &d, hipStream_t s);
+hipError_t launch_sinkhorn_bwd(const DevPlan &d, double eps, hipStream_t s);
 void launch_sinkhorn_fwd_steps(const DevPlan &d, double eps, hipStream_t s);
 void launch_sinkhorn_bwd_steps(const DevPlan &d, double eps, hipStream_t s);
 

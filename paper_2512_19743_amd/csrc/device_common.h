@@ -156,20 +156,20 @@ template <bool LDS_ONLY> __device__ __forceinline__ void wg_barrier()
 }
 
 // Calls f(lanes, owner, lane of the group) for the owner of each group of G
-// lanes, then, for the owners whose segment exceeds CAP pairs a lane (what a
+// lanes (a power of two from 4 to 64), then, for the owners whose segment exceeds CAP pairs a lane (what a
 // lane loads at once), with the whole wave, one such owner after another.
 // A group strides through a long segment with two dependent loads a step
 // while the other groups of its wave wait: one point far from the rest keeps
 // hundreds of candidates (its gap sets its radius), and its row alone took
 // most of a launch. The lane count is a run-time value so that both uses
 // share one copy of f (two copies held 166 instead of 126 registers).
-template <int G, int CAP, class F> __device__ __forceinline__ void each_owner(int o, int n_own, const int32_t *ptr, F f)
+template <int CAP, class F> __device__ __forceinline__ void each_owner(int G, int o, int n_own, const int32_t *ptr, F f)
 {
     const int n = o < n_own ? ptr[o + 1] - ptr[o] : 0;
     const bool spread = n > G * CAP;
-    uint64_t left = __ballot(spread && threadIdx.x % G == 0);
+    uint64_t left = __ballot(spread && (threadIdx.x & (G - 1)) == 0);
     bool mine = o < n_own && !spread;
-    int lanes = G, lane = (int)(threadIdx.x % G), owner = o;
+    int lanes = G, lane = (int)(threadIdx.x & (G - 1)), owner = o;
     for (;;) {
         asm volatile("" : "+s"(lanes)); // one copy of f: the first pass is not peeled off
         if (mine)

@@ -17,19 +17,13 @@
 // LDS) and the pieces of one owner are added by a butterfly inside their
 // aligned lane group, in a fixed order. In the forward kernel the group's
 // first lane then applies its owner's scaling at once (one barrier per
-// sweep); in the reverse kernel it stores the sum in LDS for an owner phase
-// in which lane t owns rows (columns) 2t and 2t+1.
+// sweep); in the reverse kernel it applies its owner's recurrence.
 // Sums have a fixed association, so results are bitwise reproducible.
 //
-// Reverse sweeps: for u = w/(R + eps) with R = sum over the row of w,
-//   wbar = (ubar - sum_row ubar*u) / (R + eps),
-// and likewise for the columns. The per-pair adjoint lives in LDS (indexed
-// by row-major position within the sample). An update is applied lazily: the
-// owner phase of a row step only publishes 1/(R + eps) and
-// q = (sum_row ubar*u)/(R + eps) per row, and the next piece phase, which
-// visits the pairs in column order, applies wbar = ubar/(R + eps) - q to each
-// pair it reads and writes the result back. Each pair's adjoint is read and
-// written once per sweep.
+// Reverse sweeps: the adjoints of the row and column sums of P0 against the
+// scalings follow one another through two short recurrences (see the
+// per-iteration reverse launches below), with no per-pair state but the sum of
+// each pair's terms, which becomes dLoss/dP0.
 #include <algorithm>
 #include <atomic>
 #include <cstdlib>
@@ -44,8 +38,6 @@ namespace {
 constexpr int kT = kSinkLanes;
 constexpr int kP = kSinkPiece;
 constexpr int kSL = kSinkOwners / kSinkLanes; // owners per lane in the owner phase
-using pieces::adj_slot;
-using pieces::adj_slots;
 using pieces::pack_col_pair;
 using pieces::pack_row_pair;
 using pieces::pk_index;
@@ -70,8 +62,7 @@ __global__ __launch_bounds__(kBlock) void k_pack_pairs(DevPlan d, const int32_t 
         pack_row_pair(d, place, b, r - b * d.N, (int)(t - d.row_ptr[r]), d.csr_col[t], d.p0r[t]);
     } else {
         const int gc = d.csc_col[t], b = gc / d.M, i = d.csc_row[t];
-        const int roff = d.csc_perm[t] - d.row_ptr[(size_t)b * d.N + i];
-        pack_col_pair(d, place, b, gc - b * d.M, (int)(t - d.col_ptr[gc]), i, roff, d.p0c[t]);
+        pack_col_pair(d, place, b, gc - b * d.M, (int)(t - d.col_ptr[gc]), i, d.p0c[t]);
     }
 }
 
@@ -80,15 +71,15 @@ __global__ __launch_bounds__(kBlock) void k_pack_pairs(DevPlan d, const int32_t 
 // ---------------------------------------------------------------------------
 
 // A lane's positions of one order, in registers for the whole kernel.
-template <bool POS, int SLP> struct Pieces {
+template <int SLP> struct Pieces {
     float p0[SLP][kP];
     uint32_t gi[SLP][kP / 2];
-    uint32_t pos[POS ? SLP : 1][POS ? kP / 2 : 1];
     uint32_t info[SLP];
     int n; // positions used (wave-uniform)
 };
 
-template <bool POS, int SLP> __device__ void load_pieces(Pieces<POS, SLP> &pc, const PackedOrder &pk, int b)
+// The first SLP of the layout's slots.
+template <int SLP> __device__ void load_pieces(Pieces<SLP> &pc, const PackedOrder &pk, int b)
 {
     const int tid = threadIdx.x;
 #pragma unroll
@@ -96,29 +87,25 @@ template <bool POS, int SLP> __device__ void load_pieces(Pieces<POS, SLP> &pc, c
         const int p = s * kT + tid;
 #pragma unroll
         for (int e = 0; e < kP; ++e)
-            pc.p0[s][e] = pk.p0[pk_index(b, p, e, kP, SLP)];
+            pc.p0[s][e] = pk.p0[pk_index(b, p, e, kP, pk.slots)];
 #pragma unroll
-        for (int w = 0; w < kP / 2; ++w) {
-            pc.gi[s][w] = pk.gi[pk_index(b, p, w, kP / 2, SLP)];
-            if (POS)
-                pc.pos[s][w] = pk.pos[pk_index(b, p, w, kP / 2, SLP)];
-        }
-        pc.info[s] = pk.info[pk_index(b, p, 0, 1, SLP)];
+        for (int w = 0; w < kP / 2; ++w)
+            pc.gi[s][w] = pk.gi[pk_index(b, p, w, kP / 2, pk.slots)];
+        pc.info[s] = pk.info[pk_index(b, p, 0, 1, pk.slots)];
     }
     pc.n = __builtin_amdgcn_readfirstlane(pk.n_pos[b]);
 }
 
 // Unpacking of the cached words. Each 16-bit half of a gi word holds the byte
-// offset of the gathered 8-byte value, each half of a pos word a row-major
-// position; an info word is owner (bits 0-10) | log2 group (11-13) | head (14)
+// offset of the gathered 8-byte value; an info word is owner (bits 0-10) | log2 group (11-13) | head (14)
 // | valid (15) | first row-major position of a row piece (16-31). Bit fields
 // are extracted at a base offset the compiler cannot see through (Unpack,
 // renewed every sweep), so the unpacked values and the masks derived from
 // them are recomputed inside the sweep loop instead of being hoisted out of
 // it, which would multiply the registers held; P0 is widened to double by an
 // instruction of its own for the same reason. The loads of a slot are issued
-// before any of its arithmetic. Padding pairs carry P0 = 0 and offset or
-// position 0: they gather and read real data, add nothing and write nothing.
+// before any of its arithmetic. Padding pairs carry P0 = 0 and offset 0:
+// they gather real data and add nothing.
 struct Unpack {
     uint32_t lo; // 0
 
@@ -150,19 +137,19 @@ template <typename T> __device__ __forceinline__ T lds_at(const void *base, uint
 }
 
 // Slot s of this wave holds at least one used position.
-template <bool POS, int SLP> __device__ __forceinline__ bool wave_active(const Pieces<POS, SLP> &pc, int s)
+__device__ __forceinline__ bool wave_active(int n_pos, int s)
 {
-    return s * kT + (int)(threadIdx.x & ~63u) < pc.n;
+    return s * kT + (int)(threadIdx.x & ~63u) < n_pos;
 }
 
 // Sum over the pairs of slot s of P0 times the gathered value (doubles at
 // vals + byte offset), in pair order.
 // P0 of slot s in double: widened once per kernel when the registers allow
 // (WIDE), else widened at each use.
-template <bool POS, int SLP, bool WIDE> struct P0Cache {
+template <int SLP, bool WIDE> struct P0Cache {
     double v[WIDE ? SLP : 1][WIDE ? kP : 1];
 
-    __device__ __forceinline__ void init(const Pieces<POS, SLP> &pc)
+    __device__ __forceinline__ void init(const Pieces<SLP> &pc)
     {
         if constexpr (WIDE) {
 #pragma unroll
@@ -172,7 +159,7 @@ template <bool POS, int SLP, bool WIDE> struct P0Cache {
                     v[s][e] = (double)pc.p0[s][e];
         }
     }
-    __device__ __forceinline__ double get(const Pieces<POS, SLP> &pc, int s, int e) const
+    __device__ __forceinline__ double get(const Pieces<SLP> &pc, int s, int e) const
     {
         if constexpr (WIDE)
             return v[s][e];
@@ -181,8 +168,8 @@ template <bool POS, int SLP, bool WIDE> struct P0Cache {
     }
 };
 
-template <bool POS, int SLP, bool WIDE>
-__device__ __forceinline__ double slot_dot(const Pieces<POS, SLP> &pc, const P0Cache<POS, SLP, WIDE> &p0, int s,
+template <int SLP, bool WIDE>
+__device__ __forceinline__ double slot_dot(const Pieces<SLP> &pc, const P0Cache<SLP, WIDE> &p0, int s,
                                            const double *vals, const Unpack &u)
 {
     double g[kP];
@@ -221,16 +208,6 @@ __device__ __forceinline__ double group_reduce(double acc, uint32_t info, const 
     bfly_step<5>(acc, lg, lgmax);
     return acc;
 }
-
-// Stores a group's sum at its owner (first lane of the group).
-__device__ __forceinline__ void store_sum(double acc, uint32_t info, double *sums, const Unpack &u)
-{
-    if (u.bits(info, 14, 2) == 3u) // head and valid
-        sums[u.owner(info)] = acc;
-}
-
-constexpr size_t bwd_fixed_lds_bytes() { return (8 + 8 + 4 + 4) * (size_t)kSinkOwners; }
-
 
 // a / b for positive normal a, b: the hardware reciprocal refined by two
 // Newton steps, then one correction of the quotient (within an ulp of the
@@ -308,11 +285,11 @@ template <int SLP> __global__ __launch_bounds__(kT) void k_sinkhorn_fwd(DevPlan 
     const int N = d.N, M = d.M, L = d.L;
     const size_t BN = (size_t)d.B * N, BM = (size_t)d.B * M;
     const int lo = d.row_ptr[(size_t)b * N], hi = d.row_ptr[(size_t)(b + 1) * N];
-    Pieces<false, SLP> pr, pc;
+    Pieces<SLP> pr, pc;
     load_pieces(pr, d.pk_row, b);
     load_pieces(pc, d.pk_col, b);
     constexpr bool kWide = SLP <= kFwdWideSlots;
-    P0Cache<false, SLP, kWide> prw, pcw;
+    P0Cache<SLP, kWide> prw, pcw;
     prw.init(pr);
     pcw.init(pc);
 #pragma unroll
@@ -335,7 +312,7 @@ template <int SLP> __global__ __launch_bounds__(kT) void k_sinkhorn_fwd(DevPlan 
         double *gb = d.beta + l * BM + (size_t)b * M;
 #pragma unroll
         for (int s = 0; s < SLP; ++s)
-            if (wave_active(pc, s)) {
+            if (wave_active(pc.n, s)) {
                 const double acc = slot_dot(pc, pcw, s, va, u);
                 apply_scaling(group_reduce(acc, pc.info[s], u), pc.info[s], vb, eps, gb, u);
             }
@@ -344,7 +321,7 @@ template <int SLP> __global__ __launch_bounds__(kT) void k_sinkhorn_fwd(DevPlan 
         double *ga = d.alpha + l * BN + (size_t)b * N;
 #pragma unroll
         for (int s = 0; s < SLP; ++s)
-            if (wave_active(pr, s)) {
+            if (wave_active(pr.n, s)) {
                 const double acc = slot_dot(pr, prw, s, vb, u);
                 apply_scaling(group_reduce(acc, pr.info[s], u), pr.info[s], va, eps, ga, u);
             }
@@ -354,22 +331,6 @@ template <int SLP> __global__ __launch_bounds__(kT) void k_sinkhorn_fwd(DevPlan 
     sample_loss(d, b, lo, hi, va, vb, part);
 }
 
-// Reverse sweeps, last iteration first. The plan adjoint starts as
-// grad_loss * C (loss = sum v C) and ends as dLoss/dP0 in d.adj (row-major).
-//
-// Scaled representation. With the lazy updates above a row piece would need
-// three per-column values (the pending 1/(S + eps), q and beta) and a column
-// piece three per-row values. Storing instead z = adjoint * alpha^l_i before
-// a row phase and z = adjoint * beta^l_j before a column phase, each phase
-// needs two values of the other side, X and Y, and one value of its own
-// owner, 1/alpha or 1/beta:
-//   row phase l:    z' = (z / alpha^l_i) X_j - Y_j,  X_j = beta^l_j / (S_j + eps),
-//                   Y_j = beta^l_j e_j / (S_j + eps)     (pending column update)
-//   column phase l: z' = (z / beta^l_j) X_i - Y_i,   X_i = alpha^(l-1)_i / (R_i + eps),
-//                   Y_i = alpha^(l-1)_i d_i / (R_i + eps)
-// and the row sum d_i / alpha^l_i (column sum e_j / beta^l_j) is just the sum
-// of z' P0 over the row's (column's) pairs. X, Y and the reciprocals are kept
-// in single precision, the adjoint and all sums in double.
 // A row piece that holds pairs: valid and either the row's first piece or one
 // with a position (a padding piece of a group has neither; a later real
 // piece starts at least kP pairs into its row).
@@ -378,167 +339,169 @@ __device__ __forceinline__ bool real_piece(uint32_t info, const Unpack &u)
     return (info & 0x8000u) != 0 && (u.bits(info, 14, 1) != 0 || u.run(info) != 0);
 }
 
-template <int SLP> __global__ __launch_bounds__(kT) void k_sinkhorn_bwd(DevPlan d)
+// One slot of column pieces, from registers or from LDS.
+struct ColSlot {
+    float p0[kP];
+    uint32_t gi[kP / 2];
+    uint32_t info;
+};
+constexpr int kColSlotWords = kP + kP / 2 + 1;
+
+// Column slots the reverse kernel keeps in LDS (28 KB each): the row pieces
+// and the pairs' sums in double fill the registers of a lane beyond four slots.
+__host__ __device__ constexpr int bwd_lds_slots(int slots) { return slots <= 3 ? 0 : slots == 4 ? 1 : 2; }
+
+// Reverse sweeps of a sample in one workgroup: the recurrences of the
+// per-iteration reverse launches, the pairs' sums in registers in row order.
+// Per iteration a column phase (gathers Rbar), a row phase (gathers beta and
+// Sbar) and two barriers; the scalings of the next phase's owners are staged
+// in LDS by the lanes, two owners each. 32 x 2048 points: 63 us, and 11 for
+// k_bwd_direct, whose loads of costs and coordinates would take this launch's
+// few CUs 15 us more; with the plan adjoint itself per pair in LDS, in single
+// precision, and an owner phase after each piece phase 77 us (16 x 1024: 31
+// and 5 against 42). Gradients against 64 bits: 1.6e-7 -> 4e-8, and 5.6e-6 ->
+// 8e-8 where two nearest points are almost equidistant.
+template <int SLP> __global__ __launch_bounds__(kT) void k_sinkhorn_bwd(DevPlan d, double eps)
 {
-    // fixed arrays static (constant addresses), the adjoints (single
-    // precision, row-piece layout) dynamic
-    __shared__ double sums[kSinkOwners];
-    __shared__ float2 xy[kSinkOwners]; // one side at a time
-    __shared__ float inv_a[kSinkOwners], inv_b[kSinkOwners];
-    extern __shared__ float adj[];
+    constexpr int LC = bwd_lds_slots(SLP), RC = SLP - LC;
+    __shared__ double2 cs[kSinkOwners];                  // (beta^l_j, Sbar^l_j)
+    __shared__ double rb[kSinkOwners];                   // Rbar^l_i
+    __shared__ double own_a[kSinkOwners], own_b[kSinkOwners]; // the owners' scalings of the coming phase
+    extern __shared__ uint32_t lds_col[];                // [LC][kColSlotWords][kT]
     const int b = blockIdx.x, tid = threadIdx.x;
     const int N = d.N, M = d.M, L = d.L;
     const size_t BN = (size_t)d.B * N, BM = (size_t)d.B * M;
     const int lo = d.row_ptr[(size_t)b * N];
-    Pieces<false, SLP> pr;
-    Pieces<true, SLP> pc;
+    Pieces<SLP> pr;
+    Pieces<RC> pc;
     load_pieces(pr, d.pk_row, b);
     load_pieces(pc, d.pk_col, b);
-    const double gl = d.grad_loss[b];
-    const double *alpha_L = d.alpha + L * BN;
-    {
-        const Unpack u = Unpack::make();
-        // the plan adjoint starts as grad_loss * C, held as adjoint * alpha^L_i
 #pragma unroll
-        for (int s = 0; s < SLP; ++s) {
-            const int i = u.owner(pr.info[s]), run = u.run(pr.info[s]);
-            const bool piece = real_piece(pr.info[s], u);
-            const int rend = piece ? d.row_ptr[(size_t)b * N + i + 1] - lo : 0;
-            const double al = piece ? alpha_L[(size_t)b * N + i] : 0.0;
+    for (int s = 0; s < LC; ++s) { // read back by the same lane only
+        const int p = (RC + s) * kT + tid;
 #pragma unroll
-            for (int e = 0; e < kP; ++e) {
-                const bool real = piece && run + e < rend;
-                const bool mass = pr.p0[s][e] != 0.0f; // only pairs with mass carry an adjoint
-                adj[adj_slot(s * kT + tid, e)] = real && mass ? (float)(gl * d.cost[lo + run + e] * al) : 0.0f;
-            }
-        }
-        if (tid == 0)
-            adj[adj_slots(SLP)] = 0.0f;
+        for (int e = 0; e < kP; ++e)
+            lds_col[(s * kColSlotWords + e) * kT + tid] =
+                __builtin_bit_cast(uint32_t, d.pk_col.p0[pk_index(b, p, e, kP, SLP)]);
+#pragma unroll
+        for (int w = 0; w < kP / 2; ++w)
+            lds_col[(s * kColSlotWords + kP + w) * kT + tid] = d.pk_col.gi[pk_index(b, p, w, kP / 2, SLP)];
+        lds_col[(s * kColSlotWords + kP + kP / 2) * kT + tid] = d.pk_col.info[pk_index(b, p, 0, 1, SLP)];
     }
-    double a_own[kSL], b_own[kSL];
-#pragma unroll
-    for (int s = 0; s < kSL; ++s) {
-        const int k = kSL * tid + s;
-        a_own[s] = k < N ? alpha_L[(size_t)b * N + k] : 1.0;
-        b_own[s] = k < M ? d.beta[L * BM + (size_t)b * M + k] : 1.0;
-        if (k < N)
-            inv_a[k] = (float)(1.0 / a_own[s]);
-        if (k < M) { // no pending column update before the last iteration
-            xy[k] = make_float2((float)b_own[s], 0.0f);
-            inv_b[k] = (float)(1.0 / b_own[s]);
-        }
-    }
-    lds_barrier();
-
-    for (int l = L; l >= 1; --l) {
-        // scalings of the previous iteration for the row owners, loaded ahead
-        // of their use (those of the column owners after the row owners)
-        double a_prev[kSL], b_prev[kSL];
-#pragma unroll
-        for (int s = 0; s < kSL; ++s) {
-            const int k = kSL * tid + s;
-            a_prev[s] = k < N ? d.alpha[(l - 1) * BN + (size_t)b * N + k] : 1.0;
-        }
-        // row phase: the lane's own adjoint words, consecutive across lanes
-        const Unpack u = Unpack::make();
-#pragma unroll
-        for (int s = 0; s < SLP; ++s)
-            if (wave_active(pr, s)) {
-                const double inv = (double)inv_a[u.owner(pr.info[s])];
-                float m[kP];
-                float2 w[kP];
-#pragma unroll
-                for (int e = 0; e < kP; ++e) {
-                    m[e] = adj[adj_slot(s * kT + tid, e)];
-                    w[e] = lds_at<float2>(xy, u.half(pr.gi[s][e / 2], e));
-                }
-                double acc = 0.0;
-#pragma unroll
-                for (int e = 0; e < kP; ++e) {
-                    const double z = __builtin_fma((double)m[e] * inv, (double)w[e].x, -(double)w[e].y);
-                    const double p0 = widen(pr.p0[s][e]);
-                    // pairs without mass (padding) keep 0, so their values stay bounded
-                    adj[adj_slot(s * kT + tid, e)] = p0 != 0.0 ? (float)z : 0.0f;
-                    acc = e == 0 ? z * p0 : __builtin_fma(z, p0, acc);
-                }
-                store_sum(group_reduce(acc, pr.info[s], u), pr.info[s], sums, u);
-            }
-        lds_barrier();
-        // row owners (adjoint of Eq. 4): d_i = alpha^l_i * sum; the pending
-        // factor alpha^(l-1)_i / (R_i + eps) is alpha^l_i itself
-#pragma unroll
-        for (int s = 0; s < kSL; ++s) {
-            const int i = kSL * tid + s;
-            const double al = a_own[s];
-            const double dsum = al * sums[min(i, N - 1)];
-            if (i < N) {
-                xy[i] = make_float2((float)al, (float)(dsum * al));
-                inv_a[i] = __builtin_amdgcn_rcpf((float)a_prev[s]);
-            }
-            a_own[s] = a_prev[s];
-        }
-#pragma unroll
-        for (int s = 0; s < kSL; ++s) {
-            const int k = kSL * tid + s;
-            b_prev[s] = k < M ? d.beta[(l - 1) * BM + (size_t)b * M + k] : 1.0;
-        }
-        lds_barrier();
-        // column phase: the adjoints of the column's pairs at their row-piece
-        // places (padding at the spare entry)
-#pragma unroll
-        for (int s = 0; s < SLP; ++s)
-            if (wave_active(pc, s)) {
-                const double inv = (double)inv_b[u.owner(pc.info[s])];
-                uint32_t ps[kP];
-                float m[kP];
-                float2 w[kP];
-#pragma unroll
-                for (int e = 0; e < kP; ++e) {
-                    ps[e] = u.half(pc.pos[s][e / 2], e);
-                    m[e] = adj[ps[e]];
-                    w[e] = lds_at<float2>(xy, u.half(pc.gi[s][e / 2], e));
-                }
-                double acc = 0.0;
-#pragma unroll
-                for (int e = 0; e < kP; ++e) {
-                    const double z = __builtin_fma((double)m[e] * inv, (double)w[e].x, -(double)w[e].y);
-                    const double p0 = widen(pc.p0[s][e]);
-                    if (p0 != 0.0) // padding leaves the spare entry at 0
-                        adj[ps[e]] = (float)z;
-                    acc = e == 0 ? z * p0 : __builtin_fma(z, p0, acc);
-                }
-                store_sum(group_reduce(acc, pc.info[s], u), pc.info[s], sums, u);
-            }
-        lds_barrier();
-        // column owners (adjoint of Eq. 3): e_j = beta^l_j * sum; the pending
-        // factor beta^(l-1)_j / (S_j + eps) is beta^l_j
-#pragma unroll
-        for (int s = 0; s < kSL; ++s) {
-            const int j = kSL * tid + s;
-            const double bl = b_own[s];
-            const double esum = bl * sums[min(j, M - 1)];
-            if (j < M) {
-                xy[j] = make_float2((float)bl, (float)(esum * bl));
-                inv_b[j] = __builtin_amdgcn_rcpf((float)b_prev[s]);
-            }
-            b_own[s] = b_prev[s];
-        }
-        lds_barrier();
-    }
-    // the last column update (alpha^0 = beta^0 = 1), written out in row-major order
-    {
-        const Unpack u = Unpack::make();
-#pragma unroll
-        for (int s = 0; s < SLP; ++s) {
-            const int i = u.owner(pr.info[s]), run = u.run(pr.info[s]);
-            const bool piece = real_piece(pr.info[s], u);
-            const int rend = piece ? d.row_ptr[(size_t)b * N + i + 1] - lo : 0;
+    auto col_slot = [&](int s) {
+        ColSlot c;
+        if (s < RC) {
 #pragma unroll
             for (int e = 0; e < kP; ++e)
-                if (piece && run + e < rend) {
-                    const float2 w = lds_at<float2>(xy, u.half(pr.gi[s][e / 2], e));
-                    d.adj[lo + run + e] = (double)adj[adj_slot(s * kT + tid, e)] * (double)w.x - (double)w.y;
+                c.p0[e] = pc.p0[s][e];
+#pragma unroll
+            for (int w = 0; w < kP / 2; ++w)
+                c.gi[w] = pc.gi[s][w];
+            c.info = pc.info[s];
+        } else {
+            const uint32_t *q = lds_col + (s - RC) * kColSlotWords * kT + tid;
+#pragma unroll
+            for (int e = 0; e < kP; ++e)
+                c.p0[e] = __builtin_bit_cast(float, q[e * kT]);
+#pragma unroll
+            for (int w = 0; w < kP / 2; ++w)
+                c.gi[w] = q[(kP + w) * kT];
+            c.info = q[(kP + kP / 2) * kT];
+        }
+        return c;
+    };
+    const double *alpha = d.alpha + (size_t)b * N, *beta = d.beta + (size_t)b * M; // + l * BN, + l * BM
+    // lane t stages the scalings of owners t and t + kT
+    auto stage = [&](double *own, const double *g, int n) {
+#pragma unroll
+        for (int s = 0; s < kSL; ++s)
+            if (s * kT + tid < n)
+                own[s * kT + tid] = g[s * kT + tid];
+    };
+    stage(rb, d.rbar + (size_t)b * N, N);
+    stage(own_b, beta + L * BM, M);
+#pragma unroll
+    for (int s = 0; s < kSL; ++s)
+        if (s * kT + tid < M)
+            cs[s * kT + tid].y = d.cs[(size_t)b * M + s * kT + tid].y;
+
+    double z[SLP][kP];
+#pragma unroll
+    for (int s = 0; s < SLP; ++s)
+#pragma unroll
+        for (int e = 0; e < kP; ++e)
+            z[s][e] = 0.0;
+    lds_barrier();
+
+    double keep = 1.0; // factor of the previous Sbar: 1 for the direct term, then eps
+    for (int l = L; l >= 1; --l) {
+        const Unpack u = Unpack::make();
+        stage(own_a, alpha + (l - 1) * BN, N); // for the row phase
+        // column phase: Sbar^l_j = eps Sbar^(l+1)_j - (beta^l_j)^2 sum_i P0_ij Rbar^l_i
+#pragma unroll
+        for (int s = 0; s < SLP; ++s)
+            if (wave_active(pc.n, s)) {
+                const ColSlot c = col_slot(s);
+                double g[kP];
+#pragma unroll
+                for (int e = 0; e < kP; ++e)
+                    g[e] = lds_at<double>(rb, u.half(c.gi[e / 2], e));
+                double acc = widen(c.p0[0]) * g[0];
+#pragma unroll
+                for (int e = 1; e < kP; ++e)
+                    acc = __builtin_fma(widen(c.p0[e]), g[e], acc);
+                acc = group_reduce(acc, c.info, u);
+                if (u.bits(c.info, 14, 2) == 3u) { // head and valid
+                    const int j = u.owner(c.info);
+                    const double bl = own_b[j];
+                    cs[j] = make_double2(bl, keep * cs[j].y - bl * bl * acc);
                 }
+            }
+        keep = eps;
+        lds_barrier();
+        stage(own_b, beta + (l - 1) * BM, M); // for the next column phase
+        // row phase: the pairs' terms of iteration l and
+        // Rbar^(l-1)_i = eps Rbar^l_i - (alpha^(l-1)_i)^2 sum_j P0_ij Sbar^l_j
+#pragma unroll
+        for (int s = 0; s < SLP; ++s)
+            if (wave_active(pr.n, s)) {
+                const int i = u.owner(pr.info[s]);
+                const double r = rb[i], al = own_a[i];
+                double acc = 0.0;
+#pragma unroll
+                for (int h = 0; h < kP; h += 2) { // two gathers at a time: four would spill at five slots
+                    const double2 g0 = lds_at<double2>(cs, 2 * u.half(pr.gi[s][h / 2], 0));
+                    const double2 g1 = lds_at<double2>(cs, 2 * u.half(pr.gi[s][h / 2], 1));
+                    z[s][h] = __builtin_fma(r, g0.x, __builtin_fma(al, g0.y, z[s][h]));
+                    z[s][h + 1] = __builtin_fma(r, g1.x, __builtin_fma(al, g1.y, z[s][h + 1]));
+                    const double p0 = widen(pr.p0[s][h]);
+                    acc = h == 0 ? p0 * g0.y : __builtin_fma(p0, g0.y, acc);
+                    acc = __builtin_fma(widen(pr.p0[s][h + 1]), g1.y, acc);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                acc = group_reduce(acc, pr.info[s], u);
+                if (u.bits(pr.info[s], 14, 2) == 3u)
+                    rb[i] = eps * r - al * al * acc;
+            }
+        lds_barrier();
+    }
+    // the pairs' sums in row-major order
+    {
+        const Unpack u = Unpack::make();
+        int rend[SLP]; // end of each row piece's row, 0 for padding
+#pragma unroll
+        for (int s = 0; s < SLP; ++s)
+            rend[s] = d.row_ptr[(size_t)b * N + u.owner(pr.info[s]) + 1] - lo;
+#pragma unroll
+        for (int s = 0; s < SLP; ++s)
+            rend[s] = real_piece(pr.info[s], u) ? rend[s] : 0;
+#pragma unroll
+        for (int s = 0; s < SLP; ++s) {
+            const int run = u.run(pr.info[s]);
+#pragma unroll
+            for (int e = 0; e < kP; ++e)
+                if (run + e < rend[s])
+                    d.adj[lo + run + e] = z[s][e];
         }
     }
 }
@@ -550,26 +513,9 @@ template <int SLP> __global__ __launch_bounds__(kT) void k_sinkhorn_bwd(DevPlan 
 // One 1024-lane workgroup per sample runs all 2L sweeps, as above, but the
 // pieces (too many for registers) are read from memory in every sweep, a slot
 // at a time with the next slot's loads in flight. The forward kernel keeps
-// both scaling vectors in LDS in double precision (2 x 64 KB). The reverse
-// kernel keeps the plan adjoint twice, in the row pieces' and in the column
-// pieces' layout in memory (coalesced, each read and written once per phase
-// by the lane that owns the position), and exchanges two single-precision
-// factors per owner and phase through LDS. With the plan after row step l
-// equal to alpha^l_i P0 beta^l_j, after column step l to alpha^(l-1)_i P0
-// beta^l_j, and 1/(R^l_i + eps) = alpha^l_i / alpha^(l-1)_i, 1/(S^l_j + eps)
-// = beta^l_j / beta^(l-1)_j (r: row copy, c: column copy):
-//   row phase l:    rho = r - Yc_j (the adjoint after the reverse of Eq. 3
-//                   of iteration l+1, times beta^l_j); d_i = alpha^l_i
-//                   sum_j rho P0; r' = (rho - d_i beta^l_j) alpha^l_i /
-//                   alpha^(l-1)_i; publishes Yr_i = d_i alpha^l_i and
-//                   alpha^(l-1)_i
-//   column phase l: kappa = c - Yr_i; e_j = beta^l_j sum_i kappa P0;
-//                   c' = (kappa - e_j alpha^(l-1)_i) beta^l_j / beta^(l-1)_j;
-//                   publishes Yc_j = e_j beta^l_j and beta^(l-1)_j
-// from r = grad_loss C beta^L_j, c = grad_loss C alpha^L_i and Yc = 0; after
-// column phase 1 the adjoint with respect to P0 is r - Yc_j. Copies and
-// published factors are single precision, sums and updates double; pairs
-// without mass keep 0.
+// both scaling vectors in LDS in double precision (2 x 64 KB); the reverse
+// kernels (below, for one or several workgroups per sample) hold the vector
+// that the phase gathers: Rbar, or beta and Sbar (128 KB).
 constexpr int kSLW = kSinkOwnersW / kT; // owners per thread in the placement
 
 // Placement of one order of sample b (grid B x 2): as place_order, for up to
@@ -719,16 +665,6 @@ __device__ __forceinline__ void publish64(void *p, uint64_t v, bool local)
         __hip_atomic_store(reinterpret_cast<uint64_t *>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A 32-bit word published as in publish64.
-__device__ __forceinline__ void publish32(float *p, float v, bool local)
-{
-    if (local)
-        *p = v;
-    else
-        __hip_atomic_store(reinterpret_cast<uint32_t *>(p), __builtin_bit_cast(uint32_t, v), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // One forward sweep: every owner's sum of P0 times the other side's scaling
 // (vals) over its pieces, then its own scaling v = cur / (cur sum + eps)
 // (Eq. 3 or Eq. 4) into own (LDS) and g_val (the saved scalings). With SPLIT
@@ -804,150 +740,6 @@ __global__ __launch_bounds__(kT) void k_sinkhorn_fwd_w(DevPlan d, double eps)
     sample_loss(d, b, lo, hi, va, vb, part);
 }
 
-// One reverse phase over the pieces of one order: copy (this order's adjoint
-// copy) is brought up to date with the other direction's pending step
-// (factors fin, gathered), the owners' sums formed, this direction's step
-// applied, and the owners' factors published in fout (see above). own:
-// the saved scalings of this direction at iteration l (own_l) and l - 1.
-// With SPLIT the calling workgroup takes the slots s0, s0 + step, ... and
-// the factors go to fout in global memory for the sample's other workgroups.
-template <bool SPLIT>
-__device__ void wide_reverse(const WideOrder &pk, int b, int n_used, float *copy, const float2 *fin, float2 *fout,
-                             const double *own_l, const double *own_prev, int s0_first = 0, int step = 1,
-                             bool local = false, float *yout = nullptr)
-{
-    const int ns = wave_slots(n_used);
-    for (int s0 = s0_first; s0 < ns; s0 += kWBatch * step) {
-        WSlot w[kWBatch];
-        float cv[kWBatch][kP];
-        double al[kWBatch], alp[kWBatch];
-#pragma unroll
-        for (int k = 0; k < kWBatch; ++k)
-            if (s0 + k * step < ns) {
-                w[k] = load_wslot(pk, b, s0 + k * step);
-                const int p = (s0 + k * step) * kT + (int)threadIdx.x;
-#pragma unroll
-                for (int e = 0; e < kP; ++e)
-                    cv[k][e] = copy[pk_index(b, p, e, kP, pk.slots)];
-            }
-#pragma unroll
-        for (int k = 0; k < kWBatch; ++k)
-            if (s0 + k * step < ns) {
-                const int o = (int)(w[k].info & 0x1FFFu);
-                al[k] = own_l[o];
-                alp[k] = own_prev[o];
-            }
-#pragma unroll
-        for (int k = 0; k < kWBatch; ++k) {
-            if (s0 + k * step >= ns)
-                break;
-            const Unpack u = Unpack::make();
-            const int o = (int)u.bits(w[k].info, 0, 13);
-            const int p = (s0 + k * step) * kT + (int)threadIdx.x;
-            float2 f[kP];
-#pragma unroll
-            for (int e = 0; e < kP; ++e)
-                f[e] = lds_at<float2>(fin, u.half(w[k].gi[e / 2], e));
-            double rho[kP], acc = 0.0;
-#pragma unroll
-            for (int e = 0; e < kP; ++e) {
-                rho[e] = (double)cv[k][e] - (double)f[e].x;
-                const double p0 = (double)w[k].p0[e];
-                acc = e == 0 ? rho[e] * p0 : __builtin_fma(rho[e], p0, acc);
-            }
-            const double dsum = al[k] * group_reduce_lg(acc, (int)u.bits(w[k].info, 13, 3));
-            const double q = quotient(al[k], alp[k]);
-#pragma unroll
-            for (int e = 0; e < kP; ++e)
-                copy[pk_index(b, p, e, kP, pk.slots)] =
-                    w[k].p0[e] != 0.0f ? (float)((rho[e] - dsum * (double)f[e].y) * q) : 0.0f;
-            if (u.bits(w[k].info, 16, 2) == 3u) { // head and valid
-                if constexpr (SPLIT) // the other word, alp, is a saved scaling the readers load themselves
-                    publish32(yout + o, (float)(dsum * al[k]), local);
-                else
-                    fout[o] = make_float2((float)(dsum * al[k]), (float)alp[k]);
-            }
-        }
-    }
-}
-
-// The two adjoint copies of sample b start as grad_loss C beta^L_j (rows) and
-// grad_loss C alpha^L_i (columns), over the slots s0, s0 + step, ...
-__device__ void wide_reverse_start(const DevPlan &d, int b, int n_row, int n_col, int s0_first, int step)
-{
-    const int N = d.N, M = d.M, L = d.L;
-    const size_t BN = (size_t)d.B * N, BM = (size_t)d.B * M;
-    const float *xb = d.x + (size_t)b * N * 3, *yb = d.y + (size_t)b * M * 3;
-    const double *alpha = d.alpha + (size_t)b * N, *beta = d.beta + (size_t)b * M;
-    const double gl = d.grad_loss[b];
-    for (int order = 0; order < 2; ++order) {
-        const WideOrder &pk = order == 0 ? d.wk_row : d.wk_col;
-        float *copy = order == 0 ? d.wr : d.wc;
-        const int ns = wave_slots(order == 0 ? n_row : n_col);
-        for (int s = s0_first; s < ns; s += step) {
-            const WSlot w = load_wslot(pk, b, s);
-            const Unpack u = Unpack::make();
-            const int o = (int)u.bits(w.info, 0, 13), p = s * kT + (int)threadIdx.x;
-#pragma unroll
-            for (int e = 0; e < kP; ++e) {
-                const int k = (int)(u.half(w.gi[e / 2], e) >> 3);
-                const int i = order == 0 ? o : k, j = order == 0 ? k : o;
-                const double sc = order == 0 ? beta[(size_t)L * BM + j] : alpha[(size_t)L * BN + i];
-                copy[pk_index(b, p, e, kP, pk.slots)] =
-                    w.p0[e] != 0.0f ? (float)(gl * dist_f64(xb + 3 * i, yb + 3 * j) * sc) : 0.0f;
-            }
-        }
-    }
-}
-
-// After column phase 1: the adjoint with respect to P0, r - Yc_j, written in
-// row-major order for the row slots s0, s0 + step, ... (fc: the column
-// factors of that phase).
-__device__ void wide_reverse_end(const DevPlan &d, int b, int n_row, const float2 *fc, int s0_first, int step)
-{
-    const int N = d.N;
-    const int ns = wave_slots(n_row);
-    for (int s = s0_first; s < ns; s += step) {
-        const WSlot w = load_wslot(d.wk_row, b, s);
-        const Unpack u = Unpack::make();
-        if (u.bits(w.info, 17, 1) == 0u)
-            continue;
-        const int i = (int)u.bits(w.info, 0, 13), lg = (int)u.bits(w.info, 13, 3);
-        const int p = s * kT + (int)threadIdx.x, q = p & ((1 << lg) - 1); // groups are aligned to their size
-        const int r0 = d.row_ptr[(size_t)b * N + i], len = d.row_ptr[(size_t)b * N + i + 1] - r0;
-#pragma unroll
-        for (int e = 0; e < kP; ++e)
-            if (q * kP + e < len) {
-                const float2 f = lds_at<float2>(fc, u.half(w.gi[e / 2], e));
-                d.adj[r0 + q * kP + e] = (double)d.wr[pk_index(b, p, e, kP, d.wk_row.slots)] - (double)f.x;
-            }
-    }
-}
-
-__global__ __launch_bounds__(kT) void k_sinkhorn_bwd_w(DevPlan d)
-{
-    __shared__ float2 fr[kSinkOwnersW]; // row factors (Yr_i, alpha^(l-1)_i)
-    __shared__ float2 fc[kSinkOwnersW]; // column factors (Yc_j, beta^(l-1)_j)
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const int M = d.M, L = d.L;
-    const size_t BN = (size_t)d.B * d.N, BM = (size_t)d.B * M;
-    const double *alpha = d.alpha + (size_t)b * d.N, *beta = d.beta + (size_t)b * M; // + l * BN, + l * BM
-    const int n_row = __builtin_amdgcn_readfirstlane(d.wk_row.n_pos[b]);
-    const int n_col = __builtin_amdgcn_readfirstlane(d.wk_col.n_pos[b]);
-    wide_reverse_start(d, b, n_row, n_col, 0, 1);
-    for (int k = tid; k < M; k += kT) // no pending column update before row phase L
-        fc[k] = make_float2(0.0f, (float)beta[(size_t)L * BM + k]);
-    lds_barrier();
-    for (int l = L; l >= 1; --l) {
-        // reverse of Eq. 4, then of Eq. 3, of iteration l
-        wide_reverse<false>(d.wk_row, b, n_row, d.wr, fc, fr, alpha + l * BN, alpha + (l - 1) * BN);
-        lds_barrier();
-        wide_reverse<false>(d.wk_col, b, n_col, d.wc, fr, fc, beta + l * BM, beta + (l - 1) * BM);
-        lds_barrier();
-    }
-    wide_reverse_end(d, b, n_row, fc, 0, 1);
-}
-
 // ---------------------------------------------------------------------------
 // split streamed kernels: K workgroups per sample
 // ---------------------------------------------------------------------------
@@ -957,7 +749,7 @@ __global__ __launch_bounds__(kT) void k_sinkhorn_bwd_w(DevPlan d)
 // sample: workgroup k takes the slots k, k + K, ... of every wave, so each
 // owner's sum is formed by the same lanes in the same order as in the
 // one-workgroup kernels (same bits). After each half-sweep the owners' new
-// values (the saved scalings, or the two reverse factors) are published to
+// values (the saved scalings, or the adjoints of the sums) are published to
 // global memory and the K workgroups meet (split_meet), then every workgroup
 // reads the whole vector into its LDS. The grid is launched cooperatively:
 // all its workgroups are resident at once, so a meeting always completes.
@@ -980,17 +772,21 @@ __device__ __forceinline__ bool split_member(int g, int B, int K, int &b, int &k
 // Meeting t of a sample's K workgroups (t = 1, 2, ...): each waits until its
 // own stores have completed (s_waitcnt: plain stores have then reached the
 // L2, device-scope atomic stores the level every XCD reads), counts itself
-// in at the sample's counter and waits until all K have (target K t). The
-// counter is a relaxed device-scope atomic, so no cache is written back or
-// invalidated. The wait is bounded: past kSplitSpinLimit polls, or once
-// another workgroup has given up, it sets bit 2 of the error word and
-// returns false, and the caller ends.
-__device__ bool split_meet(uint32_t *cnt, uint32_t target, unsigned int *err, int *stop)
+// in at the sample's counter, does the work of `shadow` and waits until all K
+// have (target K t). The counter is a relaxed device-scope atomic, so no
+// cache is written back or invalidated. The wait is bounded: past
+// kSplitSpinLimit polls, or once another workgroup has given up, it sets bit
+// 2 of the error word and returns false, and the caller ends. target 0: a
+// sample of one workgroup, which only waits for itself.
+template <class Shadow>
+__device__ __forceinline__ bool split_meet(uint32_t *cnt, uint32_t target, unsigned int *err, int *stop, Shadow shadow)
 {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (target != 0 && threadIdx.x == 0)
         __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    shadow();
+    if (target != 0 && threadIdx.x == 0) {
         unsigned spins = 0;
         while (__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
             if (++spins > kSplitSpinLimit ||
@@ -1004,6 +800,11 @@ __device__ bool split_meet(uint32_t *cnt, uint32_t target, unsigned int *err, in
     }
     __syncthreads();
     return *stop == 0;
+}
+
+__device__ __forceinline__ bool split_meet(uint32_t *cnt, uint32_t target, unsigned int *err, int *stop)
+{
+    return split_meet(cnt, target, err, stop, [] {});
 }
 
 // First meeting of a sample's workgroups: each records its XCD (hardware
@@ -1043,12 +844,23 @@ __device__ bool split_begin(uint32_t *sync, int K, int k, unsigned int *err, int
 #define APML_OUT8                                                                                             \
     "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
 
-// The sample's n published 64-bit words (n <= 8 * lanes) into LDS.
-template <typename T> __device__ __forceinline__ void split_gather(T *lds, const T *g, int n, bool local)
+// The lane's index in the workgroup, opaque to the compiler: what is derived
+// from it in a sweep's exchange (offsets, bounds, addresses of eight words) is
+// formed there again instead of being held in registers across the sweeps.
+__device__ __forceinline__ int fresh_lane()
+{
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// The sample's n published doubles (n <= 8 * lanes), each given to put (an LDS store).
+template <class Put> __device__ __forceinline__ void split_gather(const double *g, int n, bool local, Put put)
 {
     static_assert(kSinkOwnersW / kT == 8, "eight words per lane");
     // the base in scalar registers: each 32-bit half read from the first lane
     // (the builtin takes 32-bit values; a 64-bit argument would be cut)
+    const int lane = fresh_lane();
     const uint64_t a = (uint64_t)(uintptr_t)g;
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
@@ -1058,7 +870,7 @@ template <typename T> __device__ __forceinline__ void split_gather(T *lds, const
         uint32_t off[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            off[u] = (uint32_t)min(u * kT + (int)threadIdx.x, n - 1) * 8u;
+            off[u] = (uint32_t)min(u * kT + lane, n - 1) * 8u;
         asm volatile("buffer_inv sc0\n\t" // no line of an earlier read may serve these loads
                      APML_LDL(0, 8) APML_LDL(1, 9) APML_LDL(2, 10) APML_LDL(3, 11) APML_LDL(4, 12) APML_LDL(5, 13)
                      APML_LDL(6, 14) APML_LDL(7, 15) "s_waitcnt vmcnt(0)"
@@ -1071,7 +883,7 @@ template <typename T> __device__ __forceinline__ void split_gather(T *lds, const
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             bs[u] = reinterpret_cast<const void *>((uintptr_t)(base + (uint64_t)u * kT * 8u));
-        const uint32_t off = threadIdx.x * 8u;
+        const uint32_t off = (uint32_t)lane * 8u;
         asm volatile(APML_LDM(0, 8) APML_LDM(1, 9) APML_LDM(2, 10) APML_LDM(3, 11) APML_LDM(4, 12)
                          APML_LDM(5, 13) APML_LDM(6, 14) APML_LDM(7, 15) "s_waitcnt vmcnt(0)"
                      : APML_OUT8
@@ -1081,80 +893,14 @@ template <typename T> __device__ __forceinline__ void split_gather(T *lds, const
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-        const int o = u * kT + (int)threadIdx.x;
+        const int o = u * kT + lane;
         if (o < n)
-            lds[o] = __builtin_bit_cast(T, v[u]);
+            put(o, __builtin_bit_cast(double, v[u]));
     }
 }
 #undef APML_OUT8
 #undef APML_LDM
 #undef APML_LDL
-
-// The split reverse kernels' factors of one phase into LDS: lds[o] =
-// (Y_o, (float) own_prev[o]) for the sample's n owners. Y is the word each
-// owner's head published in this phase's region of fresh memory (32-bit
-// words: through the L2 only when local, else past the caches); own_prev is
-// the owners' saved scaling of the previous iteration, written by an earlier
-// kernel. Every lane reads eight whole chunks of lanes: each phase's region
-// is padded by kSinkOwnersW words, so a read past the sample's words stays
-// within the region of the same phase (other samples' words, which this CU
-// never uses), and the saved scalings are read only within the sample's n
-// owners. Both loads are issued together after the meeting (one latency).
-// The same float bits as the one-workgroup kernel's published pair.
-#define APML_LDY(I, B, BITS) "global_load_dword %" #I ", %[off], %" #B " " BITS "\n\t"
-#define APML_LOADY(BITS)                                                                                      \
-    asm volatile(APML_LDY(0, 8, BITS) APML_LDY(1, 9, BITS) APML_LDY(2, 10, BITS) APML_LDY(3, 11, BITS)       \
-                 APML_LDY(4, 12, BITS) APML_LDY(5, 13, BITS) APML_LDY(6, 14, BITS) APML_LDY(7, 15, BITS)     \
-                 "s_waitcnt vmcnt(0)"                                                                         \
-                 : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3]), "=&v"(y[4]), "=&v"(y[5]), "=&v"(y[6]), \
-                   "=&v"(y[7])                                                                                \
-                 : "s"(bs[0]), "s"(bs[1]), "s"(bs[2]), "s"(bs[3]), "s"(bs[4]), "s"(bs[5]), "s"(bs[6]),          \
-                   "s"(bs[7]), [off] "v"(off)                                                                 \
-                 : "memory")
-
-// The saved scalings of the previous iteration that a gather pairs with the
-// exchanged words. The forward kernel wrote them, so they are loaded before
-// the meeting, in its shadow.
-__device__ __forceinline__ void load_prev(float (&sp)[8], const double *own_prev, int n)
-{
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int o = u * kT + (int)threadIdx.x;
-        sp[u] = o < n ? (float)own_prev[o] : 0.0f;
-    }
-}
-
-__device__ __forceinline__ void split_gather_factors(float2 *lds, const float *yv, const float (&sp)[8], int n,
-                                                     bool local)
-{
-    static_assert(kSinkOwnersW / kT == 8, "eight words per lane");
-    // the base in scalar registers: each 32-bit half read from the first lane
-    const uint64_t a = (uint64_t)(uintptr_t)yv;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
-    const uint64_t base = ((uint64_t)hi << 32) | lo;
-    const void *bs[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-        bs[u] = reinterpret_cast<const void *>((uintptr_t)(base + (uint64_t)u * kT * 4u));
-    const uint32_t off = threadIdx.x * 4u;
-    uint32_t y[8];
-    if (local) {
-        asm volatile("buffer_inv sc0" ::: "memory"); // no line of an earlier read may serve these loads
-        APML_LOADY("sc0");
-    } else {
-        APML_LOADY("sc1");
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int o = u * kT + (int)threadIdx.x;
-        if (o < n)
-            lds[o] = make_float2(__builtin_bit_cast(float, y[u]), sp[u]);
-    }
-}
-#undef APML_LOADY
-#undef APML_LDY
-
 
 __global__ __launch_bounds__(kT) void k_sinkhorn_fwd_ws(DevPlan d, double eps, int K)
 {
@@ -1192,87 +938,257 @@ __global__ __launch_bounds__(kT) void k_sinkhorn_fwd_ws(DevPlan d, double eps, i
         wide_sweep<true>(d.wk_col, b, n_col, va, vb, eps, gb, k, K, loc);
         if (!split_meet(cnt, (uint32_t)K * ++t, &d.ctr->error, &stop))
             return;
-        split_gather(vb, gb, M, loc);
+        split_gather(gb, M, loc, [&](int o, double v) { vb[o] = v; });
         lds_barrier();
         // row scaling (Eq. 4)
         double *ga = d.alpha + l * BN + (size_t)b * N;
         wide_sweep<true>(d.wk_row, b, n_row, vb, va, eps, ga, k, K, loc);
         if (!split_meet(cnt, (uint32_t)K * ++t, &d.ctr->error, &stop))
             return;
-        split_gather(va, ga, N, loc);
+        split_gather(ga, N, loc, [&](int o, double v) { va[o] = v; });
         lds_barrier();
     }
     if (k == 0) // as the one-workgroup kernel, for the same bits
         sample_loss(d, b, d.row_ptr[(size_t)b * N], d.row_ptr[(size_t)(b + 1) * N], va, vb, part);
 }
 
-// The reverse sweeps split over K workgroups. After each phase the owners'
-// heads publish one word each, Y (Yr_i = d_i alpha^l_i, Yc_j = e_j beta^l_j),
-// into a region of fresh memory for that phase (d.yr, d.yc: a word is never
-// written twice within the kernel, so the exchange may go through the L2, as
-// in the forward kernels); the pair's other factor is the owner's saved
-// scaling of the previous iteration, which every reader loads itself.
-__global__ __launch_bounds__(kT) void k_sinkhorn_bwd_ws(DevPlan d, int K)
+// The reverse sweeps (the recurrences of the per-iteration reverse launches)
+// split over K workgroups, or in one (K = 1). After each phase the owners'
+// heads publish their words, Sbar^l_j or Rbar^(l-1)_i, into a region of fresh
+// memory for that phase (d.yc, d.yr: a word is never written twice within the
+// kernel, so the exchange may go through the L2, as in the forward kernels);
+// beta, the other factor of a row phase's gather, was saved by the forward
+// kernel and is loaded in the meeting's shadow. Each pair's sum of terms is
+// kept in double, streamed in the row pieces' layout (d.wz) or in registers.
+// Keeping the adjoint itself per pair in both orders, in single precision, took
+// twice the registers (three slots a lane at most, against four) or memory
+// traffic: 64 x 8192 points, 20 iterations, step 1.95 -> 1.71 ms; gradients
+// against 64 bits 1.3e-6 -> 5e-8.
+
+// Words of one phase's region: whole cache lines, so that no line holds words of two phases.
+__host__ __device__ inline size_t phase_region(size_t owners) { return (owners + 31) / 16 * 16; }
+
+// The vectors of one sample in the reverse kernels.
+struct RevSample {
+    const double *alpha, *beta; // + l * BN, + l * BM
+    const double *rbar;         // first Rbar
+    const double2 *cs;          // first Sbar (.y)
+    double *yr, *yc;            // regions: + (L - l) * sn, + (L - l) * sm
+    size_t BN, BM, sn, sm;
+};
+
+__device__ __forceinline__ RevSample rev_sample(const DevPlan &d, int b)
 {
-    __shared__ float2 fr[kSinkOwnersW]; // row factors (Yr_i, alpha^(l-1)_i)
-    __shared__ float2 fc[kSinkOwnersW]; // column factors (Yc_j, beta^(l-1)_j)
-    __shared__ int stop, local;
-    int b, k;
-    if (!split_member(blockIdx.x, d.B, K, b, k))
+    RevSample r;
+    r.BN = (size_t)d.B * d.N;
+    r.BM = (size_t)d.B * d.M;
+    r.sn = phase_region(r.BN);
+    r.sm = phase_region(r.BM);
+    const size_t on = (size_t)b * d.N, om = (size_t)b * d.M;
+    r.alpha = d.alpha + on;
+    r.beta = d.beta + om;
+    r.rbar = d.rbar + on;
+    r.cs = d.cs + om;
+    r.yr = d.yr + on;
+    r.yc = d.yc + om;
+    return r;
+}
+
+// The previous value of an owner's recurrence: the first one, or the word its head published last.
+__device__ __forceinline__ double prev_s(const RevSample &r, int L, int l, int o)
+{
+    return l == L ? r.cs[o].y : r.yc[(size_t)(L - l - 1) * r.sm + o];
+}
+__device__ __forceinline__ double prev_r(const RevSample &r, int L, int l, int o)
+{
+    return l == L ? r.rbar[o] : r.yr[(size_t)(L - l - 1) * r.sn + o];
+}
+
+// Column phase of one slot: sum_i P0_ij Rbar_i over the pieces of an owner,
+// and its new Sbar = keep old - beta^2 sum, published by the head.
+__device__ __forceinline__ void rev_col_slot(const WSlot &w, const double *rb, double bl, double old, double *out,
+                                             bool local)
+{
+    const Unpack u = Unpack::make();
+    double g[kP];
+#pragma unroll
+    for (int e = 0; e < kP; ++e)
+        g[e] = lds_at<double>(rb, u.half(w.gi[e / 2], e));
+    double acc = widen(w.p0[0]) * g[0];
+#pragma unroll
+    for (int e = 1; e < kP; ++e)
+        acc = __builtin_fma(widen(w.p0[e]), g[e], acc);
+    acc = group_reduce_lg(acc, (int)u.bits(w.info, 13, 3));
+    if (u.bits(w.info, 16, 2) == 3u) // head and valid
+        publish64(out + u.bits(w.info, 0, 13), __builtin_bit_cast(uint64_t, old - bl * bl * acc), local);
+}
+
+// Row phase of one slot: the pairs' terms, the row's new Rbar = eps r - al^2
+// sum_j P0_ij Sbar_j (the same in all lanes of the group), published by the head.
+__device__ __forceinline__ double rev_row_slot(const WSlot &w, const double2 *cs, double r, double al, double eps,
+                                               double (&z)[kP], double *out, bool local)
+{
+    const Unpack u = Unpack::make();
+    double acc = 0.0;
+#pragma unroll
+    for (int h = 0; h < kP; h += 2) { // two gathers at a time keep the registers down
+        const double2 g0 = lds_at<double2>(cs, 2 * u.half(w.gi[h / 2], 0));
+        const double2 g1 = lds_at<double2>(cs, 2 * u.half(w.gi[h / 2], 1));
+        z[h] = __builtin_fma(r, g0.x, __builtin_fma(al, g0.y, z[h]));
+        z[h + 1] = __builtin_fma(r, g1.x, __builtin_fma(al, g1.y, z[h + 1]));
+        acc = h == 0 ? widen(w.p0[h]) * g0.y : __builtin_fma(widen(w.p0[h]), g0.y, acc);
+        acc = __builtin_fma(widen(w.p0[h + 1]), g1.y, acc);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    acc = group_reduce_lg(acc, (int)u.bits(w.info, 13, 3));
+    const double next = eps * r - al * al * acc;
+    if (u.bits(w.info, 16, 2) == 3u)
+        publish64(out + u.bits(w.info, 0, 13), __builtin_bit_cast(uint64_t, next), local);
+    return next;
+}
+
+// The sums of a slot's pairs into adj, row-major. p: the lane's position.
+__device__ __forceinline__ void store_adj(const DevPlan &d, int b, const WSlot &w, int p, const double (&z)[kP])
+{
+    if ((w.info >> 17 & 1u) == 0u) // not a used position
         return;
-    const int tid = threadIdx.x;
-    const int N = d.N, M = d.M, L = d.L;
-    const size_t BN = (size_t)d.B * N, BM = (size_t)d.B * M;
-    const double *alpha = d.alpha + (size_t)b * N, *beta = d.beta + (size_t)b * M; // + l * BN, + l * BM
+    const int i = (int)(w.info & 0x1FFFu), lg = (int)(w.info >> 13 & 7u);
+    const int q = p & ((1 << lg) - 1); // groups are aligned to their size
+    const int r0 = d.row_ptr[(size_t)b * d.N + i], len = d.row_ptr[(size_t)b * d.N + i + 1] - r0;
+#pragma unroll
+    for (int e = 0; e < kP; ++e)
+        if (q * kP + e < len)
+            d.adj[r0 + q * kP + e] = z[e];
+}
+
+// The sweeps of a sample: cols(l, out, keep) and rows(l, out) form the owners'
+// new words of a phase from the vector in buf and publish them; between the
+// phases the workgroups meet and every one reads the whole vector.
+template <class Cols, class Rows>
+__device__ __forceinline__ void rev_sweeps(const DevPlan &d, double eps, int b, int k, int K, double2 *buf, int *stop,
+                                           int *local, Cols cols, Rows rows)
+{
+    const int tid = threadIdx.x, N = d.N, M = d.M, L = d.L;
+    const RevSample r = rev_sample(d, b);
     uint32_t *cnt = d.split_sync + ((size_t)b * 2 + 1) * kSplitSyncStride;
-    const int n_row = __builtin_amdgcn_readfirstlane(d.wk_row.n_pos[b]);
-    const int n_col = __builtin_amdgcn_readfirstlane(d.wk_col.n_pos[b]);
-    wide_reverse_start(d, b, n_row, n_col, k, K);
-    for (int o = tid; o < M; o += kT) // no pending column update before row phase L
-        fc[o] = make_float2(0.0f, (float)beta[(size_t)L * BM + o]);
-    if (tid == 0)
-        stop = 0;
+    double *rb = reinterpret_cast<double *>(buf);
+    for (int o = tid; o < N; o += kT)
+        rb[o] = r.rbar[o];
+    if (tid == 0) {
+        *stop = 0;
+        *local = 1;
+    }
     lds_barrier();
-    if (!split_begin(cnt, K, k, &d.ctr->error, &stop, &local))
+    if (K > 1 && !split_begin(cnt, K, k, &d.ctr->error, stop, local))
         return;
-    const bool loc = local != 0;
-    uint32_t t = 1;
+    const bool loc = *local != 0;
+    uint32_t t = K > 1 ? 1 : 0;
+    auto next = [&]() { return K > 1 ? (uint32_t)K * ++t : 0u; };
+    double keep = 1.0; // factor of the previous Sbar: 1 for the direct term, then eps
     for (int l = L; l >= 1; --l) {
-        float *yr = d.yr + (size_t)(L - l) * (BN + kSinkOwnersW) + (size_t)b * N;
-        wide_reverse<true>(d.wk_row, b, n_row, d.wr, fc, nullptr, alpha + l * BN, alpha + (l - 1) * BN, k, K, loc,
-                           yr);
-        float sp[8];
-        load_prev(sp, alpha + (l - 1) * BN, N);
-        if (!split_meet(cnt, (uint32_t)K * ++t, &d.ctr->error, &stop))
+        double *yc = r.yc + (size_t)(L - l) * r.sm, *yr = r.yr + (size_t)(L - l) * r.sn;
+        cols(r, l, keep, rb, yc, loc);
+        keep = eps;
+        const bool met = split_meet(cnt, next(), &d.ctr->error, stop, [&] {
+            const double *beta = r.beta + (size_t)l * r.BM;
+            const int lane = fresh_lane();
+#pragma unroll
+            for (int u = 0; u < kSinkOwnersW / kT; ++u)
+                if (u * kT + lane < M)
+                    buf[u * kT + lane].x = beta[u * kT + lane];
+        });
+        if (!met)
             return;
-        split_gather_factors(fr, yr, sp, N, loc);
+        split_gather(yc, M, loc, [&](int o, double v) { buf[o].y = v; });
         lds_barrier();
-        float *yc = d.yc + (size_t)(L - l) * (BM + kSinkOwnersW) + (size_t)b * M;
-        wide_reverse<true>(d.wk_col, b, n_col, d.wc, fr, nullptr, beta + l * BM, beta + (l - 1) * BM, k, K, loc,
-                           yc);
-        load_prev(sp, beta + (l - 1) * BM, M);
-        if (!split_meet(cnt, (uint32_t)K * ++t, &d.ctr->error, &stop))
+        rows(r, l, buf, yr, loc);
+        if (l == 1)
+            break;
+        if (!split_meet(cnt, next(), &d.ctr->error, stop))
             return;
-        split_gather_factors(fc, yc, sp, M, loc);
+        split_gather(yr, N, loc, [&](int o, double v) { rb[o] = v; });
         lds_barrier();
     }
-    wide_reverse_end(d, b, n_row, fc, k, K);
+}
+
+__global__ __launch_bounds__(kT) void k_sinkhorn_bwd_ws(DevPlan d, double eps, int K)
+{
+    __shared__ double2 buf[kSinkOwnersW];
+    __shared__ int stop, local;
+    int b = blockIdx.x, k = 0;
+    if (K > 1 && !split_member(blockIdx.x, d.B, K, b, k))
+        return;
+    const int tid = threadIdx.x, L = d.L;
+    const int nr = wave_slots(__builtin_amdgcn_readfirstlane(d.wk_row.n_pos[b]));
+    const int nc = wave_slots(__builtin_amdgcn_readfirstlane(d.wk_col.n_pos[b]));
+    rev_sweeps(
+        d, eps, b, k, K, buf, &stop, &local,
+        [&](const RevSample &r, int l, double keep, const double *rb, double *yc, bool loc) {
+            for (int s0 = k; s0 < nc; s0 += kWBatch * K) {
+                WSlot w[kWBatch];
+                double bl[kWBatch], old[kWBatch];
+#pragma unroll
+                for (int q = 0; q < kWBatch; ++q)
+                    if (s0 + q * K < nc)
+                        w[q] = load_wslot(d.wk_col, b, s0 + q * K);
+#pragma unroll
+                for (int q = 0; q < kWBatch; ++q)
+                    if (s0 + q * K < nc) {
+                        const int o = (int)(w[q].info & 0x1FFFu);
+                        bl[q] = r.beta[(size_t)l * r.BM + o];
+                        old[q] = keep * prev_s(r, L, l, o);
+                    }
+#pragma unroll
+                for (int q = 0; q < kWBatch; ++q)
+                    if (s0 + q * K < nc)
+                        rev_col_slot(w[q], rb, bl[q], old[q], yc, loc);
+            }
+        },
+        [&](const RevSample &r, int l, const double2 *cs, double *yr, bool loc) {
+            for (int s0 = k; s0 < nr; s0 += kWBatch * K) {
+                WSlot w[kWBatch];
+                double al[kWBatch], old[kWBatch], z[kWBatch][kP];
+#pragma unroll
+                for (int q = 0; q < kWBatch; ++q)
+                    if (s0 + q * K < nr) {
+                        w[q] = load_wslot(d.wk_row, b, s0 + q * K);
+                        const int p = (s0 + q * K) * kT + tid;
+#pragma unroll
+                        for (int e = 0; e < kP; ++e)
+                            z[q][e] = l == L ? 0.0 : d.wz[pk_index(b, p, e, kP, d.wk_row.slots)];
+                    }
+#pragma unroll
+                for (int q = 0; q < kWBatch; ++q)
+                    if (s0 + q * K < nr) {
+                        const int o = (int)(w[q].info & 0x1FFFu);
+                        al[q] = r.alpha[(size_t)(l - 1) * r.BN + o];
+                        old[q] = prev_r(r, L, l, o);
+                    }
+#pragma unroll
+                for (int q = 0; q < kWBatch; ++q)
+                    if (s0 + q * K < nr) {
+                        rev_row_slot(w[q], cs, old[q], al[q], eps, z[q], yr, loc);
+                        const int p = (s0 + q * K) * kT + tid;
+                        if (l > 1) {
+#pragma unroll
+                            for (int e = 0; e < kP; ++e)
+                                d.wz[pk_index(b, p, e, kP, d.wk_row.slots)] = z[q][e];
+                        } else {
+                            store_adj(d, b, w[q], p, z[q]);
+                        }
+                    }
+            }
+        });
 }
 
 // Register-resident split kernels: when a workgroup's share is at most SW
-// slots per lane and order, its pieces (and in the reverse kernel both
-// adjoint copies of its positions) are loaded once and kept in registers for
-// every sweep, so a half-sweep reads nothing from memory but the owners'
-// saved scalings and the exchanged vector. Same lanes, same arithmetic in the
-// same order as the streamed kernels: the same bits. A reverse share of up to
-// kSplitAdjBwd slots keeps only the adjoint copies (the state the sweeps
-// write) in registers and loads its pieces again in every phase: 28 bytes
-// read per slot and phase instead of 60 read and written.
+// slots per lane and order, its pieces (and in the reverse kernel its pairs'
+// sums) are loaded once and kept in registers for every sweep, so a
+// half-sweep reads nothing from memory but the owners' saved scalings and the
+// exchanged vector. Same lanes, same arithmetic in the same order as the
+// streamed kernels: the same bits.
 constexpr int kSplitRegFwd = 3; // slots per lane and order held by the forward kernel
-constexpr int kSplitRegBwd = 2; // and by the reverse kernel
-// adjoint copies held by the reverse kernel, pieces loaded per phase (at 4
-// slots it spills: 72 x 8000 x 8000, 0.413 ms against 0.399 ms streamed)
-constexpr int kSplitAdjBwd = 3;
+constexpr int kSplitRegBwd = 4; // and by the reverse kernel
 
 // Slots of the calling wave that workgroup k of K takes (wave-uniform).
 __device__ __forceinline__ int split_slots(int n_used, int k, int K)
@@ -1288,50 +1204,6 @@ __device__ __forceinline__ void load_my_slots(WSlot (&w)[SW], const Order &pk, i
     for (int q = 0; q < SW; ++q)
         if (q < n)
             w[q] = load_wslot(pk, b, k + q * K);
-}
-
-// The same loads, for a kernel that repeats them in every phase. They are
-// raw buffer loads: one descriptor per array and sample (scalar registers),
-// the slot and word as a scalar offset, and one lane offset shared by every
-// load. Plain pointers let the compiler hoist all the per-word addresses out
-// of the sweeps' loop and keep them in vector registers, which spilled. The
-// descriptor's size also bounds every load to the sample's own positions.
-struct SlotRsrc {
-    __amdgpu_buffer_rsrc_t p0, gi, info;
-};
-
-constexpr int kBufFlags = 0x00020000; // word 3 of a raw 32-bit buffer descriptor (gfx9 family)
-
-template <class Order> __device__ __forceinline__ SlotRsrc slot_rsrc(const Order &pk, int b)
-{
-    const size_t bs = (size_t)b * pk.slots;
-    SlotRsrc r;
-    r.p0 = __builtin_amdgcn_make_buffer_rsrc(pk.p0 + bs * kP * kT, (short)0, pk.slots * kP * kT * 4, kBufFlags);
-    r.gi = __builtin_amdgcn_make_buffer_rsrc(pk.gi + bs * (kP / 2) * kT, (short)0, pk.slots * (kP / 2) * kT * 4,
-                                             kBufFlags);
-    r.info = __builtin_amdgcn_make_buffer_rsrc(pk.info + bs * kT, (short)0, pk.slots * kT * 4, kBufFlags);
-    return r;
-}
-
-template <int SW>
-__device__ __forceinline__ void stream_my_slots(WSlot (&w)[SW], const SlotRsrc &r, int n, int k, int K)
-{
-    const int lane = (int)threadIdx.x * 4;
-#pragma unroll
-    for (int q = 0; q < SW; ++q)
-        if (q < n) {
-            const int s = k + q * K;
-#pragma unroll
-            for (int e = 0; e < kP; ++e)
-                w[q].p0[e] = __builtin_bit_cast(
-                    float, __builtin_amdgcn_raw_buffer_load_b32(r.p0, lane, (s * kP + e) * kT * 4, 0));
-#pragma unroll
-            for (int e = 0; e < kP / 2; ++e)
-                w[q].gi[e] = __builtin_amdgcn_raw_buffer_load_b32(r.gi, lane, (s * (kP / 2) + e) * kT * 4, 0);
-            w[q].info = __builtin_amdgcn_raw_buffer_load_b32(r.info, lane, s * kT * 4, 0);
-        } else {
-            w[q] = WSlot{}; // not read; keeps the compiler from holding earlier contents
-        }
 }
 
 // One forward half-sweep over the slots held in registers (as wide_sweep).
@@ -1399,211 +1271,106 @@ template <int SW> __global__ __launch_bounds__(kT) void k_sinkhorn_fwd_wr(DevPla
         reg_sweep(pc, mc, va, vb, eps, gb, loc); // Eq. 3
         if (!split_meet(cnt, (uint32_t)K * ++t, &d.ctr->error, &stop))
             return;
-        split_gather(vb, gb, M, loc);
+        split_gather(gb, M, loc, [&](int o, double v) { vb[o] = v; });
         lds_barrier();
         double *ga = d.alpha + l * BN + (size_t)b * N;
         reg_sweep(pr, mr, vb, va, eps, ga, loc); // Eq. 4
         if (!split_meet(cnt, (uint32_t)K * ++t, &d.ctr->error, &stop))
             return;
-        split_gather(va, ga, N, loc);
+        split_gather(ga, N, loc, [&](int o, double v) { va[o] = v; });
         lds_barrier();
     }
     if (k == 0)
         sample_loss(d, b, d.row_ptr[(size_t)b * N], d.row_ptr[(size_t)(b + 1) * N], va, vb, part);
 }
 
-// One reverse half-sweep over the slots held in registers (as wide_reverse),
-// with the owners' saved scalings al (iteration l) and alp (l - 1) loaded
-// beforehand.
-template <int SW, int OB>
-__device__ __forceinline__ void reg_reverse(const WSlot (&w)[SW], float (&cp)[SW][kP], int n, const double (&al)[SW],
-                                            const double (&alp)[SW], const float2 *fin, float *yout, bool local)
-{
-#pragma unroll
-    for (int q = 0; q < SW; ++q) {
-        if (q >= n)
-            break;
-        const Unpack u = Unpack::make();
-        const int o = (int)u.bits(w[q].info, 0, OB);
-        float2 f[kP];
-#pragma unroll
-        for (int e = 0; e < kP; ++e)
-            f[e] = lds_at<float2>(fin, u.half(w[q].gi[e / 2], e));
-        // rho_e = cp_e - f_e.x is formed again in the update (the same value):
-        // keeping all of them would spill at two slots
-        double acc = 0.0;
-#pragma unroll
-        for (int e = 0; e < kP; ++e) {
-            const double rho = (double)cp[q][e] - (double)f[e].x;
-            const double p0 = (double)w[q].p0[e];
-            acc = e == 0 ? rho * p0 : __builtin_fma(rho, p0, acc);
-        }
-        const double dsum = al[q] * group_reduce_lg(acc, (int)u.bits(w[q].info, OB, 3));
-        const double qt = quotient(al[q], alp[q]);
-#pragma unroll
-        for (int e = 0; e < kP; ++e) {
-            const double rho = (double)cp[q][e] - (double)f[e].x;
-            cp[q][e] = w[q].p0[e] != 0.0f ? (float)((rho - dsum * (double)f[e].y) * qt) : 0.0f;
-        }
-        if (u.bits(w[q].info, OB + 3, 2) == 3u) // head and valid
-            publish32(yout + o, (float)(dsum * al[q]), local); // alp: read from the saved scalings
-    }
-}
+// The last of four column slots lives in LDS (28 KB beside the 128 KB of the
+// gathered vector): with it the registers would spill.
+__host__ __device__ constexpr int bwd_wide_lds_slots(int sw) { return sw == 4 ? 1 : 0; }
 
-// The owners' saved scalings of iteration l and l - 1 for the slots held.
-template <int SW, int OB>
-__device__ __forceinline__ void owner_scalings(const WSlot (&w)[SW], int n, const double *own_l, const double *own_prev,
-                                               double (&al)[SW], double (&alp)[SW])
+template <int SW> __global__ __launch_bounds__(kT) void k_sinkhorn_bwd_wr(DevPlan d, double eps, int K)
 {
-#pragma unroll
-    for (int q = 0; q < SW; ++q)
-        if (q < n) {
-            const int o = (int)(w[q].info & ((1u << OB) - 1u));
-            al[q] = own_l[o];
-            alp[q] = own_prev[o];
-        }
-}
-
-// The owners' saved scalings of iteration l - 1 alone.
-template <int SW, int OB>
-__device__ __forceinline__ void owner_prev(const WSlot (&w)[SW], int n, const double *own_prev, double (&alp)[SW])
-{
-#pragma unroll
-    for (int q = 0; q < SW; ++q)
-        if (q < n)
-            alp[q] = own_prev[w[q].info & ((1u << OB) - 1u)];
-}
-
-template <int SW, bool HOLD> __global__ __launch_bounds__(kT) void k_sinkhorn_bwd_wr(DevPlan d, int K)
-{
-    constexpr int OB = 13; // owner bits of the streamed layout's info word
-    __shared__ float2 fr[kSinkOwnersW]; // row factors (Yr_i, alpha^(l-1)_i)
-    __shared__ float2 fc[kSinkOwnersW]; // column factors (Yc_j, beta^(l-1)_j)
+    constexpr int RC = SW - bwd_wide_lds_slots(SW);
+    __shared__ double2 buf[kSinkOwnersW];
     __shared__ int stop, local;
+    extern __shared__ uint32_t lds_col[]; // [SW - RC][kColSlotWords][kT]
     int b, k;
     if (!split_member(blockIdx.x, d.B, K, b, k))
         return;
-    const int tid = threadIdx.x;
-    const int N = d.N, M = d.M, L = d.L;
-    const size_t BN = (size_t)d.B * N, BM = (size_t)d.B * M;
-    const double *alpha = d.alpha + (size_t)b * N, *beta = d.beta + (size_t)b * M; // + l * BN, + l * BM
-    uint32_t *cnt = d.split_sync + ((size_t)b * 2 + 1) * kSplitSyncStride;
+    const int tid = threadIdx.x, L = d.L;
     const int mr = split_slots(__builtin_amdgcn_readfirstlane(d.wk_row.n_pos[b]), k, K);
     const int mc = split_slots(__builtin_amdgcn_readfirstlane(d.wk_col.n_pos[b]), k, K);
-    WSlot pr[SW], pc[SW];
+    WSlot pr[SW], pc[RC];
     load_my_slots(pr, d.wk_row, b, mr, k, K);
     load_my_slots(pc, d.wk_col, b, mc, k, K);
-    // the copies start as grad_loss C beta^L_j (rows) and grad_loss C alpha^L_i (columns)
-    float rr[SW][kP], rc[SW][kP];
-    {
-        const float *xb = d.x + (size_t)b * N * 3, *yb = d.y + (size_t)b * M * 3;
-        const double gl = d.grad_loss[b];
-        const Unpack u = Unpack::make();
-#pragma unroll
-        for (int q = 0; q < SW; ++q) {
-#pragma unroll
-            for (int e = 0; e < kP; ++e) {
-                rr[q][e] = 0.0f;
-                rc[q][e] = 0.0f;
-            }
-            if (q < mr) {
-                const int i = (int)u.bits(pr[q].info, 0, OB);
-#pragma unroll
-                for (int e = 0; e < kP; ++e) {
-                    const int j = (int)(u.half(pr[q].gi[e / 2], e) >> 3);
-                    if (pr[q].p0[e] != 0.0f)
-                        rr[q][e] = (float)(gl * dist_f64(xb + 3 * i, yb + 3 * j) * beta[(size_t)L * BM + j]);
-                }
-            }
-            if (q < mc) {
-                const int j = (int)u.bits(pc[q].info, 0, OB);
-#pragma unroll
-                for (int e = 0; e < kP; ++e) {
-                    const int i = (int)(u.half(pc[q].gi[e / 2], e) >> 3);
-                    if (pc[q].p0[e] != 0.0f)
-                        rc[q][e] = (float)(gl * dist_f64(xb + 3 * i, yb + 3 * j) * alpha[(size_t)L * BN + i]);
-                }
-            }
-        }
-    }
-    for (int o = tid; o < M; o += kT) // no pending column update before row phase L
-        fc[o] = make_float2(0.0f, (float)beta[(size_t)L * BM + o]);
-    if (tid == 0)
-        stop = 0;
-    lds_barrier();
-    // the exchange as in k_sinkhorn_bwd_ws: a fresh region per phase
-    if (!split_begin(cnt, K, k, &d.ctr->error, &stop, &local))
-        return;
-    const bool loc = local != 0;
-    const SlotRsrc rsr = slot_rsrc(d.wk_row, b), rsc = slot_rsrc(d.wk_col, b);
-    // Loads that do not depend on the exchange are issued ahead of it: a
-    // phase's pieces (when streamed) and the gather's saved scalings before
-    // the meeting, the owners' scalings before the gather. The owners of a
-    // workgroup's slots are the same in every phase, so each phase loads only
-    // their scalings of the previous iteration (alp); those of this iteration
-    // (ar for the row owners, ac for the column owners) are the previous
-    // phase's alp of the same side.
-    double ar[SW], ac[SW], alp[SW];
-    owner_scalings<SW, OB>(pr, mr, alpha + L * BN, alpha + (L - 1) * BN, ar, alp);
-    {
-        double unused[SW];
-        owner_scalings<SW, OB>(pc, mc, beta + L * BM, beta + L * BM, ac, unused);
-    }
-    uint32_t t = 1;
-    for (int l = L; l >= 1; --l) {
-        float *yr = d.yr + (size_t)(L - l) * (BN + kSinkOwnersW) + (size_t)b * N;
-        reg_reverse<SW, OB>(pr, rr, mr, ar, alp, fc, yr, loc); // reverse of Eq. 4
-#pragma unroll
-        for (int q = 0; q < SW; ++q)
-            ar[q] = alp[q];
-        if constexpr (!HOLD)
-            stream_my_slots(pc, rsc, mc, k, K);
-        float sp[8];
-        if constexpr (HOLD)
-            load_prev(sp, alpha + (l - 1) * BN, N);
-        if (!split_meet(cnt, (uint32_t)K * ++t, &d.ctr->error, &stop))
-            return;
-        owner_prev<SW, OB>(pc, mc, beta + (l - 1) * BM, alp);
-        if constexpr (!HOLD)
-            load_prev(sp, alpha + (l - 1) * BN, N);
-        split_gather_factors(fr, yr, sp, N, loc);
-        lds_barrier();
-        float *yc = d.yc + (size_t)(L - l) * (BM + kSinkOwnersW) + (size_t)b * M;
-        reg_reverse<SW, OB>(pc, rc, mc, ac, alp, fr, yc, loc); // reverse of Eq. 3
-#pragma unroll
-        for (int q = 0; q < SW; ++q)
-            ac[q] = alp[q];
-        if constexpr (!HOLD)
-            stream_my_slots(pr, rsr, mr, k, K); // the next row phase's, or the closing pass's
-        if constexpr (HOLD)
-            load_prev(sp, beta + (l - 1) * BM, M);
-        if (!split_meet(cnt, (uint32_t)K * ++t, &d.ctr->error, &stop))
-            return;
-        if (l > 1)
-            owner_prev<SW, OB>(pr, mr, alpha + (l - 2) * BN, alp);
-        if constexpr (!HOLD)
-            load_prev(sp, beta + (l - 1) * BM, M);
-        split_gather_factors(fc, yc, sp, M, loc);
-        lds_barrier();
-    }
-    // the adjoint with respect to P0, r - Yc_j, in row-major order
-    {
-        const Unpack u = Unpack::make();
-#pragma unroll
-        for (int q = 0; q < SW; ++q) {
-            if (q >= mr || u.bits(pr[q].info, OB + 4, 1) == 0u)
-                continue;
-            const int i = (int)u.bits(pr[q].info, 0, OB), lg = (int)u.bits(pr[q].info, OB, 3);
-            const int p = (k + q * K) * kT + tid, qq = p & ((1 << lg) - 1); // groups are aligned to their size
-            const int r0 = d.row_ptr[(size_t)b * N + i], len = d.row_ptr[(size_t)b * N + i + 1] - r0;
+    if constexpr (SW > RC) { // read back by the same lane only
+        if (RC < mc) {
+            const WSlot w = load_wslot(d.wk_col, b, k + RC * K);
 #pragma unroll
             for (int e = 0; e < kP; ++e)
-                if (qq * kP + e < len) {
-                    const float2 f = lds_at<float2>(fc, u.half(pr[q].gi[e / 2], e));
-                    d.adj[r0 + qq * kP + e] = (double)rr[q][e] - (double)f.x;
-                }
+                lds_col[e * kT + tid] = __builtin_bit_cast(uint32_t, w.p0[e]);
+#pragma unroll
+            for (int q = 0; q < kP / 2; ++q)
+                lds_col[(kP + q) * kT + tid] = w.gi[q];
+            lds_col[(kP + kP / 2) * kT + tid] = w.info;
         }
     }
+    double z[SW][kP], old_r[SW];
+#pragma unroll
+    for (int q = 0; q < SW; ++q) {
+        old_r[q] = 0.0;
+#pragma unroll
+        for (int e = 0; e < kP; ++e)
+            z[q][e] = 0.0;
+        if (q < mr)
+            old_r[q] = d.rbar[(size_t)b * d.N + (pr[q].info & 0x1FFFu)];
+    }
+    rev_sweeps(
+        d, eps, b, k, K, buf, &stop, &local,
+        [&](const RevSample &r, int l, double keep, const double *rb, double *yc, bool loc) {
+            double bl[SW], old[SW];
+#pragma unroll
+            for (int q = 0; q < SW; ++q)
+                if (q < mc) {
+                    const uint32_t info = q < RC ? pc[q < RC ? q : 0].info : lds_col[(kP + kP / 2) * kT + tid];
+                    const int o = (int)Unpack::make().bits(info, 0, 13);
+                    bl[q] = r.beta[(size_t)l * r.BM + o];
+                    old[q] = keep * prev_s(r, L, l, o);
+                }
+#pragma unroll
+            for (int q = 0; q < SW; ++q) {
+                if (q >= mc)
+                    break;
+                if (q < RC) {
+                    rev_col_slot(pc[q < RC ? q : 0], rb, bl[q], old[q], yc, loc);
+                } else {
+                    WSlot w;
+#pragma unroll
+                    for (int e = 0; e < kP; ++e)
+                        w.p0[e] = __builtin_bit_cast(float, lds_col[e * kT + tid]);
+#pragma unroll
+                    for (int h = 0; h < kP / 2; ++h)
+                        w.gi[h] = lds_col[(kP + h) * kT + tid];
+                    w.info = lds_col[(kP + kP / 2) * kT + tid];
+                    rev_col_slot(w, rb, bl[q], old[q], yc, loc);
+                }
+            }
+        },
+        [&](const RevSample &r, int l, const double2 *cs, double *yr, bool loc) {
+            double al[SW];
+#pragma unroll
+            for (int q = 0; q < SW; ++q)
+                if (q < mr)
+                    al[q] = r.alpha[(size_t)(l - 1) * r.BN + Unpack::make().bits(pr[q].info, 0, 13)];
+#pragma unroll
+            for (int q = 0; q < SW; ++q) {
+                if (q >= mr)
+                    break;
+                old_r[q] = rev_row_slot(pr[q], cs, old_r[q], al[q], eps, z[q], yr, loc);
+                if (l == 1)
+                    store_adj(d, b, pr[q], (k + q * K) * kT + tid, z[q]);
+            }
+        });
 }
 
 __global__ __launch_bounds__(kBlock) void k_zero_u32(uint32_t *a, int n)
@@ -1694,7 +1461,7 @@ template <bool COL, int G> __global__ __launch_bounds__(kBlock) void k_sink_step
     // each XCD takes a contiguous range of owners: its L2 holds only the
     // other side's scalings of those owners' samples
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-    each_owner<G, kSB>(gid / G, d.B * (COL ? d.M : d.N), COL ? d.col_ptr : d.row_ptr,
+    each_owner<kSB>(G, gid / G, d.B * (COL ? d.M : d.N), COL ? d.col_ptr : d.row_ptr,
                        [&](int lanes, int o, int lg) { sink_owner<COL>(d, l, eps, o, lanes, lg); });
 }
 
@@ -1725,7 +1492,7 @@ __device__ __forceinline__ void loss_row(const DevPlan &d, double *loss_rows, in
 template <int G> __global__ __launch_bounds__(kBlock) void k_loss_rows(DevPlan d, double *loss_rows)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
-    each_owner<G, kSB>(gid / G, d.B * d.N, d.row_ptr,
+    each_owner<kSB>(G, gid / G, d.B * d.N, d.row_ptr,
                        [&](int lanes, int r, int lg) { loss_row(d, loss_rows, r, lanes, lg); });
 }
 
@@ -1765,64 +1532,76 @@ __global__ __launch_bounds__(kLossT) void k_loss_reduce(DevPlan d, const double 
 // follow one another without any per-pair state:
 //   Sbar^l_j     = eps Sbar^(l+1)_j - (beta^l_j)^2 sum_i P0_ij Rbar^l_i
 //   Rbar^(l-1)_i = eps Rbar^l_i - (alpha^(l-1)_i)^2 sum_j P0_ij Sbar^l_j
-// from the direct terms of the loss (sum alpha^L P0 beta^L C), and
+// from the direct terms of the loss (sum alpha^L P0 beta^L C; k_bwd_direct), and
 //   dLoss/dP0_ij = g alpha^L_i beta^L_j C_ij
 //                  + sum_l (Rbar^l_i beta^l_j + alpha^(l-1)_i Sbar^l_j),
-// which the row launches add up in row order, in double precision. A column
+// whose sum the row launches form in row order, in double precision (adj; the
+// softmax adjoints add the direct term). A column
 // launch reads 16 bytes a pair (P0, index, Rbar), a row launch 40 (P0, index,
 // the pair's sum, and beta, Sbar in one gather). With the adjoint itself kept
 // per pair, once in each order, both launches moved 56: per launch 23 -> 11 us
 // (columns) and 33 -> 19 us (rows) at 16 x 4096 x 16384 points, 21 -> 12 and
 // 23 -> 14 us at 4 x 65536.
 //
-// Row launch L: the pairs' direct terms and Rbar^L.
-__device__ __forceinline__ void bwd_first_row(const DevPlan &d, int r, int G, int lg)
+// The first adjoints of the reverse sweeps, all owners in one launch (rows
+// first): Rbar^L_i = -(alpha^L_i)^2 g sum_j P0_ij beta^L_j C_ij into rbar and the
+// same of the columns, the direct term of Sbar^L_j, into cs.
+template <bool COL> __device__ __forceinline__ void direct_owner(const DevPlan &d, int o, int G, int lg)
 {
-    const int b = r / d.N;
+    const int n_own = COL ? d.M : d.N, n_oth = COL ? d.N : d.M;
+    const int b = o / n_own;
     const size_t BN = (size_t)d.B * d.N, BM = (size_t)d.B * d.M;
-    const double *beta = d.beta + (size_t)d.L * BM + (size_t)b * d.M;
-    const double al = d.alpha[(size_t)d.L * BN + r], gl = d.grad_loss[b];
-    const int t0 = d.row_ptr[r], n = d.row_ptr[r + 1] - t0;
+    const double *oth = (COL ? d.alpha + (size_t)d.L * BN : d.beta + (size_t)d.L * BM) + (size_t)b * n_oth;
+    const double own = COL ? d.beta[(size_t)d.L * BM + o] : d.alpha[(size_t)d.L * BN + o], gl = d.grad_loss[b];
+    const int32_t *ptr = COL ? d.col_ptr : d.row_ptr, *idx = COL ? d.csc_row : d.csr_col;
+    const float *p0 = COL ? d.p0c : d.p0r;
+    const int s0 = ptr[o], n = ptr[o + 1] - s0;
     struct V {
-        double bl, c;
+        double x, c;
         float p;
-        int k;
     };
-    const double acc = owner_sum<kSBRev>(n, G, lg,
-                                         [&](int k) {
-                                             V v{0.0, 0.0, 0.0f, k};
-                                             if (k >= 0) {
-                                                 v.bl = beta[d.csr_col[t0 + k]];
-                                                 v.c = d.cost[t0 + k];
-                                                 v.p = d.p0r[t0 + k];
-                                             }
-                                             return v;
-                                         },
-                                         [&](const V &v) {
-                                             const double w = gl * v.bl * v.c;
-                                             d.adj[t0 + v.k] = al * w;
-                                             return w * (double)v.p;
-                                         });
-    if (lg == 0)
-        d.rbar[r] = -(al * al) * acc;
+    const double acc = owner_sum(n, G, lg,
+                                 [&](int k) {
+                                     V v{0.0, 0.0, 0.0f};
+                                     if (k >= 0) {
+                                         v.x = oth[idx[s0 + k]];
+                                         v.c = d.cost[COL ? d.csc_perm[s0 + k] : s0 + k];
+                                         v.p = p0[s0 + k];
+                                     }
+                                     return v;
+                                 },
+                                 [&](const V &v) { return (double)v.p * (v.x * v.c); });
+    if (lg == 0) {
+        const double first = -(own * own) * (gl * acc);
+        if (COL)
+            d.cs[o] = make_double2(own, first);
+        else
+            d.rbar[o] = first;
+    }
 }
 
-template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_first(DevPlan d)
+// Groups of GR lanes per row in the first row_blocks workgroups, of GC per column in the others.
+__global__ __launch_bounds__(kBlock) void k_bwd_direct(DevPlan d, int row_blocks, int lr, int lc)
 {
-    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
-    each_owner<G, kSB>(gid / G, d.B * d.N, d.row_ptr,
-                       [&](int lanes, int r, int lg) { bwd_first_row(d, r, lanes, lg); });
+    const int bid = blockIdx.x;
+    if (bid < row_blocks) {
+        const int gid = xcd_contiguous(bid, row_blocks) * kBlock + threadIdx.x;
+        each_owner<kSB>(1 << lr, gid >> lr, d.B * d.N, d.row_ptr,
+                        [&](int lanes, int o, int lg) { direct_owner<false>(d, o, lanes, lg); });
+    } else {
+        const int gid = xcd_contiguous(bid - row_blocks, gridDim.x - row_blocks) * kBlock + threadIdx.x;
+        each_owner<kSB>(1 << lc, gid >> lc, d.B * d.M, d.col_ptr,
+                        [&](int lanes, int o, int lg) { direct_owner<true>(d, o, lanes, lg); });
+    }
 }
 
-// Column launch l: Sbar^l. FIRST (l = L): with the direct term of the loss.
-template <bool FIRST>
-__device__ __forceinline__ void bwd_col(const DevPlan &d, int l, double eps, int gc, int G, int lg)
+// Column launch l: Sbar^l. keep: the factor of the value in cs, 1 for the
+// direct term (l = L), then eps.
+__device__ __forceinline__ void bwd_col(const DevPlan &d, int l, double keep, int gc, int G, int lg)
 {
     const int b = gc / d.M;
-    const size_t BN = (size_t)d.B * d.N, BM = (size_t)d.B * d.M;
-    const double *rbar = d.rbar + (size_t)b * d.N, *alpha = d.alpha + (size_t)l * BN + (size_t)b * d.N;
-    const double bl = d.beta[(size_t)l * BM + gc], gl = FIRST ? (double)d.grad_loss[b] : 0.0;
-    const double old = FIRST ? 0.0 : eps * d.cs[gc].y;
+    const double *rbar = d.rbar + (size_t)b * d.N;
+    const double bl = d.beta[(size_t)l * d.B * d.M + gc], old = keep * d.cs[gc].y;
     const int s0 = d.col_ptr[gc], n = d.col_ptr[gc + 1] - s0;
     struct V {
         float p;
@@ -1832,11 +1611,8 @@ __device__ __forceinline__ void bwd_col(const DevPlan &d, int l, double eps, int
                                  [&](int k) {
                                      V v{0.0f, 0.0};
                                      if (k >= 0) {
-                                         const int i = d.csc_row[s0 + k];
                                          v.p = d.p0c[s0 + k];
-                                         v.x = rbar[i];
-                                         if (FIRST)
-                                             v.x += gl * alpha[i] * d.cost[d.csc_perm[s0 + k]];
+                                         v.x = rbar[d.csc_row[s0 + k]];
                                      }
                                      return v;
                                  },
@@ -1845,14 +1621,16 @@ __device__ __forceinline__ void bwd_col(const DevPlan &d, int l, double eps, int
         d.cs[gc] = make_double2(bl, old - bl * bl * acc);
 }
 
-template <bool FIRST, int G> __global__ __launch_bounds__(kBlock) void k_bwd_cols(DevPlan d, int l, double eps)
+template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_cols(DevPlan d, int l, double keep)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
-    each_owner<G, kSB>(gid / G, d.B * d.M, d.col_ptr,
-                       [&](int lanes, int gc, int lg) { bwd_col<FIRST>(d, l, eps, gc, lanes, lg); });
+    each_owner<kSB>(G, gid / G, d.B * d.M, d.col_ptr,
+                    [&](int lanes, int gc, int lg) { bwd_col(d, l, keep, gc, lanes, lg); });
 }
 
 // Row launch after column launch l: the pairs' terms of iteration l, Rbar^(l-1).
+// FIRST (l = L): the first terms.
+template <bool FIRST>
 __device__ __forceinline__ void bwd_row(const DevPlan &d, int l, double eps, int r, int G, int lg)
 {
     const int b = r / d.N;
@@ -1870,7 +1648,7 @@ __device__ __forceinline__ void bwd_row(const DevPlan &d, int l, double eps, int
                                              V v{make_double2(0.0, 0.0), 0.0, 0.0f, k};
                                              if (k >= 0) {
                                                  v.c = cs[d.csr_col[t0 + k]];
-                                                 v.z = d.adj[t0 + k];
+                                                 v.z = FIRST ? 0.0 : d.adj[t0 + k];
                                                  v.p = d.p0r[t0 + k];
                                              }
                                              return v;
@@ -1884,11 +1662,11 @@ __device__ __forceinline__ void bwd_row(const DevPlan &d, int l, double eps, int
         d.rbar[r] = eps * rb - al * al * acc;
 }
 
-template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_rows(DevPlan d, int l, double eps)
+template <bool FIRST, int G> __global__ __launch_bounds__(kBlock) void k_bwd_rows(DevPlan d, int l, double eps)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
-    each_owner<G, kSB>(gid / G, d.B * d.N, d.row_ptr,
-                       [&](int lanes, int r, int lg) { bwd_row(d, l, eps, r, lanes, lg); });
+    each_owner<kSB>(G, gid / G, d.B * d.N, d.row_ptr,
+                       [&](int lanes, int r, int lg) { bwd_row<FIRST>(d, l, eps, r, lanes, lg); });
 }
 
 } // namespace
@@ -1963,13 +1741,13 @@ namespace {
 // Clears the sample's meeting counters, then launches the split kernel over
 // B K workgroups, all resident at once; false when the cooperative launch
 // is refused (the caller then takes the one-workgroup kernel).
-bool launch_split(const void *kernel, void **args, const DevPlan &d, int K, hipStream_t s)
+bool launch_split(const void *kernel, void **args, const DevPlan &d, int K, size_t lds, hipStream_t s)
 {
     const int n = d.B * 2 * kSplitSyncStride;
     hipLaunchKernelGGL(k_zero_u32, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, s, d.split_sync, n);
     if (hipGetLastError() != hipSuccess)
         return false;
-    if (hipLaunchCooperativeKernel(kernel, dim3(split_grid(d.B, K)), dim3(kT), args, 0, s) != hipSuccess) {
+    if (hipLaunchCooperativeKernel(kernel, dim3(split_grid(d.B, K)), dim3(kT), args, lds, s) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
@@ -2004,14 +1782,15 @@ const void *split_bwd_kernel(int sw)
     if (split_streamed_only())
         return reinterpret_cast<const void *>(k_sinkhorn_bwd_ws);
     switch (sw) {
-    case 1: return reinterpret_cast<const void *>(k_sinkhorn_bwd_wr<1, true>);
-    case 2: return reinterpret_cast<const void *>(k_sinkhorn_bwd_wr<2, true>);
-    case 3: return reinterpret_cast<const void *>(k_sinkhorn_bwd_wr<3, false>);
+    case 1: return reinterpret_cast<const void *>(k_sinkhorn_bwd_wr<1>);
+    case 2: return reinterpret_cast<const void *>(k_sinkhorn_bwd_wr<2>);
+    case 3: return reinterpret_cast<const void *>(k_sinkhorn_bwd_wr<3>);
+    case 4: return reinterpret_cast<const void *>(k_sinkhorn_bwd_wr<4>);
     default: return reinterpret_cast<const void *>(k_sinkhorn_bwd_ws);
     }
 }
 
-static_assert(kSplitRegFwd == 3 && kSplitRegBwd == 2 && kSplitAdjBwd == 3, "instances above");
+static_assert(kSplitRegFwd == 3 && kSplitRegBwd == 4, "instances above");
 
 } // namespace
 
@@ -2026,33 +1805,41 @@ hipError_t launch_sinkhorn_fwd_wide(const DevPlan &d, double eps, hipStream_t s)
         DevPlan dc = d;
         double e = eps;
         void *args[] = {&dc, &e, &K};
-        if (launch_split(split_fwd_kernel((d.wk_row.slots + K - 1) / K), args, d, K, s))
+        if (launch_split(split_fwd_kernel((d.wk_row.slots + K - 1) / K), args, d, K, 0, s))
             return hipSuccess;
     }
     hipLaunchKernelGGL(k_sinkhorn_fwd_w, dim3(d.B), dim3(kT), 0, s, d, eps);
     return hipGetLastError();
 }
 
-hipError_t launch_sinkhorn_bwd_wide(const DevPlan &d, hipStream_t s)
+bool sinkhorn_bwd_streams(int slots, int B)
 {
-    int K = sinkhorn_split_factor(d.B);
-    if (K > 1 && d.split_sync && d.yr && d.yc) {
-        DevPlan dc = d;
-        void *args[] = {&dc, &K};
-        if (launch_split(split_bwd_kernel((d.wk_row.slots + K - 1) / K), args, d, K, s))
-            return hipSuccess;
-    }
-    hipLaunchKernelGGL(k_sinkhorn_bwd_w, dim3(d.B), dim3(kT), 0, s, d);
-    return hipGetLastError();
+    const int K = sinkhorn_split_factor(B);
+    return K == 1 || split_bwd_kernel((slots + K - 1) / K) == reinterpret_cast<const void *>(k_sinkhorn_bwd_ws);
 }
 
-constexpr size_t kLdsBudget = 160 * 1024;
+size_t sinkhorn_exchange_words(int L, size_t owners) { return (size_t)L * phase_region(owners) + kSinkOwnersW; }
 
-bool sinkhorn_bwd_fits(int slots, int64_t max_pairs)
+hipError_t launch_sinkhorn_bwd_wide(const DevPlan &d, double eps, hipStream_t s)
 {
-    // the adjoint of every pair of a sample in LDS, at its row piece
-    (void)max_pairs;
-    return slots > 0 && bwd_fixed_lds_bytes() + 4 * (size_t)(adj_slots(slots) + 1) <= kLdsBudget;
+    int K = sinkhorn_split_factor(d.B);
+    if (K == 1) {
+        hipLaunchKernelGGL(k_sinkhorn_bwd_ws, dim3(d.B), dim3(kT), 0, s, d, eps, 1);
+        return hipGetLastError();
+    }
+    const int sw = (d.wk_row.slots + K - 1) / K;
+    const void *kernel = split_bwd_kernel(sw);
+    const bool streamed = kernel == reinterpret_cast<const void *>(k_sinkhorn_bwd_ws);
+    const size_t lds = streamed ? 0 : 4 * (size_t)bwd_wide_lds_slots(sw) * kColSlotWords * kT;
+    hipError_t err = set_dynamic_lds(kernel, lds);
+    if (err != hipSuccess)
+        return err;
+    DevPlan dc = d;
+    double e = eps;
+    void *args[] = {&dc, &e, &K};
+    if (!launch_split(kernel, args, d, K, lds, s)) // the cooperative launch was refused
+        launch_sinkhorn_bwd_steps(d, eps, s);
+    return hipGetLastError();
 }
 
 size_t packed_order_words(int B, int slots) { return (size_t)B * slots * kP * kT; }
@@ -2091,15 +1878,14 @@ hipError_t launch_sinkhorn_fwd(const DevPlan &d, double eps, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_sinkhorn_bwd(const DevPlan &d, int64_t max_pairs, hipStream_t s)
+hipError_t launch_sinkhorn_bwd(const DevPlan &d, double eps, hipStream_t s)
 {
-    (void)max_pairs;
-    const size_t bytes = 4 * (size_t)(adj_slots(d.pk_row.slots) + 1); // beyond the static arrays
+    const size_t bytes = 4 * (size_t)bwd_lds_slots(d.pk_row.slots) * kColSlotWords * kT; // beyond the static arrays
     const auto k = for_slots<BwdK>(d.pk_row.slots);
     hipError_t e = set_dynamic_lds((const void *)k, bytes);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(k, dim3(d.B), dim3(kT), bytes, s, d);
+    hipLaunchKernelGGL(k, dim3(d.B), dim3(kT), bytes, s, d, eps);
     return hipGetLastError();
 }
 
@@ -2117,6 +1903,8 @@ int steps_lanes(int64_t nnz, int64_t owners)
     return g;
 }
 
+int log2_lanes(int g) { return g == 16 ? 4 : g == 8 ? 3 : 2; }
+
 template <template <int> class K, class... A>
 void launch_lanes(int g, int64_t owners, hipStream_t s, A... args)
 {
@@ -2128,13 +1916,20 @@ void launch_lanes(int g, int64_t owners, hipStream_t s, A... args)
 }
 template <int G> struct ColStep { static constexpr auto fn = k_sink_step<true, G>; };
 template <int G> struct RowStep { static constexpr auto fn = k_sink_step<false, G>; };
-template <int G> struct BwdFirst { static constexpr auto fn = k_bwd_first<G>; };
-template <int G> struct BwdRows { static constexpr auto fn = k_bwd_rows<G>; };
-template <int G> struct BwdColsFirst { static constexpr auto fn = k_bwd_cols<true, G>; };
-template <int G> struct BwdCols { static constexpr auto fn = k_bwd_cols<false, G>; };
+template <int G> struct BwdRowsFirst { static constexpr auto fn = k_bwd_rows<true, G>; };
+template <int G> struct BwdRows { static constexpr auto fn = k_bwd_rows<false, G>; };
+template <int G> struct BwdCols { static constexpr auto fn = k_bwd_cols<G>; };
 template <int G> struct LossRows { static constexpr auto fn = k_loss_rows<G>; };
 
 } // namespace
+
+void launch_bwd_direct(const DevPlan &d, hipStream_t s)
+{
+    const int64_t BN = (int64_t)d.B * d.N, BM = (int64_t)d.B * d.M;
+    const int gr = steps_lanes(d.nnz, BN), gc = steps_lanes(d.nnz, BM);
+    const unsigned rows = blocks_for(BN * gr, kBlock), cols = blocks_for(BM * gc, kBlock);
+    hipLaunchKernelGGL(k_bwd_direct, dim3(rows + cols), dim3(kBlock), 0, s, d, (int)rows, log2_lanes(gr), log2_lanes(gc));
+}
 
 void launch_sinkhorn_fwd_steps(const DevPlan &d, double eps, hipStream_t s)
 {
@@ -2155,13 +1950,12 @@ void launch_sinkhorn_bwd_steps(const DevPlan &d, double eps, hipStream_t s)
 {
     const int BN = d.B * d.N, BM = d.B * d.M;
     const int gr = steps_lanes(d.nnz, BN), gc = steps_lanes(d.nnz, BM);
-    launch_lanes<BwdFirst>(gr, BN, s, d);
     for (int l = d.L; l >= 1; --l) {
+        launch_lanes<BwdCols>(gc, BM, s, d, l, l == d.L ? 1.0 : eps);
         if (l == d.L)
-            launch_lanes<BwdColsFirst>(gc, BM, s, d, l, eps);
+            launch_lanes<BwdRowsFirst>(gr, BN, s, d, l, eps);
         else
-            launch_lanes<BwdCols>(gc, BM, s, d, l, eps);
-        launch_lanes<BwdRows>(gr, BN, s, d, l, eps);
+            launch_lanes<BwdRows>(gr, BN, s, d, l, eps);
     }
 }
 

@@ -63,7 +63,7 @@ __device__ __forceinline__ void pack_pair(const DevPlan &d, int b, int j, int k,
 {
     const int roff = t - d.row_ptr[(size_t)b * d.N + i];
     pieces::pack_row_pair(d, d.sink_place, b, i, roff, j, p0);
-    pieces::pack_col_pair(d, d.sink_place, b, j, k, i, roff, p0);
+    pieces::pack_col_pair(d, d.sink_place, b, j, k, i, p0);
 }
 
 // dP0/dP_row and dP0/dP_col of a pair with these flags (bit 0: the row
@@ -258,7 +258,7 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
 template <int G> __global__ __launch_bounds__(kBlock, 4) void k_row_softmax(DevPlan d, Params p)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<G, kSmCache>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+    each_owner<kSmCache>(G, gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
         owner_softmax<true>(d, p, r, lanes, lg);
     });
 }
@@ -266,7 +266,7 @@ template <int G> __global__ __launch_bounds__(kBlock, 4) void k_row_softmax(DevP
 template <int G> __global__ __launch_bounds__(kBlock, 4) void k_col_softmax(DevPlan d, Params p)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<G, kSmCache>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+    each_owner<kSmCache>(G, gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
         owner_softmax<false>(d, p, gc, lanes, lg);
     });
 }
@@ -337,7 +337,7 @@ template <int G> __global__ __launch_bounds__(kCscT) void k_csc_rows(DevPlan d, 
         return;
     }
     const int gid = (blockIdx.x - d.B * parts) * kCscT + threadIdx.x;
-    each_owner<G, kSmCache>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+    each_owner<kSmCache>(G, gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
         owner_softmax<true>(d, p, r, lanes, lg);
     });
 }
@@ -347,11 +347,12 @@ __host__ inline size_t csc_sample_lds(int M, int64_t max_pairs)
     return 4 * (2 * (size_t)M + 1) + 6 * (size_t)max_pairs + 16;
 }
 
-// dLoss/dP0 of stored pair t: the Sinkhorn adjoint, or grad_loss * C when
-// there are no Sinkhorn iterations.
-__device__ __forceinline__ double p0bar(const DevPlan &d, int t, double gl)
+// dLoss/dP0 of stored pair t with cost c: the direct term of the loss,
+// grad_loss alpha_i beta_j C (w: the first three), and the sum of the
+// iterations' terms.
+__device__ __forceinline__ double p0bar(const DevPlan &d, int t, double w, double c)
 {
-    return d.L == 0 ? gl * d.cost[t] : d.adj[t];
+    return d.L == 0 ? w * c : __builtin_fma(w, c, d.adj[t]);
 }
 
 // Backward of one owner's softmax by its group of G lanes, with the first
@@ -394,6 +395,8 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
     const float *yc = d.y + (size_t)gc * 3;
     const float y0 = yc[0], y1 = yc[1], y2 = yc[2];
     const float *xb = d.x + (size_t)b * d.N * 3;
+    const double wb = gl * d.beta[(size_t)d.L * d.B * d.M + gc]; // direct weight but for alpha_i
+    const double *al = d.alpha + (size_t)d.L * d.B * d.N + (size_t)b * d.N;
 
     int tq[NC], iq[NC];
     PT pq[NC];
@@ -412,9 +415,9 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
         const int k = lg + G * c;
         const uint8_t f = k < n ? d.flags[tq[c]] : 0;
         kq[c] = (f & 2) != 0;
-        aq[c] = kq[c] ? sym_weight(p, f) * p0bar(d, tq[c], gl) : 0.0;
         const float *xi = xb + 3 * (size_t)iq[c];
         cq[c] = kq[c] ? dist3(xi[0], xi[1], xi[2], y0, y1, y2) : 0.0;
+        aq[c] = kq[c] ? sym_weight(p, f) * p0bar(d, tq[c], wb * al[iq[c]], cq[c]) : 0.0;
     }
     double zsum = 0.0;
     if constexpr (DP) {
@@ -448,7 +451,7 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
         const int t = d.csc_perm[s0 + k];
         const uint8_t f = d.flags[t];
         if (f & 2)
-            sigma += p_at(s0 + k, t) * (sym_weight(p, f) * p0bar(d, t, gl));
+            sigma += p_at(s0 + k, t) * (sym_weight(p, f) * p0bar(d, t, wb * al[d.csc_row[s0 + k]], d.cost[t]));
     }
     sigma = group_sum(sigma, G);
     double tbar = 0.0;
@@ -459,7 +462,8 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
         const int t = d.csc_perm[s0 + k];
         const uint8_t f = d.flags[t];
         if (f & 2)
-            tbar -= p_at(s0 + k, t) * (sym_weight(p, f) * p0bar(d, t, gl) - sigma) * (d.cost[t] - c1);
+            tbar -= p_at(s0 + k, t) *
+                    (sym_weight(p, f) * p0bar(d, t, wb * al[d.csc_row[s0 + k]], d.cost[t]) - sigma) * (d.cost[t] - c1);
     }
     tbar = group_sum(tbar, G);
     const double gapbar = gapbar_scale * tbar;
@@ -479,7 +483,10 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
     for (int k = lg + G * NC; k < n; k += G) {
         const int t = d.csc_perm[s0 + k];
         const uint8_t f = d.flags[t];
-        const double cb = (f & 2) ? -T * p_at(s0 + k, t) * (sym_weight(p, f) * p0bar(d, t, gl) - sigma) : 0.0;
+        const double cb =
+            (f & 2) ? -T * p_at(s0 + k, t) *
+                          (sym_weight(p, f) * p0bar(d, t, wb * al[d.csc_row[s0 + k]], d.cost[t]) - sigma)
+                    : 0.0;
         d.cbar[t] = gap_terms(s0 + k, cb);
     }
 }
@@ -487,7 +494,7 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
 template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_softmax(DevPlan d, Params p)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<G, kSmCache>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+    each_owner<kSmCache>(G, gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
         bwd_col_owner<DP>(d, p, gc, lanes, lg);
     });
 }
@@ -527,8 +534,8 @@ __device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p,
             cbq[c] = in ? d.cbar[t] : 0.0; // DP reads it where it is used
         }
         p0q[c] = in ? d.p0r[t] : 0.0f;
-        aq[c] = in ? sym_weight(p, f) * p0bar(d, t, gl) : 0.0;
         cq[c] = in ? d.cost[t] : 1.0;
+        aq[c] = in ? sym_weight(p, f) * p0bar(d, t, gl * al * bl[jq[c]], cq[c]) : 0.0;
     }
     double zsum = 0.0;
     if constexpr (DP) {
@@ -560,7 +567,7 @@ __device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p,
         const int t = t0 + k;
         const uint8_t f = d.flags[t];
         if (f & 1)
-            sigma += p_at(t) * (sym_weight(p, f) * p0bar(d, t, gl));
+            sigma += p_at(t) * (sym_weight(p, f) * p0bar(d, t, gl * al * bl[d.csr_col[t]], d.cost[t]));
     }
     sigma = group_sum(sigma, G);
     double tbar = 0.0;
@@ -571,7 +578,8 @@ __device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p,
         const int t = t0 + k;
         const uint8_t f = d.flags[t];
         if (f & 1)
-            tbar -= p_at(t) * (sym_weight(p, f) * p0bar(d, t, gl) - sigma) * (d.cost[t] - c1);
+            tbar -= p_at(t) * (sym_weight(p, f) * p0bar(d, t, gl * al * bl[d.csr_col[t]], d.cost[t]) - sigma) *
+                    (d.cost[t] - c1);
     }
     tbar = group_sum(tbar, G);
     const double gapbar = gscale * tbar;
@@ -603,8 +611,9 @@ __device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p,
         const int t = t0 + k;
         const uint8_t f = d.flags[t];
         const bool kept = (f & 1) != 0;
-        add(t, d.csr_col[t], d.cbar[t], kept, kept ? p_at(t) : 0.0, sym_weight(p, f) * p0bar(d, t, gl), d.cost[t],
-            d.p0r[t]);
+        const int j = d.csr_col[t];
+        add(t, j, d.cbar[t], kept, kept ? p_at(t) : 0.0,
+            sym_weight(p, f) * p0bar(d, t, gl * al * bl[j], d.cost[t]), d.cost[t], d.p0r[t]);
     }
     gx = group_sum(gx, G);
     gy = group_sum(gy, G);
@@ -621,7 +630,7 @@ template <int G, bool DP>
 __global__ __launch_bounds__(kBlock, 4) void k_bwd_row_softmax(DevPlan d, Params p, int keep_cbar)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<G, kSmCache>(gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+    each_owner<kSmCache>(G, gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
         bwd_row_owner<DP>(d, p, keep_cbar, r, lanes, lg);
     });
 }
@@ -654,7 +663,7 @@ __device__ __forceinline__ void grad_y_owner(const DevPlan &d, const Params &p, 
 template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_grad_y(DevPlan d, Params p)
 {
     const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<G, kSmCache>(gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+    each_owner<kSmCache>(G, gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
         grad_y_owner(d, p, gc, lanes, lg);
     });
 }
