@@ -249,10 +249,9 @@ def memory_sweep(trials: int):
                "nnz_per_point": float(per.mean() / (2 * n)),
                "peak_library_mb": peak / 1e6, "bytes_per_point": peak / (2 * n),
                "peak_torch_mb": peak_torch / 1e6, "ms_fwd_bwd": ms,
-               "dense_model_mb": 16.0 * n * n / 1e6}
-        # the dense path (P0 and the plan in float32, the adjoint in float64:
-        # 16 bytes per pair) where it fits comfortably
-        if 16.0 * n * n < 100e9:
+               "dense_model_mb": 4.0 * n * n / 1e6}
+        # the dense path (P0 in float32, 4 bytes per pair) up to 65536 points
+        if n <= 65536:
             def dstep():
                 loss, plan = apml.apml_dense_forward(x, y, prm)
                 apml.apml_dense_backward(plan, x, y, gl)
@@ -303,11 +302,10 @@ def torch_peak_bytes(step) -> int:
 
 
 def dense_bytes(B, N, M, L, d=3) -> int:
-    """Device memory of one dense forward + backward: P0 and the plan (float32)
-    and the plan adjoint (float64) per pair, and an upper bound of the
-    per-point vectors (statistics, Sinkhorn sums and their products, column
-    partial sums)."""
-    return 16 * B * N * M + (96 + 16 * (L + 1) + 8 * d * 64) * B * (N + M)
+    """Device memory of one dense forward + backward: P0 (float32) per pair,
+    and an upper bound of the per-point vectors (statistics, coordinates, the
+    scalings and adjoint sums of every iteration, partial sums)."""
+    return 4 * B * N * (M + 3) + (128 + 12 * (d + 8) + 16 * (L + 1) + 2048 + 8 * d * 64) * B * (N + M)
 
 
 def dense_baseline(x, y, gl, w, sparse_ms, sparse_peak, steps):
@@ -329,7 +327,7 @@ def dense_baseline(x, y, gl, w, sparse_ms, sparse_peak, steps):
     torch.cuda.empty_cache()
     free = torch.cuda.mem_get_info()[0]
     if need > 0.8 * free:
-        return {"skipped": f"needs {need / 1e9:.1f} GB of device memory (16 B per pair), "
+        return {"skipped": f"needs {need / 1e9:.1f} GB of device memory (4 B per pair), "
                            f"{free / 1e9:.1f} GB free", "model_gb": need / 1e9,
                 "memory_ratio_dense_over_sparse_model": need / sparse_peak}
 
@@ -353,7 +351,7 @@ def dense_baseline(x, y, gl, w, sparse_ms, sparse_peak, steps):
     torch.cuda.empty_cache()
     return {"ms_per_step": ms, "peak_hbm_mb": peak / 1e6, "steps": n, "model_gb": need / 1e9,
             "time_ratio_dense_over_sparse": ms / sparse_ms, "memory_ratio_dense_over_sparse": peak / sparse_peak,
-            "what": "apml_dense_forward + apml_dense_backward: P0, the plan and its adjoint as N x M matrices"}
+            "what": "apml_dense_forward + apml_dense_backward: P0 as an N x M matrix, every pair in every pass"}
 
 
 def cpu_model() -> str:

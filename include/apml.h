@@ -184,9 +184,9 @@ apml_status apml_forward_backward_noalloc(const float *x, const float *y, int32_
  * distance as in the sparse path; the temperatures follow Eq. 1 with the gap
  * clamp (Sec. III-D), the softmaxes Eq. 2 over all pairs, P0 = (P_row +
  * P_col)/2, then L column (Eq. 3) and row (Eq. 4) scalings, loss = sum P C.
- * The plan keeps P0 and the Sinkhorn plan as float32 N x M matrices per
- * sample; the backward pass adds a float64 N x M adjoint. Device memory comes
- * from the same pool or caller allocator as the sparse path.
+ * The plan keeps P0 as a float32 N x M matrix per sample (4 bytes a pair) and
+ * per-point vectors. Device memory comes from the same pool or caller
+ * allocator as the sparse path.
  *   x, y    device, float32 [B, N, d] / [B, M, d] contiguous
  *   params  as for apml_forward; gap_mode and sym_mode must be the defaults
  *           (else APML_ERR_UNSUPPORTED); dense_scan and tau are ignored

@@ -1254,7 +1254,7 @@ struct apml_dense_plan {
     int B = 0, N = 0, M = 0, d = 0, L = 0;
     int device = 0;
     hipStream_t stream = nullptr;
-    Arena keep; // the per-owner vectors, P0, the plan, the Sinkhorn sums
+    Arena keep; // the per-owner vectors and P0
     DenseDev dv{};
 };
 
@@ -1291,18 +1291,18 @@ apml_status validate_dense(const float *x, const float *y, int32_t B, int32_t N,
 }
 
 // Per-owner vectors of one direction, carved from c.
-void lay_side(Carve &c, DenseSide &s, size_t n)
+void lay_side(Carve &c, DenseSide &s, size_t n, int dp, int L)
 {
     s.k1 = c.take<int32_t>(n);
     s.k2 = c.take<int32_t>(n);
     s.c1 = c.take<double>(n);
     s.g = c.take<double>(n);
     s.T = c.take<double>(n);
-    s.Z = c.take<double>(n);
+    s.iZ = c.take<double>(n);
     s.clamped = c.take<uint8_t>(n);
-    s.sigma = c.take<double>(n);
-    s.gbar = c.take<double>(n);
-    s.e = c.take<double>(n);
+    s.pf = c.take<float>(n * dp);
+    s.pd = c.take<double>(n * dp);
+    s.sc = c.take<double>((size_t)(L + 1) * n);
 }
 
 } // namespace
@@ -1374,17 +1374,14 @@ apml_status apml_dense_forward(const float *x, const float *y, int32_t B, int32_
     D.x = x;
     D.y = y;
     D.loss = loss;
-    dense_chunks(B, N, M, &D.chunks, &D.chunk);
-    const size_t BN = (size_t)B * N, BM = (size_t)B * M, pairs = (size_t)B * N * M, L = (size_t)prm.n_iter;
+    D.dp = dense_padded_dim(d);
+    D.ld = (M + 3) & ~3;
+    const size_t BN = (size_t)B * N, BM = (size_t)B * M;
     auto lay = [&](Carve &c) {
-        lay_side(c, D.row, BN);
-        lay_side(c, D.col, BM);
-        D.S = c.take<double>(std::max<size_t>(L, 1) * BM);
-        D.R = c.take<double>(std::max<size_t>(L, 1) * BN);
-        D.a_cum = c.take<double>((L + 1) * BN);
-        D.c_cum = c.take<double>((L + 1) * BM);
-        D.P0 = c.take<float>(pairs);
-        D.P = c.take<float>(pairs);
+        lay_side(c, D.row, BN, D.dp, D.L);
+        lay_side(c, D.col, BM, D.dp, D.L);
+        D.rowc = c.take<double>(BN);
+        D.P0 = c.take<float>(BN * D.ld);
     };
     {
         Carve size;
@@ -1396,12 +1393,23 @@ apml_status apml_dense_forward(const float *x, const float *y, int32_t B, int32_
     }
     Arena tmp;
     tmp.stream = s;
-    D.part = tmp.get<double>((size_t)D.chunks * BM);
-    if (tmp.failed)
-        return fail(APML_ERR_OUT_OF_MEMORY, "device allocation failed (dense scratch)");
+    {
+        const DenseScratch n = dense_scratch(D);
+        auto scratch = [&](Carve &c) {
+            D.owner_part = c.take<double>(n.owner);
+            D.part[0] = c.take<double>(n.part);
+            D.part[1] = c.take<double>(n.part);
+        };
+        Carve size;
+        scratch(size);
+        Carve c{tmp.get<uint8_t>(size.off)};
+        if (tmp.failed)
+            return fail(APML_ERR_OUT_OF_MEMORY, "device allocation failed (dense scratch)");
+        scratch(c);
+    }
     launch_dense_forward(D, log_ratio(M, prm.p_min), log_ratio(N, prm.p_min), s);
     HIP_TRY(hipGetLastError());
-    D.part = nullptr;
+    D.owner_part = D.part[0] = D.part[1] = nullptr;
     tmp.release();
     if (plan_out) {
         guard.p = nullptr;
@@ -1423,13 +1431,29 @@ apml_status apml_dense_backward(apml_dense_plan *plan, const float *x, const flo
     D.grad_loss = grad_loss;
     D.grad_x = grad_x;
     D.grad_y = grad_y;
-    const size_t BM = (size_t)plan->B * plan->M, pairs = (size_t)plan->B * plan->N * plan->M;
+    const size_t BN = (size_t)plan->B * plan->N, BM = (size_t)plan->B * plan->M, L = (size_t)plan->L;
     Arena tmp;
     tmp.stream = s;
-    D.A = tmp.get<double>(pairs);
-    D.part = tmp.get<double>((size_t)D.chunks * BM * (size_t)plan->d);
-    if (tmp.failed)
-        return fail(APML_ERR_OUT_OF_MEMORY, "device allocation failed (dense backward)");
+    {
+        const DenseScratch n = dense_scratch(D);
+        auto scratch = [&](Carve &c) {
+            D.row.sb = c.take<double>(L * BN);
+            D.col.sb = c.take<double>(L * BM);
+            D.row.sigma = c.take<double>(BN);
+            D.col.sigma = c.take<double>(BM);
+            D.row.gbar = c.take<double>(BN);
+            D.col.gbar = c.take<double>(BM);
+            D.part[0] = c.take<double>(n.part);
+            D.part[1] = c.take<double>(n.part);
+            D.pair = c.take<double>(n.pair);
+        };
+        Carve size;
+        scratch(size);
+        Carve c{tmp.get<uint8_t>(size.off)};
+        if (tmp.failed)
+            return fail(APML_ERR_OUT_OF_MEMORY, "device allocation failed (dense backward)");
+        scratch(c);
+    }
     launch_dense_backward(D, s);
     HIP_TRY(hipGetLastError());
     tmp.release();

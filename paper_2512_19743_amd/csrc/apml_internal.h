@@ -453,29 +453,40 @@ constexpr int kDenseMaxD = 16; // largest point dimension of the dense path
 // Per-owner vectors of one direction (rows: [B*N], columns: [B*M]).
 struct DenseSide {
     int32_t *k1, *k2;          // indices of the minimum and the second minimum
-    double *c1, *g, *T, *Z;    // minimum cost, clamped gap, temperature (Eq. 1), softmax normaliser (Eq. 2)
+    double *c1, *g, *T, *iZ;   // minimum cost, clamped gap, temperature (Eq. 1), 1 / softmax normaliser (Eq. 2)
     uint8_t *clamped;          // gap clamped: no temperature gradient
-    double *sigma, *gbar, *e;  // backward: softmax adjoint sum, gap adjoint, scratch
+    float *pf;                 // coordinates padded to dp, in single
+    double *pd;                // and in double precision
+    double *sc;                // [L+1]: scalings of every iteration (see dense_apml.hip)
+    double *sb;                // [L], backward: adjoints of the row (column) sums of every iteration
+    double *sigma, *gbar;      // backward: softmax adjoint sum, gap adjoint
 };
 
 struct DenseDev {
     int B, N, M, d, L;
+    int dp;                      // dense_padded_dim(d)
+    int ld;                      // row pitch of P0: M rounded up to a multiple of 4
     double delta, eps_gap, eps_stab, eps_dist;
     int tgrad_full;              // temperature differentiated (apml_tgrad_mode FULL)
     const float *x, *y;          // [B, N, d], [B, M, d]
     DenseSide row, col;
-    float *P0, *P;               // [B][N][M]: initial plan, plan after the Sinkhorn iterations
-    double *S, *R;               // [L][B*M], [L][B*N]: column and row sums of every iteration
-    double *a_cum, *c_cum;       // [L+1][B*N], [L+1][B*M]: cumulative row and column scalings
-    double *part;                // [chunks][B*M] (x d for the gradient): partial sums of the column passes
-    int chunks, chunk;           // row chunks of the column passes and their length
+    float *P0;                   // [B][N][ld]: initial plan
+    double *rowc;                // [B*N]: sum_j P0 beta^L C
+    double *owner_part;          // forward: the owners' partial statistics
+    double *part[2];             // partial column sums of a sweep and of the next
+    double *pair;                // backward: partial sums of the softmax and distance adjoints
     float *loss;                 // [B]
-    double *A;                   // [B][N][M]: plan adjoint (backward)
     const float *grad_loss;
     float *grad_x, *grad_y;
 };
 
-void dense_chunks(int B, int N, int M, int *chunks, int *chunk);
+int dense_padded_dim(int d);
+void dense_pair_chunks(int B, int n_own, int n_oth, int *chunks, int *len);
+// Doubles of owner_part, of each part and of pair.
+struct DenseScratch {
+    size_t owner, part, pair;
+};
+DenseScratch dense_scratch(const DenseDev &D);
 void launch_dense_forward(const DenseDev &D, double lk_row, double lk_col, hipStream_t s);
 void launch_dense_backward(const DenseDev &D, hipStream_t s);
 

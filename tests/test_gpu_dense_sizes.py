@@ -1,0 +1,64 @@
+"""GPU parity of the dense APML path at the edges of its launches: row lengths
+around the waves per row of the fused sweep (256, 512, 1024, 2048, 4096, 8192
+columns; longer rows take separate row and column products), lengths that are
+not a multiple of four, few rows, many iterations (the thin product of the
+adjoint in one step of 16 iterations, or several) and scalings that would leave
+the range of a double without the powers of two kept out of them."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_19743_amd as apml
+from oracle.dense import dense_apml
+from workloads import custom
+
+from ._parity import GRAD_RTOL, LOSS_RTOL, note, rel_norm
+from .test_gpu_dense import _against_oracle, run_dense
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    apml.load()
+
+
+@pytest.mark.parametrize("N,M", [(3, 2), (5, 3), (65, 63), (64, 256), (67, 257), (130, 512), (33, 514), (70, 1024),
+                                 (300, 1025), (64, 2048), (50, 2049), (34, 4096), (35, 4099), (40, 8192), (37, 8195),
+                                 (2049, 70), (8200, 20)])
+def test_dense_row_lengths(N, M):
+    X, Y = custom(65, 2, N, M, reference="sphere", prediction="uniform_cube")
+    _against_oracle(X, Y, "sizes", n_iter=3, gbar=[1.0, -0.5])
+
+
+@pytest.mark.parametrize("L", [2, 15, 16, 17, 33])
+def test_dense_thin_product_lengths(L):
+    X, Y = custom(66, 3, 90, 150, sigma=0.05)
+    _against_oracle(X, Y, f"L={L}", n_iter=L)
+
+
+# alpha grows by N / M (beta shrinks) in each iteration: 2^(3 * 500) and 2^(-1.6 * 800)
+@pytest.mark.parametrize("N,M,L", [(96, 12, 500), (12, 36, 800)])
+def test_dense_scalings_stay_in_range(N, M, L):
+    X, Y = custom(67, 1, N, M, reference="sphere", prediction="uniform_cube")
+    _against_oracle(X, Y, f"range L={L}", n_iter=L)
+
+
+@pytest.mark.parametrize("d", [1, 3, 4, 7, 8, 9, 16])
+def test_dense_dimensions_with_many_points(d):
+    rng = np.random.default_rng(200 + d)
+    B, N, M = 2, 131, 270
+    Y = rng.standard_normal((B, M, d)).astype(np.float32)
+    X = (Y[:, rng.permutation(M)[:N]] + 0.2 * rng.standard_normal((B, N, d))).astype(np.float32)
+    note(f"dense dimension d={d}")
+    loss, gx, gy = run_dense(X, Y, gbar=[1.0, -0.7], n_iter=6)
+    for b in range(B):
+        x = torch.from_numpy(X[b].astype(np.float64)).requires_grad_(True)
+        y = torch.from_numpy(Y[b].astype(np.float64)).requires_grad_(True)
+        ref, _ = dense_apml(x, y, tau=0.0, n_iter=6)
+        (ref * [1.0, -0.7][b]).backward()
+        assert abs(loss[b] - ref.item()) <= LOSS_RTOL * abs(ref.item())
+        assert rel_norm(gx[b], x.grad.numpy()) <= GRAD_RTOL
+        assert rel_norm(gy[b], y.grad.numpy()) <= GRAD_RTOL
