@@ -1298,6 +1298,7 @@ void lay_side(Carve &c, DenseSide &s, size_t n, int dp, int L)
     s.c1 = c.take<double>(n);
     s.g = c.take<double>(n);
     s.T = c.take<double>(n);
+    s.n2 = c.take<double>(n);
     s.iZ = c.take<double>(n);
     s.clamped = c.take<uint8_t>(n);
     s.pf = c.take<float>(n * dp);

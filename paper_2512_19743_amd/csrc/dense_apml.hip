@@ -25,10 +25,10 @@
 //    k_dpair forms on the matrix cores (double precision) for the pairs it
 //    holds, never in memory.
 //  * C and both softmaxes are recomputed from the coordinates where needed.
-// 32 x 2048 x 2048 points, 10 iterations, forward + backward: 26.6 -> 5.0 ms
+// 32 x 2048 x 2048 points, 10 iterations, forward + backward: 26.6 -> 4.3 ms
 // against a plan matrix read and written in every half-iteration and a
 // double-precision adjoint matrix; bounds by launch: the sweeps read P0 at
-// 4.8 TB/s, the others are bound by double-precision arithmetic (a square
+// 5.2 TB/s, the others are bound by double-precision arithmetic (a square
 // root and one or two exponentials per pair).
 //
 // Sums have a fixed association: every result is bitwise reproducible.
@@ -69,7 +69,54 @@ __device__ __forceinline__ void merge_top2(float &m1, int &k1, float &m2, int &k
     }
 }
 
-// C = ||a - b||_2 in double precision (Sec. III-A); u: the differences.
+// sqrt of a squared distance between float coordinates: 0, or between 1e-90
+// and 1e79, so the reciprocal square root needs none of the library's scaling
+// (0 is taken as 1e-300: its root, 1e-150, is added to nothing smaller than
+// 1e-45). One Goldschmidt step and a residual correction: within an ulp.
+__device__ __forceinline__ double root(double s)
+{
+    s = __builtin_fmax(s, 1e-300);
+    const double y = __builtin_amdgcn_rsq(s);
+    double g = s * y, h = 0.5 * y;
+    const double r = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, r, g);
+    h = __builtin_fma(h, r, h);
+    return __builtin_fma(__builtin_fma(-g, g, s), h, g);
+}
+
+// 2^t for t up to 1024 (below -1100: 0): 2^n (1 + f q(f)), n the nearest whole
+// number and |f| <= 1/2, q the polynomial that interpolates (2^f - 1) / f at
+// eleven Chebyshev nodes (relative error 2e-17 of 2^f, exactly 1 at 0). 17
+// operations against the library exponential's 26, which with the root's 8
+// against 19 bound these kernels (32 x 2048 x 2048 points: k_dz 430 -> 319 us,
+// k_dp0 335 -> 269, k_dpair 701 -> 589 and 443 -> 388).
+__device__ __forceinline__ double exp2_of(double t)
+{
+    t = __builtin_fmax(t, -1100.0);
+    const double n = __builtin_rint(t), f = t - n;
+    double q = 4.4549605981865186e-10;
+    q = __builtin_fma(q, f, 7.072585949269223e-09);
+    q = __builtin_fma(q, f, 1.0178062445845774e-07);
+    q = __builtin_fma(q, f, 1.321544258792169e-06);
+    q = __builtin_fma(q, f, 1.525273382983612e-05);
+    q = __builtin_fma(q, f, 0.0001540353044173605);
+    q = __builtin_fma(q, f, 0.0013333558146416936);
+    q = __builtin_fma(q, f, 0.009618129107606888);
+    q = __builtin_fma(q, f, 0.0555041086648216);
+    q = __builtin_fma(q, f, 0.24022650695910097);
+    q = __builtin_fma(q, f, 0.6931471805599453);
+    return __builtin_ldexp(__builtin_fma(f, q, 1.0), (int)n);
+}
+
+// 1 / v for normal v: the hardware reciprocal and two Newton steps.
+__device__ __forceinline__ double inverse(double v)
+{
+    double r = __builtin_amdgcn_rcp(v);
+    r = __builtin_fma(r, __builtin_fma(-v, r, 1.0), r);
+    return __builtin_fma(r, __builtin_fma(-v, r, 1.0), r);
+}
+
+// C = ||a - b||_2 in double precision (Sec. III-A).
 template <int DP> __device__ __forceinline__ double cost_of(const double (&a)[DP], const double (&b)[DP])
 {
     double t = a[0] - b[0];
@@ -79,13 +126,13 @@ template <int DP> __device__ __forceinline__ double cost_of(const double (&a)[DP
         t = a[k] - b[k];
         s = __builtin_fma(t, t, s);
     }
-    return sqrt(s);
+    return root(s);
 }
 
-// Softmax entry (Eq. 2) of a pair of cost C for an owner with -T, C1 and 1/Z.
-__device__ __forceinline__ double softmax_of(double C, double nT, double c1, double iZ)
+// Softmax entry (Eq. 2) of a pair of cost C for an owner with n2 = -T log2(e), C1 and 1/Z.
+__device__ __forceinline__ double softmax_of(double C, double n2, double c1, double iZ)
 {
-    return exp(nT * (C - c1)) * iZ;
+    return exp2_of(n2 * (C - c1)) * iZ;
 }
 
 // ---------------------------------------------------------------------------
@@ -229,6 +276,7 @@ __global__ __launch_bounds__(kBlock) void k_dstat(DenseDev D, Split sp, const fl
     s.c1[o] = c1;
     s.g[o] = g;
     s.T[o] = (rows ? lk_row : lk_col) / g;
+    s.n2[o] = -1.4426950408889634 * s.T[o];
     s.clamped[o] = clamped;
     s.sc[o] = 1.0;
 }
@@ -245,7 +293,7 @@ template <int DP> __global__ __launch_bounds__(kBlock) void k_dz(DenseDev D, Spl
 #pragma unroll
     for (int k = 0; k < DP; ++k)
         a[k] = own.pd[go * DP + k];
-    const double nT = -own.T[go], c1 = own.c1[go];
+    const double n2 = own.n2[go], c1 = own.c1[go];
     const const_ptr<double> q = as_const(oth.pd) + (size_t)w.b * w.n_oth * DP;
     double z = 0.0;
 #pragma unroll 2
@@ -254,7 +302,7 @@ template <int DP> __global__ __launch_bounds__(kBlock) void k_dz(DenseDev D, Spl
 #pragma unroll
         for (int k = 0; k < DP; ++k)
             p[k] = q[(size_t)j * DP + k];
-        z += exp(nT * (cost_of(a, p) - c1));
+        z += exp2_of(n2 * (cost_of(a, p) - c1));
     }
     if (w.o < w.n_own)
         part[(w.rows ? 0 : (size_t)sp.chunks_r * D.B * D.N) + (size_t)w.chunk * D.B * w.n_own + go] = z;
@@ -294,9 +342,9 @@ template <int DP> __global__ __launch_bounds__(kBlock) void k_dp0(DenseDev D, in
 #pragma unroll
     for (int k = 0; k < DP; ++k)
         a[k] = D.col.pd[c * DP + k];
-    const double nT = -D.col.T[c], c1 = D.col.c1[c], iZ = j < D.M ? D.col.iZ[c] : 0.0;
+    const double n2 = D.col.n2[c], c1 = D.col.c1[c], iZ = j < D.M ? D.col.iZ[c] : 0.0;
     const const_ptr<double> q = as_const(D.row.pd) + (size_t)b * D.N * DP;
-    const const_ptr<double> rT = as_const(D.row.T) + (size_t)b * D.N, rc1 = as_const(D.row.c1) + (size_t)b * D.N,
+    const const_ptr<double> rn2 = as_const(D.row.n2) + (size_t)b * D.N, rc1 = as_const(D.row.c1) + (size_t)b * D.N,
                             rZ = as_const(D.row.iZ) + (size_t)b * D.N;
     float *out = D.P0 + ((size_t)b * D.N) * D.ld + j;
     double sum = 0.0;
@@ -306,7 +354,7 @@ template <int DP> __global__ __launch_bounds__(kBlock) void k_dp0(DenseDev D, in
         for (int k = 0; k < DP; ++k)
             p[k] = q[(size_t)i * DP + k];
         const double C = cost_of(a, p);
-        const float p0 = (float)(0.5 * (softmax_of(C, -rT[i], rc1[i], rZ[i]) + softmax_of(C, nT, c1, iZ)));
+        const float p0 = (float)(0.5 * (softmax_of(C, rn2[i], rc1[i], rZ[i]) + softmax_of(C, n2, c1, iZ)));
         const float v = j < D.M ? p0 : 0.0f;
         if (j < D.ld)
             out[(size_t)i * D.ld] = v;
@@ -348,7 +396,7 @@ __device__ __forceinline__ double column_value(const DenseDev &D, const Sweep &s
     const size_t BM = (size_t)D.B * D.M;
     if constexpr (MODE == FWD) {
         const double prev = D.col.sc[(size_t)(s.l - 1) * BM + c] * s.f_in;
-        return prev / (prev * sum + D.eps_stab);
+        return prev * inverse(prev * sum + D.eps_stab);
     } else {
         const double cl = D.col.sc[(size_t)s.l * BM + c];
         const double old = s.l < D.L ? s.f_in * D.col.sb[(size_t)s.l * BM + c] : 0.0;
@@ -376,7 +424,7 @@ template <DenseMode MODE>
 __device__ __forceinline__ double row_value(const DenseDev &D, const Sweep &s, const RowOld &o, double dot)
 {
     if constexpr (MODE == FWD)
-        return o.a / (o.a * dot + D.eps_stab) * s.f_out;
+        return o.a * inverse(o.a * dot + D.eps_stab) * s.f_out;
     else
         return s.f_out * (D.eps_stab * o.r - o.a * o.a * dot);
 }
@@ -395,10 +443,10 @@ template <int N> __device__ __forceinline__ double row_ror(double v)
     return __builtin_bit_cast(double, w);
 }
 
-// Wave sums of four values at once: lane l returns that of v[l % 4]. Two
-// exchanges halve the values a lane holds, so that four sums cost little
-// more than one.
-__device__ __forceinline__ double wave_sum4(const double (&v)[4])
+// Sums of four values at once over each row of 16 lanes: lane l returns that
+// of v[l % 4]. Two exchanges halve the values a lane holds, so that four sums
+// cost little more than one.
+__device__ __forceinline__ double row_sum4(const double (&v)[4])
 {
     const bool b0 = threadIdx.x & 1, b1 = threadIdx.x & 2;
     const double lo = (b0 ? v[1] : v[0]) + partner<0>(b0 ? v[0] : v[1]);
@@ -406,6 +454,13 @@ __device__ __forceinline__ double wave_sum4(const double (&v)[4])
     double s = (b1 ? hi : lo) + partner<1>(b1 ? lo : hi);
     s += row_ror<4>(s);
     s += row_ror<8>(s);
+    return s;
+}
+
+// And over the wave.
+__device__ __forceinline__ double wave_sum4(const double (&v)[4])
+{
+    double s = row_sum4(v);
     s += __shfl_xor(s, 16);
     s += __shfl_xor(s, 32);
     return s;
@@ -428,8 +483,9 @@ __device__ __forceinline__ double lane_value(double v, int lane)
 template <DenseMode MODE, int W, int Q> __global__ __launch_bounds__(64 * W) void k_dsweep(DenseDev D, Sweep s)
 {
     constexpr int T = 64 * W;
-    constexpr bool AHEAD = W < 16; // the next rows in flight (beyond 128 registers a lane at 16 waves)
-    __shared__ double sums[2][W][4];
+    constexpr int AHEAD = W == 16 ? 0 : 1; // row groups in flight ahead (none fit the 128 registers at 16 waves)
+    constexpr int SUMS = W == 1 ? 0 : W <= 4 ? 4 : 1; // sums a wave leaves in LDS per row: of its rows of 16 lanes, or one
+    __shared__ double sums[2][W * (SUMS ? SUMS : 1)][4];
     const int g = xcd_contiguous(blockIdx.x, gridDim.x); // a sample's blocks share an L2
     const int b = s.b0 + g / s.nb, blk = g % s.nb;
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
@@ -481,14 +537,20 @@ template <DenseMode MODE, int W, int Q> __global__ __launch_bounds__(64 * W) voi
                 p[k][q] = j4 < ld4 ? P[(size_t)min(r + k, r1 - 1) * ld4 + j4] : make_float4(0.f, 0.f, 0.f, 0.f);
             }
     };
-    float4 p[4][Q], nx[4][Q];
+    auto old_of = [&](int r) { return row_old<MODE>(D, s, row0 + min(r + (lane & 3), r1 - 1)); };
+    float4 p[4][Q], ahead[AHEAD ? AHEAD : 1][4][Q];
     load(p, r0);
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a)
+        load(ahead[a], r0 + 4 * (a + 1)); // past the block: its last row again
+    RowOld old_next = old_of(r0);
     int par = 0;
     for (int r = r0; r < r1; r += 4, par ^= 1) {
-        const int mine = min(r + (lane & 3), r1 - 1);
-        const RowOld old = row_old<MODE>(D, s, row0 + mine);
-        if (AHEAD && r + 4 < r1)
-            load(nx, r + 4);
+        const RowOld old = old_next;
+        old_next = old_of(r + 4);
+        float4 last[4][Q];
+        if constexpr (AHEAD > 0)
+            load(last, r + 4 * (AHEAD + 1));
         double dot[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -501,15 +563,16 @@ template <DenseMode MODE, int W, int Q> __global__ __launch_bounds__(64 * W) voi
                 dot[k] = __builtin_fma((double)p[k][q].w, v[q][3], dot[k]);
             }
         }
-        double t = wave_sum4(dot);
-        if constexpr (W > 1) {
-            if (lane < 4)
-                sums[par][wave][lane] = t; // the other half is still read by slower waves
+        double t = SUMS == 4 ? row_sum4(dot) : wave_sum4(dot);
+        if constexpr (SUMS > 0) {
+            if ((lane & (64 / SUMS - 1)) < 4)
+                sums[par][wave * SUMS + (SUMS == 4 ? lane >> 4 : 0)][lane & 3] = t; // the other half is still read
             lds_barrier();
-            t = 0.0;
+            double part[4] = {};
 #pragma unroll
-            for (int w = 0; w < W; ++w)
-                t += sums[par][w][lane & 3];
+            for (int w = 0; w < W * SUMS; ++w)
+                part[w & 3] += sums[par][w][lane & 3];
+            t = (part[0] + part[1]) + (part[2] + part[3]);
         }
         const double w = row_value<MODE>(D, s, old, t);
         if (wave == 0 && lane < 4 && r + lane < r1)
@@ -527,13 +590,18 @@ template <DenseMode MODE, int W, int Q> __global__ __launch_bounds__(64 * W) voi
                 }
             }
         }
-        if constexpr (AHEAD) {
+        if constexpr (AHEAD > 0) {
 #pragma unroll
             for (int k = 0; k < 4; ++k)
 #pragma unroll
-                for (int q = 0; q < Q; ++q)
-                    p[k][q] = nx[k][q];
-        } else if (r + 4 < r1) {
+                for (int q = 0; q < Q; ++q) {
+                    p[k][q] = ahead[0][k][q];
+#pragma unroll
+                    for (int a = 0; a + 1 < AHEAD; ++a)
+                        ahead[a][k][q] = ahead[a + 1][k][q];
+                    ahead[AHEAD - 1][k][q] = last[k][q];
+                }
+        } else {
             load(p, r + 4);
         }
     }
@@ -718,7 +786,7 @@ template <int DP, bool GRAD> struct PairLds {
     double u[kKC][kUP];
     double xyz[kPairT][DP];
     double dir[kPairT];
-    double nT[GRAD ? kPairT : 1], c1[GRAD ? kPairT : 1], iZ[GRAD ? kPairT : 1], sig[GRAD ? kPairT : 1];
+    double nT[GRAD ? kPairT : 1], n2[GRAD ? kPairT : 1], c1[GRAD ? kPairT : 1], iZ[GRAD ? kPairT : 1], sig[GRAD ? kPairT : 1];
     int2 k12[GRAD ? kPairT : 1];
 };
 
@@ -755,7 +823,7 @@ __global__ __launch_bounds__(kBlock, DP <= 4 ? 4 : 2) void k_dpair(DenseDev D, i
 #pragma unroll
     for (int k = 0; k < DP; ++k)
         a[k] = own.pd[po * DP + k];
-    const double nT = -own.T[po], c1 = own.c1[po], iZ = own.iZ[po];
+    const double nT = -own.T[po], n2 = own.n2[po], c1 = own.c1[po], iZ = own.iZ[po];
     const double sig = GRAD ? own.sigma[po] : 0.0;
     const double dir = own.sc[(size_t)D.L * D.B * n_own + po];
     double bop[kKC / 4]; // this lane's owner values of a step's columns k = 4 s + l / 16
@@ -779,6 +847,7 @@ __global__ __launch_bounds__(kBlock, DP <= 4 ? 4 : 2) void k_dpair(DenseDev D, i
             sh.dir[tid] = oth.sc[(size_t)D.L * D.B * n_oth + q];
             if constexpr (GRAD) {
                 sh.nT[tid] = -oth.T[q];
+                sh.n2[tid] = oth.n2[q];
                 sh.c1[tid] = oth.c1[q];
                 sh.iZ[tid] = oth.iZ[q];
                 sh.sig[tid] = oth.sigma[q];
@@ -823,11 +892,11 @@ __global__ __launch_bounds__(kBlock, DP <= 4 ? 4 : 2) void k_dpair(DenseDev D, i
                     u[k] = a[k] - sh.xyz[i][k];
                     q = k == 0 ? u[k] * u[k] : __builtin_fma(u[k], u[k], q);
                 }
-                const double C = sqrt(q);
+                const double C = root(q);
                 const double v = dir * sh.dir[i]; // alpha^L beta^L
                 const double half = 0.5 * __builtin_fma(gl * v, C, pb[r]);
                 const double e = C - c1;
-                double p = exp(nT * e) * iZ;
+                double p = exp2_of(n2 * e) * iZ;
                 if constexpr (!GRAD) {
                     p = i < cnt ? p : 0.0;
                     const double ph = p * half;
@@ -835,7 +904,7 @@ __global__ __launch_bounds__(kBlock, DP <= 4 ? 4 : 2) void k_dpair(DenseDev D, i
                     acc[1] = __builtin_fma(ph, e, acc[1]);
                     acc[2] = __builtin_fma(p, e, acc[2]);
                 } else {
-                    const double po_ = softmax_of(C, sh.nT[i], sh.c1[i], sh.iZ[i]);
+                    const double po_ = softmax_of(C, sh.n2[i], sh.c1[i], sh.iZ[i]);
                     const float p0 = (float)(0.5 * (p + po_));
                     double cb = gl * ((double)p0 * v);
                     cb = __builtin_fma(nT * p, half - sig, cb);
@@ -848,7 +917,7 @@ __global__ __launch_bounds__(kBlock, DP <= 4 ? 4 : 2) void k_dpair(DenseDev D, i
                         if (o == k12.x)
                             cb -= gb;
                     }
-                    const double w = i < cnt ? cb / (C + D.eps_dist) : 0.0;
+                    const double w = i < cnt ? cb * inverse(C + D.eps_dist) : 0.0;
 #pragma unroll
                     for (int k = 0; k < DP; ++k)
                         acc[k] = __builtin_fma(w, u[k], acc[k]);
@@ -949,21 +1018,24 @@ Split owner_split(const DenseDev &D)
     return s;
 }
 
-// Most partial sums per column that a sweep adds up itself; more of them
-// (few samples, cut into many row blocks) are added by a launch of their own.
+// Partial sums per column, one per row block, that a sweep adds up itself
+// (every block reads them all, from beyond its L2); more are added by a launch
+// of its own (5 us).
 constexpr int kOwnParts = 16;
 constexpr int kMostParts = 128;
 constexpr int kSweepMax = 8192; // longest rows of k_dsweep
 
 int sweep_waves(int M) { return M <= 512 ? 1 : M <= 1024 ? 2 : M <= 2048 ? 4 : M <= 4096 ? 8 : 16; }
 
-// Row blocks per sample and rows per block of the sweeps: about 4096 waves,
-// at least 16 rows a block.
+// Row blocks per sample and rows per block of the sweeps: 16 blocks where they
+// hold 2048 waves (32 x 2048 x 2048: 103 us a sweep, against 117 with 32), else
+// more, of at least 16 rows: with few waves on a SIMD the time is that of a
+// block's chain of row groups, about a microsecond each (1 x 2048 x 2048:
+// 25 us a sweep with 32 blocks, 15 with 128).
 void row_blocks(const DenseDev &D, int *nb, int *rb)
 {
-    const int waves = D.M <= kSweepMax ? sweep_waves(D.M) : 4 * ceil_to(D.ld, kBlock);
-    const int want = std::min(kMostParts, std::max(1, ceil_to(4096, (int64_t)D.B * waves)));
-    const int n = std::min(want > kOwnParts && want < 2 * kOwnParts ? kOwnParts : want, std::max(1, D.N / 16));
+    const int64_t waves = (int64_t)D.B * (D.M <= kSweepMax ? sweep_waves(D.M) : 16);
+    const int n = std::max(1, std::min({kMostParts, std::max(kOwnParts, ceil_to(2048, waves)), D.N / 16}));
     *rb = ceil_to(ceil_to(D.N, n), 4) * 4;
     *nb = ceil_to(D.N, *rb);
 }
