@@ -437,13 +437,15 @@ apml_status wait_for(hipStream_t s)
 }
 
 // Chunks of the broadcast range so that the support scan has about
-// target / 1024 waves per SIMD on 256 CUs, each chunk at least min_chunk
-// points long.
-void choose_chunks(int B, int n_own, int n_bc, int *S, int *chunk, int min_chunk, int64_t target = 8192)
+// target / 1024 waves per SIMD on 256 CUs (half as many: 30 -> 35 us at
+// 32 x 2048 x 2048, the workgroups' hits differ too much): at least 256 points long, or down to
+// 64 in at most 32 chunks (a chunk's hits are visited one after another, which
+// sets the time of a few small samples: 2 x 256 x 256 26 -> 9 us, 16 x 1024 28 -> 9.5).
+void choose_chunks(int B, int n_own, int n_bc, int *S, int *chunk, int64_t target = 8192)
 {
     const int64_t waves = (int64_t)B * ceil_div(n_own, 64);
     int s = (int)std::max<int64_t>(1, (target + waves - 1) / waves);
-    s = std::min(s, std::max(1, n_bc / min_chunk));
+    s = std::min(s, std::max({1, n_bc / 256, std::min(32, n_bc / 64)}));
     int len = ceil_div(n_bc, s);
     len = ceil_div(len, kUnroll) * kUnroll;
     *chunk = len;
@@ -606,7 +608,7 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
         ps.x = x;
         ps.y = y;
         const int owner_blocks = ceil_div(N, kBlock);
-        choose_chunks(B, N, M, &ea.S, &ea.chunk, 256);
+        choose_chunks(B, N, M, &ea.S, &ea.chunk);
         // the scratch of both scans in one allocation; the counting pass
         // keeps the first hits of every (row, chunk), at 16-bit offsets
         // within the chunk

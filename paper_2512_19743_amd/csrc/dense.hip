@@ -1,5 +1,4 @@
 // Dense phase of the sparse APML loss: the two scans over all B*N*M pairs.
-// VALU-bound; no matrix cores (the K=3 contraction is not a GEMM).
 //
 //   k_top2_pairs  per row and per column, the minimum and second minimum of
 //              the single-precision squared distance (Sec. III-A), each pair
@@ -13,9 +12,11 @@
 //              C <= C1 + log(1/tau)/T (Sec. III-B, Eq. 1), widened by a small
 //              relative margin and never below the second minimum.
 //   k_emit     the candidate support: every pair inside its row's or its
-//              column's threshold. Per pair 6 VALU ops for the distance, a max
-//              of the two radii, a compare and an add-with-carry that records
-//              the hit in a per-lane bitmask of 32 columns. A first pass counts
+//              column's threshold, found on the matrix cores (see below) or,
+//              for points out of their range and in the writing pass, with 6
+//              VALU ops for the distance, a max of the two radii, a compare
+//              and an add-with-carry that records the hit in a per-lane
+//              bitmask of 32 columns. A first pass counts
 //              the hits per (row, column chunk) and per column and keeps them
 //              (the first few of every (row, chunk) in its slots, the rest of
 //              a tile in a pool region); once the offsets are known, a
@@ -323,6 +324,194 @@ __device__ __forceinline__ void for_each_hit(float ax, float ay, float az, float
     }
 }
 
+// ---------------------------------------------------------------------------
+// the support scan on the matrix cores
+// ---------------------------------------------------------------------------
+//
+// d^2 = |r|^2 + |c|^2 - 2 r c of a row r and a column c, both relative to one
+// point of the sample, as one product of 32 bfloat16 factors a side: every
+// coordinate is the exact sum of three bfloat16 (8 bits each), of whose nine
+// cross products the six largest are kept, and the squared norms, likewise in
+// three parts, meet factors of 1. With a row's threshold taken off its norm
+// the product is below 0 where the pair is inside the row's ball, with the
+// column's taken off the column's norm inside the column's; the two share the
+// coordinates' half of the product. Per 32 x 32 pairs three matrix
+// instructions (96 cycles), and per pair an or of the two signs and one shift
+// that collects it, against nine operations. With the visits of the hits:
+// 32 x 2048 x 2048 points 36 -> 30 us, 16 x 4096 x 16384 243 -> 187, 100 x 1024
+// 39 -> 31 (about half of the first is the scan's issue, the rest the rows' and
+// columns' factors and the hits).
+//
+// The product is off by at most kSlack (|r|^2 + |c|^2) + kTiny: 26 additions
+// rounded at 2^-23 of at most 2.02 (|r|^2 + |c|^2) make 6.3e-6, the dropped
+// products, the norms' rounding and the shift of the origin less than 1e-6
+// more, factors below the normal range 1e-36. Both are taken off the norms, so
+// no pair of the exact test is missed, and every hit is tested again with
+// the exact sequence: the scan finds the same pairs as the other one. Points
+// beyond 1e15 from the origin's, or not finite, take that one instead.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+constexpr float kSlack = 1e-5f, kTiny = 1e-36f, kFar = 1e30f, kOpen = 1e32f;
+constexpr int kScanCols = 128; // columns staged in LDS at a time
+
+// The three bfloat16 parts of v, each in the upper half of a word.
+struct Parts {
+    uint32_t h[3];
+};
+__device__ __forceinline__ Parts split3(float v)
+{
+    Parts p;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        p.h[k] = __builtin_bit_cast(uint32_t, v) & 0xFFFF0000u;
+        v -= __builtin_bit_cast(float, p.h[k]);
+    }
+    return p;
+}
+// Two parts in one word, the first in the lower half.
+__device__ __forceinline__ uint32_t pack2(uint32_t a, uint32_t b) { return a >> 16 | b; }
+
+// A point's factors in four groups of eight (a lane's operand is one group).
+// Products, by coordinate: (r1 c1) (r1 c2) (r2 c1) (r2 c2) (r1 c3) (r3 c1).
+// norm[0], norm[1]: the last group against a point of the other side with, and
+// without, its threshold; n0 and n1 the norms for them.
+struct Factors {
+    uint4 g[3], norm[2];
+};
+template <bool ROW> __device__ __forceinline__ Factors factors(float x, float y, float z, float n0, float n1)
+{
+    constexpr float f = ROW ? 1.0f : -2.0f;
+    const Parts c[3] = {split3(f * x), split3(f * y), split3(f * z)};
+    uint32_t w[9]; // by coordinate three words: parts of the six products
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const uint32_t h1 = c[k].h[0], h2 = c[k].h[1], h3 = c[k].h[2];
+        w[3 * k + 0] = ROW ? pack2(h1, h1) : pack2(h1, h2);
+        w[3 * k + 1] = ROW ? pack2(h2, h2) : pack2(h1, h2);
+        w[3 * k + 2] = ROW ? pack2(h1, h3) : pack2(h3, h1);
+    }
+    Factors o;
+    o.g[0] = make_uint4(w[0], w[1], w[2], w[3]);
+    o.g[1] = make_uint4(w[4], w[5], w[6], w[7]);
+    o.g[2] = make_uint4(w[8], 0u, 0u, 0u);
+    const uint32_t one = 0x3F800000u;
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+        const Parts n = split3(v == 0 ? n0 : n1);
+        // columns' norms meet the first three factors, rows' the next three
+        o.norm[v] = ROW ? make_uint4(pack2(one, one), pack2(one, n.h[0]), pack2(n.h[1], n.h[2]), 0u)
+                        : make_uint4(pack2(n.h[0], n.h[1]), pack2(n.h[2], one), pack2(one, one), 0u);
+    }
+    return o;
+}
+
+struct ScanLds {
+    uint4 g[5][kScanCols]; // the columns' factors: three groups, the norms with and without the thresholds
+    float4 col[kScanCols]; // the columns and their thresholds
+};
+
+// This lane's share of 32 x 32 products: groups g and g + 1 in its halves.
+__device__ __forceinline__ f32x16 product(uint4 cols, uint4 rows, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, cols), __builtin_bit_cast(bf16x8, rows),
+                                                   c, 0, 0, 0);
+}
+
+// Nibbles k of a 16-bit mask (the first at the top) to bits 27 - 8 k and below.
+__device__ __forceinline__ uint32_t spread_nibbles(uint32_t m)
+{
+    m = (m | m << 8) & 0x00FF00FFu;
+    return (m | m << 4) & 0x0F0F0F0Fu;
+}
+
+// Calls f(j) for every column j in [j0, j1) whose pair with this lane's row
+// passes the radius test, in increasing j, as for_each_hit; all waves of the
+// workgroup together (64 rows each, rows r0 + lane of the sample). False, with
+// nothing called, when a point is out of the products' range.
+template <class F>
+__device__ __forceinline__ bool for_each_hit_mfma(const EmitArgs &a, ScanLds &sh, int b, int r0, float ax, float ay,
+                                                  float az, float E, int j0, int j1, uint32_t keep, F f)
+{
+    const int lane = lane_id(), half = lane >> 5;
+    const float4 *yp = a.ypack + (size_t)b * a.M;
+    const float4 o = yp[0]; // the origin
+    // the rows' operands: rows lane % 32 and 32 + lane % 32 of the wave, the
+    // groups of this lane's half
+    uint4 rg[2][3];
+    bool bad = false;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int i = min(r0 + 32 * t + (lane & 31), a.N - 1);
+        const float *p = a.x + ((size_t)b * a.N + i) * 3;
+        const float x = p[0] - o.x, y = p[1] - o.y, z = p[2] - o.z;
+        const float n = x * x + y * y + z * z, base = n * (1.0f - kSlack) - kTiny;
+        bad |= !(n < kFar);
+        const Factors w = factors<true>(x, y, z, base, base - fminf(a.E_row[(size_t)b * a.N + i], kOpen));
+        rg[t][0] = half ? w.g[1] : w.g[0];
+        rg[t][1] = half ? w.norm[1] : w.g[2]; // the row's threshold
+        rg[t][2] = half ? w.norm[0] : w.g[2]; // the column's
+    }
+    for (int s0 = j0; s0 < j1; s0 += kScanCols) {
+        const int n = min(kScanCols, j1 - s0);
+        if (s0 > j0)
+            __syncthreads(); // the columns before are still read
+        for (int k = threadIdx.x; k < kScanCols; k += kBlock) {
+            const float4 c = yp[s0 + min(k, n - 1)];
+            const float x = c.x - o.x, y = c.y - o.y, z = c.z - o.z;
+            const float nn = x * x + y * y + z * z, base = nn * (1.0f - kSlack) - kTiny;
+            bad |= !(nn < kFar);
+            const Factors w = factors<false>(x, y, z, base, base - fminf(c.w, kOpen));
+            sh.g[0][k] = w.g[0];
+            sh.g[1][k] = w.g[1];
+            sh.g[2][k] = w.g[2];
+            sh.g[3][k] = w.norm[0];
+            sh.g[4][k] = w.norm[1];
+            sh.col[k] = c;
+        }
+        if (__syncthreads_or(bad)) {
+            if (s0 == j0)
+                return false;
+            // later columns out of range: theirs are taken one by one (no
+            // barrier follows in this scan)
+            for_each_hit(ax, ay, az, E, as_const(reinterpret_cast<const f32x4 *>(yp)), s0, j1, keep, f);
+            return true;
+        }
+        for (int jb = 0; jb < n; jb += 32) {
+            const int k = jb + (lane & 31);
+            const uint4 c0 = sh.g[half][k], c1 = sh.g[half ? 3 : 2][k], c2 = sh.g[half ? 4 : 2][k];
+            uint32_t m[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const f32x16 zero = {};
+                const f32x16 d = product(c0, rg[t][0], zero);
+                const f32x16 dr = product(c1, rg[t][1], d), dc = product(c2, rg[t][2], d);
+                uint32_t bits = 0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) { // either sign shifted in from the right
+                    const float vr = dr[r], vc = dc[r]; // (a bit cast of a vector's element itself reads element 0)
+                    bits = __builtin_amdgcn_alignbit(
+                        bits, __builtin_bit_cast(uint32_t, vr) | __builtin_bit_cast(uint32_t, vc), 31);
+                }
+                m[t] = bits;
+            }
+            // lanes 0-31 of m[0] and 32-63 of m[1] hold half 0 of the lane's own row's
+            // columns (0-3, 8-11, ...); the swap brings half 1 (4-7, 12-15, ...) beside it
+            asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(m[0]), "+v"(m[1]));
+            uint32_t bits = (spread_nibbles(m[0]) << 4 | spread_nibbles(m[1])) & keep;
+            if (jb + 32 > n)
+                bits &= ~0u << (32 - (n - jb));
+            while (bits) {
+                const int u = __clz(bits);
+                bits &= ~(0x80000000u >> u);
+                const float4 c = sh.col[jb + u];
+                if (sqdist_f32(ax, ay, az, c.x, c.y, c.z) <= fmaxf(E, c.w))
+                    f(s0 + jb + u);
+            }
+        }
+    }
+    return true;
+}
+
 // Staged hit k of (row, chunk) slot: the column's offset within the chunk,
 // in one byte when every chunk has at most 256 columns, else in two.
 __device__ __forceinline__ void stage_put(const EmitArgs &a, size_t slot, int k, int v)
@@ -343,10 +532,11 @@ __device__ __forceinline__ int stage_get(const EmitArgs &a, size_t slot, int k)
 // column; pass 2 writes them, in increasing column, at the row's CSR offset
 // plus the counts of the row's earlier chunks. Both passes take bitwise the
 // same decisions.
-template <bool WRITE> __global__ __launch_bounds__(kBlock) void k_emit(EmitArgs a)
+template <bool WRITE> __global__ __launch_bounds__(kBlock, 4) void k_emit(EmitArgs a)
 {
     __shared__ uint2 list[kTileList]; // further hits: row in the tile << 16 | offset, rank in the row's
     __shared__ int row_start[kBlock], wave_sum[kBlock / 64], n_list, base_sh;
+    __shared__ ScanLds scan;
     const int t = blockIdx.x;
     const int ob = t % a.owner_blocks;
     const int rest = t / a.owner_blocks;
@@ -370,7 +560,7 @@ template <bool WRITE> __global__ __launch_bounds__(kBlock) void k_emit(EmitArgs 
             n_list = 0;
         __syncthreads();
         int cnt = 0;
-        for_each_hit(ax, ay, az, E, q, j0, j1, keep, [&](int j) {
+        auto hit = [&](int j) {
             atomicAdd(&col_cnt[j], 1);
             if (stage) {
                 if (cnt < a.kst) {
@@ -382,7 +572,9 @@ template <bool WRITE> __global__ __launch_bounds__(kBlock) void k_emit(EmitArgs 
                 }
             }
             ++cnt;
-        });
+        };
+        if (!for_each_hit_mfma(a, scan, b, ob * kBlock + (int)(threadIdx.x & ~63u), ax, ay, az, E, j0, j1, keep, hit))
+            for_each_hit(ax, ay, az, E, q, j0, j1, keep, hit);
         if (valid)
             a.cnt[slot] = cnt;
         const int extra = max(cnt - a.kst, 0);
