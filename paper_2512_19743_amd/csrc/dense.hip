@@ -657,6 +657,11 @@ __device__ __forceinline__ void emit_pair(const EmitArgs &a, int pos, int row, i
     }
 }
 
+// Further hits of a row taken at a time by the compaction: one at a time, the
+// slot's atomic and the load before it were waited out for each of a long
+// row's (16 x 4096 x 16384 points with uniform predictions: 137 -> 125 us).
+constexpr int kSpillBatch = 8;
+
 template <bool PLACE> __device__ __forceinline__ void emit_compact_thread(const EmitArgs &a, int64_t g)
 {
     if (g >= (int64_t)a.B * a.N * a.S)
@@ -683,9 +688,28 @@ template <bool PLACE> __device__ __forceinline__ void emit_compact_thread(const 
     if (n > a.kst) { // the row's further hits, in increasing column, from the tile's region
         const uint16_t *reg = a.spill + base;
         const uint16_t *mine = reg + kBlock + reg[i % kBlock];
-        for (int k = a.kst; k < n; ++k) {
-            const int jj = mine[k - a.kst];
-            emit_pair<PLACE>(a, pos + k, row, i, gc0 + jj, j0 + jj);
+        for (int k0 = a.kst; k0 < n; k0 += kSpillBatch) { // loads, and the slots' atomics, in flight together
+            int jj[kSpillBatch], p[kSpillBatch];
+#pragma unroll
+            for (int u = 0; u < kSpillBatch; ++u)
+                jj[u] = mine[min(k0 + u, n - 1) - a.kst];
+            if (PLACE) {
+#pragma unroll
+                for (int u = 0; u < kSpillBatch; ++u)
+                    if (k0 + u < n)
+                        p[u] = a.col_ptr[gc0 + jj[u]] + atomicAdd(&a.col_fill[gc0 + jj[u]], 1);
+            }
+#pragma unroll
+            for (int u = 0; u < kSpillBatch; ++u)
+                if (k0 + u < n) {
+                    a.csr_col[pos + k0 + u] = j0 + jj[u];
+                    a.csr_row[pos + k0 + u] = row;
+                    if (PLACE) {
+                        a.tmp_row[p[u]] = i;
+                        a.tmp_src[p[u]] = pos + k0 + u;
+                        a.csc_col[p[u]] = gc0 + jj[u];
+                    }
+                }
         }
     }
 }

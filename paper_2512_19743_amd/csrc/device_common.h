@@ -36,11 +36,20 @@ __device__ __forceinline__ double dist_f64(const float *a, const float *b)
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
-// Number of entries of a[s0, s1) below key: four loads in flight at a time
-// (a loop of one load per step waits out every load in turn).
+// Number of entries of a[s0, s1) below key: sixteen loads in flight at a time,
+// then four (a loop of one load per step waits out every load in turn).
 __device__ __forceinline__ int count_below(const int32_t *a, int s0, int s1, int key)
 {
     int n = 0, q = s0;
+    for (; q + 16 <= s1; q += 16) {
+        int v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            v[u] = a[q + u];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            n += v[u] < key;
+    }
     for (; q + 4 <= s1; q += 4) {
         const int v0 = a[q], v1 = a[q + 1], v2 = a[q + 2], v3 = a[q + 3];
         n += (v0 < key) + (v1 < key) + (v2 < key) + (v3 < key);
@@ -181,6 +190,23 @@ template <int CAP, class F> __device__ __forceinline__ void each_owner(int G, in
         lanes = 64;
         lane = lane_id();
         mine = true;
+    }
+}
+
+// use(load(k), k) for k = k0, k0 + step, ... below n, SB loads in flight at a
+// time (load must not depend on what use writes).
+template <int SB, class Load, class Use>
+__device__ __forceinline__ void strided(int k0, int n, int step, Load load, Use use)
+{
+    for (int k = k0; k < n; k += step * SB) {
+        decltype(load(0)) v[SB];
+#pragma unroll
+        for (int u = 0; u < SB; ++u)
+            v[u] = load(min(k + u * step, n - 1));
+#pragma unroll
+        for (int u = 0; u < SB; ++u)
+            if (k + u * step < n)
+                use(v[u], k + u * step);
     }
 }
 

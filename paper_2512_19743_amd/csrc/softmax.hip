@@ -56,6 +56,10 @@ __host__ inline int softmax_lanes(int64_t owners, int64_t pairs)
 // row adjoint are held to four waves per SIMD: the bound costs them 40 and 16
 // bytes of scratch in the long-segment loops, without it three waves.
 constexpr int kSmCache = 8;
+// Pairs a lane of a long segment takes at a time past those (loads in flight):
+// 6 x 1900 x 1500 with fallback rows 1.73 -> 1.59 ms; with four the registers
+// cost the other owners as much (4 x 65536: row adjoint 72 -> 96 us).
+constexpr int kLongBatch = 2;
 
 // Pair t (row-major position; row i, column j of sample b, the k-th entry of
 // its column) with P0 into the per-sample Sinkhorn pieces of both orders.
@@ -121,11 +125,9 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
             fl[c] = k < n ? d.flags[tt[c]] : 0;
         }
     }
-    auto other = [&](int k, float &x, float &y, float &z) {
+    auto other = [&](int k) { // the other point of pair k
         const float *q = oth + 3 * (size_t)idx[s0 + k];
-        x = q[0];
-        y = q[1];
-        z = q[2];
+        return make_float3(q[0], q[1], q[2]);
     };
 
     // minimum and second minimum among the stored pairs (single precision)
@@ -134,11 +136,9 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
     for (int c = 0; c < kSmCache; ++c)
         if (lg + G * c < n)
             am.see(s0 + lg + G * c, sqdist_f32(a0, a1, a2, ox[c], oy[c], oz[c]), m);
-    for (int k = lg + G * kSmCache; k < n; k += G) {
-        float x, y, z;
-        other(k, x, y, z);
-        am.see(s0 + k, sqdist_f32(a0, a1, a2, x, y, z), m);
-    }
+    strided<kLongBatch>(lg + G * kSmCache, n, G, other, [&](const float3 &q, int k) {
+        am.see(s0 + k, sqdist_f32(a0, a1, a2, q.x, q.y, q.z), m);
+    });
     int q1, q2;
     am.resolve(&q1, &q2, G);
     if (q1 == INT_MAX || q2 == INT_MAX) { // cannot happen: both minima are always emitted
@@ -180,9 +180,8 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
                 v += lg + G * c == k ? dc[c] : 0.0;
             return group_sum(v, G);
         }
-        float x, y, z;
-        other(k, x, y, z);
-        return dist3(a0, a1, a2, x, y, z);
+        const float3 v = other(k);
+        return dist3(a0, a1, a2, v.x, v.y, v.z);
     };
     const double c1 = dist_at(q1), c2 = dist_at(q2);
     const double gap = (c2 - c1) + p.delta;
@@ -206,13 +205,11 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
                 zsum += s;
         }
     }
-    for (int k = lg + G * kSmCache; k < n; k += G) {
-        float x, y, z;
-        other(k, x, y, z);
-        const double s = exp(-T * (dist3(a0, a1, a2, x, y, z) - c1));
+    strided<kLongBatch>(lg + G * kSmCache, n, G, other, [&](const float3 &q, int) {
+        const double s = exp(-T * (dist3(a0, a1, a2, q.x, q.y, q.z) - c1));
         if (s >= p.tau)
             zsum += s;
-    }
+    });
     zsum = group_sum(zsum, G);
 
     // P = s / Z on the kept pairs; rows store C, columns P0 = (P_row + P_col)/2
@@ -238,13 +235,27 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
     for (int c = 0; c < kSmCache; ++c)
         if (lg + G * c < n)
             write(lg + G * c, tt[c], dc[c], sv[c], prow[c], fl[c]);
-    for (int k = lg + G * kSmCache; k < n; k += G) {
-        float x, y, z;
-        other(k, x, y, z);
-        const double c = dist3(a0, a1, a2, x, y, z);
-        const int t = ROWS ? s0 + k : d.csc_perm[s0 + k];
-        write(k, t, c, exp(-T * (c - c1)), ROWS ? 0.0f : d.p_row[t], ROWS ? 0 : d.flags[t]);
-    }
+    struct Far {
+        float3 q;
+        int t;
+        float pr;
+        uint8_t f;
+    };
+    strided<kLongBatch>(
+        lg + G * kSmCache, n, G,
+        [&](int k) {
+            Far v{other(k), s0 + k, 0.0f, 0};
+            if (!ROWS) {
+                v.t = d.csc_perm[s0 + k];
+                v.pr = d.p_row[v.t];
+                v.f = d.flags[v.t];
+            }
+            return v;
+        },
+        [&](const Far &v, int k) {
+            const double c = dist3(a0, a1, a2, v.q.x, v.q.y, v.q.z);
+            write(k, v.t, c, exp(-T * (c - c1)), v.pr, v.f);
+        });
     if (lg == 0) {
         (ROWS ? d.T_row : d.T_col)[o] = T;
         (ROWS ? d.C1_row : d.C1_col)[o] = c1;
@@ -426,45 +437,54 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
             pq[c] = kq[c] ? exp(-T * (cq[c] - c1)) : 0.0;
             zsum += pq[c];
         }
-        for (int k = lg + G * NC; k < n; k += G) {
-            const int t = d.csc_perm[s0 + k];
-            if (d.flags[t] & 2)
-                zsum += exp(-T * (d.cost[t] - c1));
-        }
+        struct CF {
+            double c;
+            uint8_t f;
+        };
+        strided<kLongBatch>(
+            lg + G * NC, n, G,
+            [&](int k) {
+                const int t = d.csc_perm[s0 + k];
+                return CF{d.cost[t], d.flags[t]};
+            },
+            [&](const CF &v, int) {
+                if (v.f & 2)
+                    zsum += exp(-T * (v.c - c1));
+            });
         zsum = group_sum(zsum, G);
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             pq[c] = kq[c] ? pq[c] / zsum : 0.0;
     }
-    // P of a kept pair past the cached ones (column-major entry q, row-major position t)
-    auto p_at = [&](int q, int t) -> double {
-        if constexpr (DP)
-            return exp(-T * (d.cost[t] - c1)) / zsum;
-        else
-            return (double)d.p_col[q];
+    // the pairs past the cached ones
+    struct Far {
+        int t;
+        double w, adj, c;
+        float p;
+        uint8_t f;
+    };
+    auto far = [&](int k) {
+        const int q = s0 + k, t = d.csc_perm[q];
+        return Far{t, wb * al[d.csc_row[q]], d.L == 0 ? 0.0 : d.adj[t], d.cost[t], DP ? 0.0f : d.p_col[q], d.flags[t]};
+    };
+    auto far_a = [&](const Far &v) { return sym_weight(p, v.f) * __builtin_fma(v.w, v.c, v.adj); };
+    auto far_p = [&](const Far &v) -> double {
+        if (!(v.f & 2))
+            return 0.0;
+        return DP ? exp(-T * (v.c - c1)) / zsum : (double)v.p;
     };
     double sigma = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         sigma += kq[c] ? (double)pq[c] * aq[c] : 0.0;
-    for (int k = lg + G * NC; k < n; k += G) {
-        const int t = d.csc_perm[s0 + k];
-        const uint8_t f = d.flags[t];
-        if (f & 2)
-            sigma += p_at(s0 + k, t) * (sym_weight(p, f) * p0bar(d, t, wb * al[d.csc_row[s0 + k]], d.cost[t]));
-    }
+    strided<kLongBatch>(lg + G * NC, n, G, far, [&](const Far &v, int) { sigma += far_p(v) * far_a(v); });
     sigma = group_sum(sigma, G);
     double tbar = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         tbar -= kq[c] ? (double)pq[c] * (aq[c] - sigma) * (cq[c] - c1) : 0.0;
-    for (int k = lg + G * NC; k < n; k += G) {
-        const int t = d.csc_perm[s0 + k];
-        const uint8_t f = d.flags[t];
-        if (f & 2)
-            tbar -= p_at(s0 + k, t) *
-                    (sym_weight(p, f) * p0bar(d, t, wb * al[d.csc_row[s0 + k]], d.cost[t]) - sigma) * (d.cost[t] - c1);
-    }
+    strided<kLongBatch>(lg + G * NC, n, G, far,
+                        [&](const Far &v, int) { tbar -= far_p(v) * (far_a(v) - sigma) * (v.c - c1); });
     tbar = group_sum(tbar, G);
     const double gapbar = gapbar_scale * tbar;
     auto gap_terms = [&](int q, double cb) {
@@ -480,15 +500,9 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
         if (k < n)
             d.cbar[tq[c]] = gap_terms(s0 + k, kq[c] ? -T * (double)pq[c] * (aq[c] - sigma) : 0.0);
     }
-    for (int k = lg + G * NC; k < n; k += G) {
-        const int t = d.csc_perm[s0 + k];
-        const uint8_t f = d.flags[t];
-        const double cb =
-            (f & 2) ? -T * p_at(s0 + k, t) *
-                          (sym_weight(p, f) * p0bar(d, t, wb * al[d.csc_row[s0 + k]], d.cost[t]) - sigma)
-                    : 0.0;
-        d.cbar[t] = gap_terms(s0 + k, cb);
-    }
+    strided<kLongBatch>(lg + G * NC, n, G, far, [&](const Far &v, int k) {
+        d.cbar[v.t] = gap_terms(s0 + k, -T * far_p(v) * (far_a(v) - sigma));
+    });
 }
 
 template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_softmax(DevPlan d, Params p)
@@ -544,43 +558,50 @@ __device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p,
             pq[c] = kq[c] ? exp(-T * (cq[c] - c1)) : 0.0;
             zsum += pq[c];
         }
-        for (int k = lg + G * NC; k < n; k += G)
-            if (d.flags[t0 + k] & 1)
-                zsum += exp(-T * (d.cost[t0 + k] - c1));
+        struct CF {
+            double c;
+            uint8_t f;
+        };
+        strided<kLongBatch>(
+            lg + G * NC, n, G, [&](int k) { return CF{d.cost[t0 + k], d.flags[t0 + k]}; },
+            [&](const CF &v, int) {
+                if (v.f & 1)
+                    zsum += exp(-T * (v.c - c1));
+            });
         zsum = group_sum(zsum, G);
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             pq[c] = kq[c] ? pq[c] / zsum : 0.0;
     }
-    // P of a kept pair past the cached ones
-    auto p_at = [&](int t) -> double {
-        if constexpr (DP)
-            return exp(-T * (d.cost[t] - c1)) / zsum;
-        else
-            return (double)d.p_row[t];
+    // the pairs past the cached ones
+    struct Far {
+        int j;
+        double b, adj, c;
+        float p;
+        uint8_t f;
+    };
+    auto far = [&](int k) {
+        const int t = t0 + k, j = d.csr_col[t];
+        return Far{j, bl[j], d.L == 0 ? 0.0 : d.adj[t], d.cost[t], DP ? 0.0f : d.p_row[t], d.flags[t]};
+    };
+    auto far_a = [&](const Far &v) { return sym_weight(p, v.f) * __builtin_fma(gl * al * v.b, v.c, v.adj); };
+    auto far_p = [&](const Far &v) -> double {
+        if (!(v.f & 1))
+            return 0.0;
+        return DP ? exp(-T * (v.c - c1)) / zsum : (double)v.p;
     };
     double sigma = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         sigma += kq[c] ? (double)pq[c] * aq[c] : 0.0;
-    for (int k = lg + G * NC; k < n; k += G) {
-        const int t = t0 + k;
-        const uint8_t f = d.flags[t];
-        if (f & 1)
-            sigma += p_at(t) * (sym_weight(p, f) * p0bar(d, t, gl * al * bl[d.csr_col[t]], d.cost[t]));
-    }
+    strided<kLongBatch>(lg + G * NC, n, G, far, [&](const Far &v, int) { sigma += far_p(v) * far_a(v); });
     sigma = group_sum(sigma, G);
     double tbar = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         tbar -= kq[c] ? (double)pq[c] * (aq[c] - sigma) * (cq[c] - c1) : 0.0;
-    for (int k = lg + G * NC; k < n; k += G) {
-        const int t = t0 + k;
-        const uint8_t f = d.flags[t];
-        if (f & 1)
-            tbar -= p_at(t) * (sym_weight(p, f) * p0bar(d, t, gl * al * bl[d.csr_col[t]], d.cost[t]) - sigma) *
-                    (d.cost[t] - c1);
-    }
+    strided<kLongBatch>(lg + G * NC, n, G, far,
+                        [&](const Far &v, int) { tbar -= far_p(v) * (far_a(v) - sigma) * (v.c - c1); });
     tbar = group_sum(tbar, G);
     const double gapbar = gscale * tbar;
     double gx = 0.0, gy = 0.0, gz = 0.0;
@@ -607,14 +628,16 @@ __device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p,
         if (k < n)
             add(t0 + k, jq[c], DP ? d.cbar[t0 + k] : cbq[c], kq[c], (double)pq[c], aq[c], cq[c], p0q[c]);
     }
-    for (int k = lg + G * NC; k < n; k += G) {
-        const int t = t0 + k;
-        const uint8_t f = d.flags[t];
-        const bool kept = (f & 1) != 0;
-        const int j = d.csr_col[t];
-        add(t, j, d.cbar[t], kept, kept ? p_at(t) : 0.0,
-            sym_weight(p, f) * p0bar(d, t, gl * al * bl[j], d.cost[t]), d.cost[t], d.p0r[t]);
-    }
+    struct FarG {
+        Far v;
+        double cb;
+        float p0;
+    };
+    strided<1>(
+        lg + G * NC, n, G, [&](int k) { return FarG{far(k), d.cbar[t0 + k], d.p0r[t0 + k]}; },
+        [&](const FarG &v, int k) {
+            add(t0 + k, v.v.j, v.cb, (v.v.f & 1) != 0, far_p(v.v), far_a(v.v), v.v.c, v.p0);
+        });
     gx = group_sum(gx, G);
     gy = group_sum(gy, G);
     gz = group_sum(gz, G);
@@ -641,14 +664,24 @@ __device__ __forceinline__ void grad_y_owner(const DevPlan &d, const Params &p, 
     const float *yc = d.y + (size_t)gc * 3;
     const float *xb = d.x + (size_t)b * d.N * 3;
     double gx = 0.0, gy = 0.0, gz = 0.0;
-    for (int q = d.col_ptr[gc] + lg; q < d.col_ptr[gc + 1]; q += G) {
-        const int t = d.csc_perm[q];
-        const float *xi = xb + 3 * (size_t)d.csc_row[q];
-        const double w = d.cbar[t] / (d.cost[t] + p.eps_dist);
-        gx -= w * ((double)xi[0] - (double)yc[0]);
-        gy -= w * ((double)xi[1] - (double)yc[1]);
-        gz -= w * ((double)xi[2] - (double)yc[2]);
-    }
+    const int s0 = d.col_ptr[gc], n = d.col_ptr[gc + 1] - s0;
+    struct V {
+        double cb, c;
+        float3 x;
+    };
+    strided<kLongBatch>(
+        lg, n, G,
+        [&](int k) {
+            const int t = d.csc_perm[s0 + k];
+            const float *xi = xb + 3 * (size_t)d.csc_row[s0 + k];
+            return V{d.cbar[t], d.cost[t], make_float3(xi[0], xi[1], xi[2])};
+        },
+        [&](const V &v, int) {
+            const double w = v.cb / (v.c + p.eps_dist);
+            gx -= w * ((double)v.x.x - (double)yc[0]);
+            gy -= w * ((double)v.x.y - (double)yc[1]);
+            gz -= w * ((double)v.x.z - (double)yc[2]);
+        });
     gx = group_sum(gx, G);
     gy = group_sum(gy, G);
     gz = group_sum(gz, G);
