@@ -678,10 +678,8 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
         const size_t n_sort = (size_t)B * pad_x + (size_t)B * pad_y;
         sa.ctr = dv.ctr;
         crows.waves = ceil_div(N, kScanRows);
-        if (std::max(N, M) > kSortChunkPoints) // chunked sort: the frame from partial boxes
-            sa.frame_slices = ceil_div((int64_t)N + M, 16384);
+        sa.frame_slices = ceil_div((int64_t)N + M, kSortSlice);
         // the scratch of both scans in one allocation
-        Box *batch_x = nullptr, *batch_y = nullptr;
         float *E_row = nullptr;
         float4 *ypack = nullptr;
         auto lay = [&](Carve &c) {
@@ -693,9 +691,11 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
             sa.sy = c.take<float4>((size_t)B * pad_y);
             sa.box_x = c.take<Box>((size_t)B * pad_x / kRun);
             sa.box_y = c.take<Box>((size_t)B * pad_y / kRun);
-            sa.frame_part = sa.frame_slices ? c.take<float>((size_t)B * sa.frame_slices * 6) : nullptr;
-            batch_x = c.take<Box>((size_t)B * batches(pad_x));
-            batch_y = c.take<Box>((size_t)B * batches(pad_y));
+            // read before the sorted points are written: 24 bytes for every
+            // kSortSlice points in 16 bytes for every point of the larger cloud
+            sa.frame_part = (float *)(N >= M ? sa.sx : sa.sy);
+            sa.batch_x = c.take<Box>((size_t)B * batches(pad_x));
+            sa.batch_y = c.take<Box>((size_t)B * batches(pad_y));
             crows.m12s = c.take<float2>((size_t)B * pad_x);
             ccols.m12s = c.take<float2>((size_t)B * pad_y);
             E_row = c.take<float>((size_t)B * pad_x);
@@ -728,14 +728,13 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
         ccols.pad_own = pad_y;
         ccols.pad_bc = pad_x;
         ccols.waves = ceil_div(M, kScanRows);
-        crows.bc_batch = batch_y;
-        ccols.bc_batch = batch_x;
+        crows.bc_batch = sa.batch_y;
+        ccols.bc_batch = sa.batch_x;
         if (tmp.failed || dense_tmp.failed || keep.failed)
             return fail(APML_ERR_OUT_OF_MEMORY, "device allocation failed (statistics)");
         {
             PhaseTimer pt(PH_STATS, s, timed);
             HIP_TRY(launch_spatial_sort(sa, s)); // also clears the counters
-            launch_batch_boxes(sa.box_x, sa.box_y, batch_x, batch_y, B, pad_x, pad_y, false, s);
             launch_cull_top2(crows, ccols, B, dv.ctr, s);
             HIP_TRY(hipGetLastError());
             CullFinalizeDir fr{crows.m12s, sa.sx, dv.m12_row, E_row, nullptr, nullptr, nullptr, nullptr, N, pad_x,
@@ -746,7 +745,7 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
             pt.stop();
         }
         // the column batches again, now with their largest emission threshold
-        launch_batch_boxes(sa.box_x, sa.box_y, batch_x, batch_y, B, pad_x, pad_y, true, s);
+        launch_batch_boxes(sa.box_y, sa.batch_y, B, pad_y, s);
         HIP_TRY(hipGetLastError());
 
         // ---- dense scan 2: candidate support -----------------------------
@@ -756,7 +755,7 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
         ca.sy = sa.sy;
         ca.box_x = sa.box_x;
         ca.box_y = sa.box_y;
-        ca.batch_y = batch_y;
+        ca.batch_y = sa.batch_y;
         ca.B = B;
         ca.N = N;
         ca.M = M;

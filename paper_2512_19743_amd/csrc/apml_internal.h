@@ -178,23 +178,20 @@ struct SpatialArgs {
     const float *x, *y; // [B, N, 3], [B, M, 3]
     int B, N, M, pad_x, pad_y;
     uint32_t *key[2], *val[2]; // scratch: [B * pad_x + B * pad_y] each
-    float *frame_part;         // scratch [B][frame_slices][6] when a cloud exceeds one sort chunk, else NULL
+    float *frame_part;         // scratch [B][frame_slices][6]; may be part of sx or sy
     int frame_slices;
     float4 *sx, *sy;           // out: sorted clouds
     Box *box_x, *box_y;        // out: boxes of the runs
+    Box *batch_x, *batch_y;    // out: boxes of the batches
     Counters *ctr;             // cleared here
 };
 // Batches of 64 runs (2048 sorted points): the scans test a batch's box
 // before its runs'.
 __host__ __device__ inline int batches(int pad) { return (pad / kRun + 63) / 64; }
-// The box of every batch of runs of both sorted clouds (columns_only: of the
-// columns, hi.w the largest of the runs' hi.w).
-void launch_batch_boxes(const Box *box_x, const Box *box_y, Box *batch_x, Box *batch_y, int B, int pad_x, int pad_y,
-                        bool columns_only, hipStream_t s);
-size_t spatial_sort_lds();
-// Points one workgroup of the spatial sort takes; larger clouds are sorted in
-// chunks, then merged.
-constexpr int kSortChunkPoints = 8192;
+// The box of every batch of the columns' runs again, hi.w the largest of the
+// runs' hi.w.
+void launch_batch_boxes(const Box *box, Box *batch, int B, int pad, hipStream_t s);
+constexpr int kSortSlice = 4096; // points of both clouds whose bounding box one workgroup takes
 hipError_t launch_spatial_sort(const SpatialArgs &a, hipStream_t s);
 
 // One direction of the minimum / second-minimum scan: owners (X for rows, Y

@@ -1394,11 +1394,15 @@ constexpr int kSG = 4;
 constexpr int kSB = 8;
 constexpr int kSBRev = 4;
 
-__global__ __launch_bounds__(kBlock) void k_fill_ones(double *a, int n)
+// Both sides' first scalings.
+__global__ __launch_bounds__(kBlock) void k_fill_ones(DevPlan d)
 {
-    const int k = blockIdx.x * kBlock + threadIdx.x;
-    if (k < n)
-        a[k] = 1.0;
+    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int BN = d.B * d.N, BM = d.B * d.M;
+    if (k < BN)
+        d.alpha[k] = 1.0;
+    if (k < BM)
+        d.beta[k] = 1.0;
 }
 
 // Sum over an owner's pairs k = lg, lg + G, ... of f(k, position) with the
@@ -1935,8 +1939,7 @@ void launch_sinkhorn_fwd_steps(const DevPlan &d, double eps, hipStream_t s)
 {
     const int BN = d.B * d.N, BM = d.B * d.M;
     const int gr = steps_lanes(d.nnz, BN), gc = steps_lanes(d.nnz, BM);
-    hipLaunchKernelGGL(k_fill_ones, dim3(blocks_for(BN, kBlock)), dim3(kBlock), 0, s, d.alpha, BN);
-    hipLaunchKernelGGL(k_fill_ones, dim3(blocks_for(BM, kBlock)), dim3(kBlock), 0, s, d.beta, BM);
+    hipLaunchKernelGGL(k_fill_ones, dim3(blocks_for(std::max(BN, BM), kBlock)), dim3(kBlock), 0, s, d);
     for (int l = 1; l <= d.L; ++l) {
         launch_lanes<ColStep>(gc, BM, s, d, l, eps);
         launch_lanes<RowStep>(gr, BN, s, d, l, eps);
