@@ -71,11 +71,12 @@ __device__ __forceinline__ void merge_top2(float &m1, int &k1, float &m2, int &k
 
 // sqrt of a squared distance between float coordinates: 0, or between 1e-90
 // and 1e79, so the reciprocal square root needs none of the library's scaling
-// (0 is taken as 1e-300: its root, 1e-150, is added to nothing smaller than
-// 1e-45). One Goldschmidt step and a residual correction: within an ulp.
+// (1e-300 is added, below an ulp of any s but 0: its root, 1e-150, is added to
+// nothing smaller than 1e-45; a maximum instead would lose a NaN). One
+// Goldschmidt step and a residual correction: within an ulp.
 __device__ __forceinline__ double root(double s)
 {
-    s = __builtin_fmax(s, 1e-300);
+    s += 1e-300;
     const double y = __builtin_amdgcn_rsq(s);
     double g = s * y, h = 0.5 * y;
     const double r = __builtin_fma(-h, g, 0.5);
@@ -84,16 +85,15 @@ __device__ __forceinline__ double root(double s)
     return __builtin_fma(__builtin_fma(-g, g, s), h, g);
 }
 
-// 2^t for t up to 1024 (below -1100: 0): 2^n (1 + f q(f)), n the nearest whole
-// number and |f| <= 1/2, q the polynomial that interpolates (2^f - 1) / f at
+// 2^t for t up to 1024 (below -1100: 0; NaN stays, by f): 2^n (1 + f q(f)), n
+// the nearest whole number and |f| <= 1/2, q the polynomial that interpolates (2^f - 1) / f at
 // eleven Chebyshev nodes (relative error 2e-17 of 2^f, exactly 1 at 0). 17
 // operations against the library exponential's 26, which with the root's 8
 // against 19 bound these kernels (32 x 2048 x 2048 points: k_dz 430 -> 319 us,
 // k_dp0 335 -> 269, k_dpair 701 -> 589 and 443 -> 388).
 __device__ __forceinline__ double exp2_of(double t)
 {
-    t = __builtin_fmax(t, -1100.0);
-    const double n = __builtin_rint(t), f = t - n;
+    const double w = __builtin_rint(t), n = __builtin_fmax(w, -1100.0), f = t - w;
     double q = 4.4549605981865186e-10;
     q = __builtin_fma(q, f, 7.072585949269223e-09);
     q = __builtin_fma(q, f, 1.0178062445845774e-07);

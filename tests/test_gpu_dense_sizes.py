@@ -62,3 +62,20 @@ def test_dense_dimensions_with_many_points(d):
         assert abs(loss[b] - ref.item()) <= LOSS_RTOL * abs(ref.item())
         assert rel_norm(gx[b], x.grad.numpy()) <= GRAD_RTOL
         assert rel_norm(gy[b], y.grad.numpy()) <= GRAD_RTOL
+
+
+# The kernels' own root and exponential keep a NaN: a sample with a point that
+# is not finite shows it in its loss and gradients, and in no other sample's.
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("d", [3, 5])
+def test_dense_points_that_are_not_finite(value, d):
+    rng = np.random.default_rng(300 + d)
+    X, Y = (rng.standard_normal((3, n, d)).astype(np.float32) for n in (70, 130))
+    clean = run_dense(X, Y, gbar=[1.0, 1.0, 1.0], n_iter=3)
+    for cloud in (X, Y):
+        bad = [c.copy() for c in (X, Y)]
+        bad[0 if cloud is X else 1][1, 33, d - 1] = value
+        note(f"dense {value} in cloud {'X' if cloud is X else 'Y'} d={d}")
+        for got, ref in zip(run_dense(*bad, gbar=[1.0, 1.0, 1.0], n_iter=3), clean):
+            assert np.isnan(got[1]).all()
+            assert np.array_equal(got[0], ref[0]) and np.array_equal(got[2], ref[2])
