@@ -1114,8 +1114,9 @@ apml_status run_backward(apml_plan *plan, const float *x, const float *y, const 
     }
     {
         PhaseTimer pt(PH_BWD_SOFTMAX, s, plan->timed);
-        // double-precision P where the reverse sweeps keep the adjoint in
-        // double too (per-iteration sweeps), or where there are none
+        // double-precision P in the batches of the per-iteration sweeps (by
+        // their sizes, also where these replace the per-sample reverse
+        // kernels only), or where there are no sweeps
         const bool double_p = dv.L == 0 || (!plan->sink_fwd && !plan->sink_wide);
         launch_bwd_softmax(dv, plan->kp, double_p, s);
         HIP_TRY(hipGetLastError());

@@ -377,10 +377,10 @@ __device__ __forceinline__ double p0bar(const DevPlan &d, int t, double w, doubl
 // temperature adjoint cancels, and it reaches the argmins multiplied by T / g,
 // large for a small gap: with stored single-precision P the gradient error
 // reached 5e-4 there, and 9e-6 on 16 x 4096 x 16384 points (1.2e-7 with DP).
-// Taken where the reverse sweeps keep the adjoint in double (or there are
-// none); the sweeps that keep it in LDS store it in single precision, which
-// then bounds the error as much (32 samples of 2048 points: 6.7e-6 either
-// way), and P is read as stored. Both cache 4 pairs per lane (the forward 8):
+// Taken where the per-iteration launches take the sweeps (large or unequal
+// clouds) or there are none; elsewhere P is read as stored (32 x 2048 points:
+// gradient error 7e-8 against 64 bits). Both cache 4 pairs per lane (the
+// forward 8):
 // four or more waves per SIMD instead of three (the row kernel held 158
 // registers with 8), and owners rarely have more than 4 pairs per lane
 // (64 samples of 8192 points: adjoint 0.157 -> 0.134 ms; 32 of 2048:
