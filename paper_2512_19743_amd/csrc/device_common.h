@@ -177,7 +177,7 @@ template <bool LDS_ONLY> __device__ __forceinline__ void wg_barrier()
 // points repeated at a cloud's end (padded scans) keep every pair under the
 // uniform fallback, all in a few waves, four to sixteen one after another
 // (6 x 1900 x 1500 points, 40 of each cloud repeated, forward + backward: 1556 ->
-// 1358 us; 16 x 4096 x 16384 and shorter segments unchanged). The lane count is a run-time value so that all uses share one copy of f (two
+// 1358 us). The lane count is a run-time value so that all uses share one copy of f (two
 // copies held 166 instead of 126 registers).
 template <int CAP, class F>
 __device__ __forceinline__ void each_owner(int G, int bid, const LongOwners &w, int n_own, const int32_t *ptr, F f)
