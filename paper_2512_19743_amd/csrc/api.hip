@@ -837,25 +837,6 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
     const int wslots = plan->sink_fwd ? 0 : sinkhorn_slots_wide(N, M, pieces, B);
     plan->sink_wide = wslots > 0;
 
-    // Lists of the rows and columns with more than kLongPairs pairs, where
-    // there are any (the per-iteration launches then take the sweeps) and a
-    // side's owners hold 32 pairs or more on average: few long owners among short
-    // ones don't repay the two launches and the further workgroups (16 x 4096 x
-    // 16384 uniform predictions, 18 pairs a row: 1453 us without lists, 1477 with;
-    // 6 x 1900 x 1500 with fallback rows, 65 to 100: 1556 and 1358). Not in the
-    // caller's fixed scratch, whose size is the caller's own. At most 256
-    // workgroups: a thousand waves, and few to end at once where the list is
-    // short.
-    if (!bumped) {
-        int most[2] = {0, 0};
-        for (int b = 0; b < B; ++b)
-            for (int k = 0; k < 2; ++k)
-                most[k] = std::max(most[k], pieces[4 * b + 2 + k]);
-        for (int k = 0; k < 2; ++k)
-            if (most[k] > kSinkMaxGroup && nnz >= 32 * (int64_t)B * (k ? M : N))
-                (k ? dv.long_col : dv.long_row).blocks =
-                    (int)std::min<int64_t>(256, ((nnz / kLongPairs + 3) / 4 + kXcds - 1) / kXcds * kXcds);
-    }
     // ---- sparse structure -------------------------------------------------
     // (with the per-sample Sinkhorn pieces, in one allocation)
     auto lay_pairs = [&](Carve &c) {
@@ -870,11 +851,6 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
         dv.p0r = c.take<float>(nnz);
         dv.p0c = c.take<float>(nnz);
         dv.cost = c.take<double>(nnz);
-        for (LongOwners *w : {&dv.long_row, &dv.long_col})
-            if (w->blocks > 0) {
-                w->count = c.take<int32_t>(1);
-                w->list = c.take<int32_t>(nnz / kLongPairs);
-            }
         if (plan->sink_fwd) {
             const size_t w = packed_order_words(B, slots);
             for (PackedOrder *pk : {&dv.pk_row, &dv.pk_col}) {
@@ -958,8 +934,6 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
         } else {
             launch_csc_build(dv, ba, s);
         }
-        if (dv.long_row.blocks + dv.long_col.blocks > 0)
-            launch_long_owners(dv, s);
         HIP_TRY(hipGetLastError());
         pt.stop();
     }

@@ -297,23 +297,9 @@ struct WideOrder {
 };
 
 // Device view of a plan, passed by value to the sparse kernels.
-constexpr int kXcds = 8; // each with its own L2
-
-// The owners (rows, or columns) of a plan with more than kLongPairs pairs, in no
-// particular order, and the first `blocks` workgroups of a launch over all
-// owners that take them, a wave each. blocks 0: no list, every owner stays in
-// its own place.
-constexpr int kLongPairs = kSinkMaxGroup * kSinkPiece; // none where the per-sample Sinkhorn kernels run
-struct LongOwners {
-    int32_t *count = nullptr;
-    int32_t *list = nullptr;
-    int blocks = 0;
-};
-
 struct DevPlan {
     int B, N, M, L;
     int64_t nnz;
-    LongOwners long_row, long_col;
     const float *x, *y;
     int32_t *row_ptr, *col_ptr;   // [B*N+1], [B*M+1] global offsets
     int32_t *csr_col, *csr_row;   // [nnz] row-major: column j in sample, global row b*N+i
@@ -371,8 +357,6 @@ hipError_t launch_csc_and_softmax(const DevPlan &d, const Params &p, int64_t max
 hipError_t set_dynamic_lds(const void *k, size_t bytes);
 
 void launch_softmax(const DevPlan &d, const Params &p, hipStream_t s);
-// Fills the plan's lists of long owners (those with blocks).
-void launch_long_owners(const DevPlan &d, hipStream_t s);
 // Backward of both softmaxes and the distance gradient. double_p: P formed
 // again in double precision from the stored costs (for plans whose reverse
 // sweeps keep the adjoint in double, or that have none), else read as stored.

@@ -195,36 +195,7 @@ __global__ __launch_bounds__(kOffT) void k_sample_base(const int32_t *cnt, int S
     }
 }
 
-// Owners with more than kLongPairs pairs, both sides in one launch.
-__global__ __launch_bounds__(kBlock) void k_long_owners(DevPlan d)
-{
-    const int t = blockIdx.x * kBlock + threadIdx.x, BN = d.B * d.N, BM = d.B * d.M;
-    if (t >= BN + BM)
-        return;
-    const bool rows = t < BN;
-    const LongOwners &w = rows ? d.long_row : d.long_col;
-    const int o = rows ? t : t - BN;
-    const int32_t *ptr = rows ? d.row_ptr : d.col_ptr;
-    if (w.blocks > 0 && ptr[o + 1] - ptr[o] > kLongPairs)
-        w.list[atomicAdd(w.count, 1)] = o;
-}
-
-__global__ void k_clear_long(DevPlan d)
-{
-    if (d.long_row.blocks > 0)
-        *d.long_row.count = 0;
-    if (d.long_col.blocks > 0)
-        *d.long_col.count = 0;
-}
-
 } // namespace
-
-void launch_long_owners(const DevPlan &d, hipStream_t s)
-{
-    const int64_t owners = (int64_t)d.B * d.N + (int64_t)d.B * d.M;
-    hipLaunchKernelGGL(k_clear_long, dim3(1), dim3(1), 0, s, d);
-    hipLaunchKernelGGL(k_long_owners, dim3(blocks_for(owners, kBlock)), dim3(kBlock), 0, s, d);
-}
 
 size_t offsets_scratch_ints(int B, int N, int M)
 {

@@ -6,8 +6,6 @@
 #include <climits>
 #include <cstdint>
 
-#include "apml_internal.h"
-
 namespace apml {
 
 constexpr float kInf = __builtin_huge_valf();
@@ -167,45 +165,28 @@ template <bool LDS_ONLY> __device__ __forceinline__ void wg_barrier()
 }
 
 // Calls f(lanes, owner, lane of the group) for the owner of each group of G
-// lanes (a power of two from 4 to 64) of workgroup bid, then, for the
-// owners whose segment exceeds CAP pairs a lane (what a lane loads at once),
-// with the whole wave, one such owner after another. A group strides through
-// a long segment with two dependent loads a step while the other groups of its
-// wave wait: one point far from the rest keeps hundreds of candidates (its gap
-// sets its radius), and its row alone took most of a launch. Owners of w's list
-// are left out there and taken by the first w.blocks workgroups, a wave each:
-// points repeated at a cloud's end (padded scans) keep every pair under the
-// uniform fallback, all in a few waves, four to sixteen one after another
-// (6 x 1900 x 1500 points, 40 of each cloud repeated, forward + backward: 1556 ->
-// 1358 us). The lane count is a run-time value so that all uses share one copy of f (two
-// copies held 166 instead of 126 registers).
-template <int CAP, class F>
-__device__ __forceinline__ void each_owner(int G, int bid, const LongOwners &w, int n_own, const int32_t *ptr, F f)
+// lanes (a power of two from 4 to 64), then, for the owners whose segment exceeds CAP pairs a lane (what a
+// lane loads at once), with the whole wave, one such owner after another.
+// A group strides through a long segment with two dependent loads a step
+// while the other groups of its wave wait: one point far from the rest keeps
+// hundreds of candidates (its gap sets its radius), and its row alone took
+// most of a launch. The lane count is a run-time value so that both uses
+// share one copy of f (two copies held 166 instead of 126 registers).
+template <int CAP, class F> __device__ __forceinline__ void each_owner(int G, int o, int n_own, const int32_t *ptr, F f)
 {
-    const bool listed = bid < w.blocks; // the whole workgroup
-    const int gid = listed ? 0 : (bid - w.blocks) * (int)blockDim.x + (int)threadIdx.x;
-    const int o = listed ? n_own : gid / G;
     const int n = o < n_own ? ptr[o + 1] - ptr[o] : 0;
-    const bool far = w.blocks > 0 && n > kLongPairs, spread = n > G * CAP && !far;
+    const bool spread = n > G * CAP;
     uint64_t left = __ballot(spread && (threadIdx.x & (G - 1)) == 0);
-    bool mine = o < n_own && !spread && !far;
+    bool mine = o < n_own && !spread;
     int lanes = G, lane = (int)(threadIdx.x & (G - 1)), owner = o;
-    const int waves = blockDim.x / 64;
-    int next = listed ? bid * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
-    const int end = listed ? *w.count : 0;
     for (;;) {
         asm volatile("" : "+s"(lanes)); // one copy of f: the first pass is not peeled off
         if (mine)
             f(lanes, owner, lane);
-        if (left != 0) {
-            owner = __builtin_amdgcn_readlane(o, __builtin_ctzll(left));
-            left &= left - 1;
-        } else if (next < end) {
-            owner = __builtin_amdgcn_readfirstlane(w.list[next]);
-            next += w.blocks * waves;
-        } else {
+        if (left == 0)
             break;
-        }
+        owner = __builtin_amdgcn_readlane(o, __builtin_ctzll(left));
+        left &= left - 1;
         lanes = 64;
         lane = lane_id();
         mine = true;
@@ -257,17 +238,11 @@ struct Argmins {
 // and each XCD has its own L2. This maps the hardware index to a logical one
 // under which every XCD receives one contiguous range of the grid, so that
 // workgroups sharing data (one sample) share an L2.
+constexpr int kXcds = 8;
 __device__ __forceinline__ int xcd_contiguous(int bid, int grid)
 {
     const int q = grid / kXcds, r = grid % kXcds, x = bid % kXcds;
     return x * q + min(x, r) + bid / kXcds;
-}
-
-// The same for a launch whose first w.blocks workgroups (a multiple of kXcds)
-// take the long owners.
-__device__ __forceinline__ int xcd_contiguous(int bid, int grid, const LongOwners &w)
-{
-    return bid < w.blocks ? bid : w.blocks + xcd_contiguous(bid - w.blocks, grid - w.blocks);
 }
 
 inline unsigned blocks_for(int64_t n, int per_block) { return (unsigned)((n + per_block - 1) / per_block); }

@@ -1464,8 +1464,8 @@ template <bool COL, int G> __global__ __launch_bounds__(kBlock) void k_sink_step
 {
     // each XCD takes a contiguous range of owners: its L2 holds only the
     // other side's scalings of those owners' samples
-    const LongOwners &w = COL ? d.long_col : d.long_row;
-    each_owner<kSB>(G, xcd_contiguous(blockIdx.x, gridDim.x, w), w, d.B * (COL ? d.M : d.N), COL ? d.col_ptr : d.row_ptr,
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    each_owner<kSB>(G, gid / G, d.B * (COL ? d.M : d.N), COL ? d.col_ptr : d.row_ptr,
                        [&](int lanes, int o, int lg) { sink_owner<COL>(d, l, eps, o, lanes, lg); });
 }
 
@@ -1495,8 +1495,8 @@ __device__ __forceinline__ void loss_row(const DevPlan &d, double *loss_rows, in
 
 template <int G> __global__ __launch_bounds__(kBlock) void k_loss_rows(DevPlan d, double *loss_rows)
 {
-    const int bid = xcd_contiguous(blockIdx.x, gridDim.x, d.long_row); // as in k_sink_step
-    each_owner<kSB>(G, bid, d.long_row, d.B * d.N, d.row_ptr,
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
+    each_owner<kSB>(G, gid / G, d.B * d.N, d.row_ptr,
                        [&](int lanes, int r, int lg) { loss_row(d, loss_rows, r, lanes, lg); });
 }
 
@@ -1589,11 +1589,12 @@ __global__ __launch_bounds__(kBlock) void k_bwd_direct(DevPlan d, int row_blocks
 {
     const int bid = blockIdx.x;
     if (bid < row_blocks) {
-        each_owner<kSB>(1 << lr, xcd_contiguous(bid, row_blocks, d.long_row), d.long_row, d.B * d.N, d.row_ptr,
+        const int gid = xcd_contiguous(bid, row_blocks) * kBlock + threadIdx.x;
+        each_owner<kSB>(1 << lr, gid >> lr, d.B * d.N, d.row_ptr,
                         [&](int lanes, int o, int lg) { direct_owner<false>(d, o, lanes, lg); });
     } else {
-        each_owner<kSB>(1 << lc, xcd_contiguous(bid - row_blocks, gridDim.x - row_blocks, d.long_col), d.long_col,
-                        d.B * d.M, d.col_ptr,
+        const int gid = xcd_contiguous(bid - row_blocks, gridDim.x - row_blocks) * kBlock + threadIdx.x;
+        each_owner<kSB>(1 << lc, gid >> lc, d.B * d.M, d.col_ptr,
                         [&](int lanes, int o, int lg) { direct_owner<true>(d, o, lanes, lg); });
     }
 }
@@ -1626,8 +1627,8 @@ __device__ __forceinline__ void bwd_col(const DevPlan &d, int l, double keep, in
 
 template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_cols(DevPlan d, int l, double keep)
 {
-    const int bid = xcd_contiguous(blockIdx.x, gridDim.x, d.long_col); // as in k_sink_step
-    each_owner<kSB>(G, bid, d.long_col, d.B * d.M, d.col_ptr,
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
+    each_owner<kSB>(G, gid / G, d.B * d.M, d.col_ptr,
                     [&](int lanes, int gc, int lg) { bwd_col(d, l, keep, gc, lanes, lg); });
 }
 
@@ -1667,8 +1668,8 @@ __device__ __forceinline__ void bwd_row(const DevPlan &d, int l, double eps, int
 
 template <bool FIRST, int G> __global__ __launch_bounds__(kBlock) void k_bwd_rows(DevPlan d, int l, double eps)
 {
-    const int bid = xcd_contiguous(blockIdx.x, gridDim.x, d.long_row); // as in k_sink_step
-    each_owner<kSB>(G, bid, d.long_row, d.B * d.N, d.row_ptr,
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // as in k_sink_step
+    each_owner<kSB>(G, gid / G, d.B * d.N, d.row_ptr,
                        [&](int lanes, int r, int lg) { bwd_row<FIRST>(d, l, eps, r, lanes, lg); });
 }
 
@@ -1909,13 +1910,12 @@ int steps_lanes(int64_t nnz, int64_t owners)
 int log2_lanes(int g) { return g == 16 ? 4 : g == 8 ? 3 : 2; }
 
 template <template <int> class K, class... A>
-void launch_lanes(int g, const LongOwners &w, int64_t owners, hipStream_t s, A... args)
+void launch_lanes(int g, int64_t owners, hipStream_t s, A... args)
 {
-    const dim3 grid(w.blocks + blocks_for(owners * g, kBlock)); // g is 4, 8 or 16 (steps_lanes)
     switch (g) {
-    case 8: hipLaunchKernelGGL(K<8>::fn, grid, dim3(kBlock), 0, s, args...); break;
-    case 16: hipLaunchKernelGGL(K<16>::fn, grid, dim3(kBlock), 0, s, args...); break;
-    default: hipLaunchKernelGGL(K<4>::fn, grid, dim3(kBlock), 0, s, args...); break;
+    case 8: hipLaunchKernelGGL(K<8>::fn, dim3(blocks_for(owners * 8, kBlock)), dim3(kBlock), 0, s, args...); break;
+    case 16: hipLaunchKernelGGL(K<16>::fn, dim3(blocks_for(owners * 16, kBlock)), dim3(kBlock), 0, s, args...); break;
+    default: hipLaunchKernelGGL(K<4>::fn, dim3(blocks_for(owners * 4, kBlock)), dim3(kBlock), 0, s, args...); break;
     }
 }
 template <int G> struct ColStep { static constexpr auto fn = k_sink_step<true, G>; };
@@ -1931,8 +1931,7 @@ void launch_bwd_direct(const DevPlan &d, hipStream_t s)
 {
     const int64_t BN = (int64_t)d.B * d.N, BM = (int64_t)d.B * d.M;
     const int gr = steps_lanes(d.nnz, BN), gc = steps_lanes(d.nnz, BM);
-    const unsigned rows = d.long_row.blocks + blocks_for(BN * gr, kBlock),
-                   cols = d.long_col.blocks + blocks_for(BM * gc, kBlock);
+    const unsigned rows = blocks_for(BN * gr, kBlock), cols = blocks_for(BM * gc, kBlock);
     hipLaunchKernelGGL(k_bwd_direct, dim3(rows + cols), dim3(kBlock), 0, s, d, (int)rows, log2_lanes(gr), log2_lanes(gc));
 }
 
@@ -1942,11 +1941,11 @@ void launch_sinkhorn_fwd_steps(const DevPlan &d, double eps, hipStream_t s)
     const int gr = steps_lanes(d.nnz, BN), gc = steps_lanes(d.nnz, BM);
     hipLaunchKernelGGL(k_fill_ones, dim3(blocks_for(std::max(BN, BM), kBlock)), dim3(kBlock), 0, s, d);
     for (int l = 1; l <= d.L; ++l) {
-        launch_lanes<ColStep>(gc, d.long_col, BM, s, d, l, eps);
-        launch_lanes<RowStep>(gr, d.long_row, BN, s, d, l, eps);
+        launch_lanes<ColStep>(gc, BM, s, d, l, eps);
+        launch_lanes<RowStep>(gr, BN, s, d, l, eps);
     }
     // the backward scratch is free during the forward pass: use it for the row losses
-    launch_lanes<LossRows>(gr, d.long_row, BN, s, d, d.dvec);
+    launch_lanes<LossRows>(gr, BN, s, d, d.dvec);
     hipLaunchKernelGGL(k_loss_reduce, dim3(d.B), dim3(kLossT), 0, s, d, (const double *)d.dvec);
 }
 
@@ -1955,11 +1954,11 @@ void launch_sinkhorn_bwd_steps(const DevPlan &d, double eps, hipStream_t s)
     const int BN = d.B * d.N, BM = d.B * d.M;
     const int gr = steps_lanes(d.nnz, BN), gc = steps_lanes(d.nnz, BM);
     for (int l = d.L; l >= 1; --l) {
-        launch_lanes<BwdCols>(gc, d.long_col, BM, s, d, l, l == d.L ? 1.0 : eps);
+        launch_lanes<BwdCols>(gc, BM, s, d, l, l == d.L ? 1.0 : eps);
         if (l == d.L)
-            launch_lanes<BwdRowsFirst>(gr, d.long_row, BN, s, d, l, eps);
+            launch_lanes<BwdRowsFirst>(gr, BN, s, d, l, eps);
         else
-            launch_lanes<BwdRows>(gr, d.long_row, BN, s, d, l, eps);
+            launch_lanes<BwdRows>(gr, BN, s, d, l, eps);
     }
 }
 

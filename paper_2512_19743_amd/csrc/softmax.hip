@@ -268,16 +268,16 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
 
 template <int G> __global__ __launch_bounds__(kBlock, 4) void k_row_softmax(DevPlan d, Params p)
 {
-    const int bid = xcd_contiguous(blockIdx.x, gridDim.x, d.long_row); // a sample's owners share an L2
-    each_owner<kSmCache>(G, bid, d.long_row, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
+    each_owner<kSmCache>(G, gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
         owner_softmax<true>(d, p, r, lanes, lg);
     });
 }
 
 template <int G> __global__ __launch_bounds__(kBlock, 4) void k_col_softmax(DevPlan d, Params p)
 {
-    const int bid = xcd_contiguous(blockIdx.x, gridDim.x, d.long_col); // a sample's owners share an L2
-    each_owner<kSmCache>(G, bid, d.long_col, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
+    each_owner<kSmCache>(G, gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
         owner_softmax<false>(d, p, gc, lanes, lg);
     });
 }
@@ -347,8 +347,10 @@ template <int G> __global__ __launch_bounds__(kCscT) void k_csc_rows(DevPlan d, 
         csc_sample(d, b, (int)((int64_t)d.M * part / parts), (int)((int64_t)d.M * (part + 1) / parts), lds_csc);
         return;
     }
-    each_owner<kSmCache>(G, blockIdx.x - d.B * parts, LongOwners{}, d.B * d.N, d.row_ptr,
-                         [&](int lanes, int r, int lg) { owner_softmax<true>(d, p, r, lanes, lg); });
+    const int gid = (blockIdx.x - d.B * parts) * kCscT + threadIdx.x;
+    each_owner<kSmCache>(G, gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+        owner_softmax<true>(d, p, r, lanes, lg);
+    });
 }
 
 __host__ inline size_t csc_sample_lds(int M, int64_t max_pairs)
@@ -505,8 +507,8 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
 
 template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_softmax(DevPlan d, Params p)
 {
-    const int bid = xcd_contiguous(blockIdx.x, gridDim.x, d.long_col); // a sample's owners share an L2
-    each_owner<kSmCache>(G, bid, d.long_col, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
+    each_owner<kSmCache>(G, gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
         bwd_col_owner<DP>(d, p, gc, lanes, lg);
     });
 }
@@ -650,8 +652,8 @@ __device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p,
 template <int G, bool DP>
 __global__ __launch_bounds__(kBlock, 4) void k_bwd_row_softmax(DevPlan d, Params p, int keep_cbar)
 {
-    const int bid = xcd_contiguous(blockIdx.x, gridDim.x, d.long_row); // a sample's owners share an L2
-    each_owner<kSmCache>(G, bid, d.long_row, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
+    each_owner<kSmCache>(G, gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
         bwd_row_owner<DP>(d, p, keep_cbar, r, lanes, lg);
     });
 }
@@ -693,8 +695,8 @@ __device__ __forceinline__ void grad_y_owner(const DevPlan &d, const Params &p, 
 
 template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_grad_y(DevPlan d, Params p)
 {
-    const int bid = xcd_contiguous(blockIdx.x, gridDim.x, d.long_col); // a sample's owners share an L2
-    each_owner<kSmCache>(G, bid, d.long_col, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
+    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
+    each_owner<kSmCache>(G, gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
         grad_y_owner(d, p, gc, lanes, lg);
     });
 }
@@ -706,12 +708,11 @@ bool csc_sample_fits(int N, int M, int64_t max_pairs)
     return N <= 65536 && max_pairs <= 65536 && csc_sample_lds(M, max_pairs) <= 160 * 1024;
 }
 
-// Launches kernel template K with the lanes per owner of `owners`, and the
-// workgroups of their list of long ones.
-#define APML_LAUNCH_G(K, far, owners, pairs, per_block, shmem, s, ...)                                              \
+// Launches kernel template K with the lanes per owner of `owners`.
+#define APML_LAUNCH_G(K, owners, pairs, per_block, shmem, s, ...)                                                   \
     do {                                                                                                           \
         const int g_ = softmax_lanes(owners, pairs);                                                               \
-        const dim3 grid_((far).blocks + blocks_for((int64_t)(owners) * g_, per_block));                            \
+        const dim3 grid_(blocks_for((int64_t)(owners) * g_, per_block));                                           \
         if (g_ == 16)                                                                                              \
             hipLaunchKernelGGL(K<16>, grid_, dim3(per_block), shmem, s, __VA_ARGS__);                              \
         else if (g_ == 8)                                                                                          \
@@ -721,10 +722,10 @@ bool csc_sample_fits(int N, int M, int64_t max_pairs)
     } while (0)
 
 // The same for a kernel template with a second, boolean parameter X.
-#define APML_LAUNCH_GP(K, X, far, owners, pairs, s, ...)                                                            \
+#define APML_LAUNCH_GP(K, X, owners, pairs, s, ...)                                                                 \
     do {                                                                                                           \
         const int g_ = softmax_lanes(owners, pairs);                                                               \
-        const dim3 grid_((far).blocks + blocks_for((int64_t)(owners) * g_, kBlock));                               \
+        const dim3 grid_(blocks_for((int64_t)(owners) * g_, kBlock));                                              \
         if (g_ == 16)                                                                                              \
             hipLaunchKernelGGL((K<16, X>), grid_, dim3(kBlock), 0, s, __VA_ARGS__);                                \
         else if (g_ == 8)                                                                                          \
@@ -757,28 +758,28 @@ hipError_t launch_csc_and_softmax(const DevPlan &d, const Params &p, int64_t max
         hipLaunchKernelGGL(k_csc_rows<8>, grid, dim3(kCscT), bytes, s, d, p, parts);
     else
         hipLaunchKernelGGL(k_csc_rows<kGroup>, grid, dim3(kCscT), bytes, s, d, p, parts);
-    APML_LAUNCH_G(k_col_softmax, d.long_col, (int64_t)d.B * d.M, d.nnz, kBlock, 0, s, d, p);
+    APML_LAUNCH_G(k_col_softmax, (int64_t)d.B * d.M, d.nnz, kBlock, 0, s, d, p);
     return hipGetLastError();
 }
 
 void launch_softmax(const DevPlan &d, const Params &p, hipStream_t s)
 {
-    APML_LAUNCH_G(k_row_softmax, d.long_row, (int64_t)d.B * d.N, d.nnz, kBlock, 0, s, d, p);
-    APML_LAUNCH_G(k_col_softmax, d.long_col, (int64_t)d.B * d.M, d.nnz, kBlock, 0, s, d, p);
+    APML_LAUNCH_G(k_row_softmax, (int64_t)d.B * d.N, d.nnz, kBlock, 0, s, d, p);
+    APML_LAUNCH_G(k_col_softmax, (int64_t)d.B * d.M, d.nnz, kBlock, 0, s, d, p);
 }
 
 void launch_bwd_softmax(const DevPlan &d, const Params &p, bool double_p, hipStream_t s)
 {
     const int keep = d.grad_y != nullptr ? 1 : 0;
     if (double_p) {
-        APML_LAUNCH_GP(k_bwd_col_softmax, true, d.long_col, (int64_t)d.B * d.M, d.nnz, s, d, p);
-        APML_LAUNCH_GP(k_bwd_row_softmax, true, d.long_row, (int64_t)d.B * d.N, d.nnz, s, d, p, keep);
+        APML_LAUNCH_GP(k_bwd_col_softmax, true, (int64_t)d.B * d.M, d.nnz, s, d, p);
+        APML_LAUNCH_GP(k_bwd_row_softmax, true, (int64_t)d.B * d.N, d.nnz, s, d, p, keep);
     } else {
-        APML_LAUNCH_GP(k_bwd_col_softmax, false, d.long_col, (int64_t)d.B * d.M, d.nnz, s, d, p);
-        APML_LAUNCH_GP(k_bwd_row_softmax, false, d.long_row, (int64_t)d.B * d.N, d.nnz, s, d, p, keep);
+        APML_LAUNCH_GP(k_bwd_col_softmax, false, (int64_t)d.B * d.M, d.nnz, s, d, p);
+        APML_LAUNCH_GP(k_bwd_row_softmax, false, (int64_t)d.B * d.N, d.nnz, s, d, p, keep);
     }
     if (d.grad_y)
-        APML_LAUNCH_G(k_bwd_grad_y, d.long_col, (int64_t)d.B * d.M, d.nnz, kBlock, 0, s, d, p);
+        APML_LAUNCH_G(k_bwd_grad_y, (int64_t)d.B * d.M, d.nnz, kBlock, 0, s, d, p);
 }
 
 #undef APML_LAUNCH_G

@@ -50,30 +50,3 @@ def test_long_owners(m, swap):
 def test_many_long_owners(far):
     X, Y = clouds(300, 700, far, far)
     _check_batch(X, Y, f"{far} long rows", n_iter=3)
-
-
-# owners beyond 256 pairs are listed and taken by workgroups of their own where
-# a side holds 32 pairs an owner (fewer here with 15 long rows): at that edge, several samples with and without such owners, more listed owners
-# than the list's waves (1024), and neighbours that all are (points repeated at
-# the clouds' ends under the uniform fallback)
-@pytest.mark.parametrize("m", [255, 256, 257, 258])
-@pytest.mark.parametrize("far", [15, 80])
-def test_listed_owners_edge(m, far):
-    a, b = clouds(290, m, far, m), clouds(290, m, 0, m + 1)
-    X, Y = (np.concatenate([a[k], b[k], a[k]]) for k in (0, 1))
-    _check_batch(X, Y, f"listed rows of {m}", n_iter=4)
-
-
-@pytest.mark.parametrize("swap", [False, True])
-def test_more_listed_owners_than_waves(swap):
-    X, Y = clouds(1500, 400, 1300, 9)
-    if swap:
-        X, Y = Y, X
-    _check_batch(X, Y, "1300 listed owners", n_iter=3)
-
-
-@pytest.mark.parametrize("sym_mode", [0, 1])
-def test_listed_neighbours(sym_mode):
-    X, Y = (np.concatenate(c) for c in zip(*(clouds(420, 430, 0, s) for s in (1, 2))))
-    X[:, -80:], Y[:, -80:] = X[:, :80], Y[:, :80]
-    _check_batch(X, Y, f"listed neighbours sym_mode={sym_mode}", n_iter=3, gap_mode=1, sym_mode=sym_mode)
