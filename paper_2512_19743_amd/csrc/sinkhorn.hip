@@ -454,7 +454,7 @@ template <int SLP> __global__ __launch_bounds__(kT) void k_sinkhorn_bwd(DevPlan 
                 if (u.bits(c.info, 14, 2) == 3u) { // head and valid
                     const int j = u.owner(c.info);
                     const double bl = own_b[j];
-                    cs[j] = make_double2(bl, keep * cs[j].y - bl * bl * acc);
+                    cs[j] = make_double2(bl, keep * cs[j].y - bl * (bl * acc));
                 }
             }
         keep = eps;
@@ -481,7 +481,7 @@ template <int SLP> __global__ __launch_bounds__(kT) void k_sinkhorn_bwd(DevPlan 
                 }
                 acc = group_reduce(acc, pr.info[s], u);
                 if (u.bits(pr.info[s], 14, 2) == 3u)
-                    rb[i] = eps * r - al * al * acc;
+                    rb[i] = eps * r - al * (al * acc);
             }
         lds_barrier();
     }
@@ -1020,7 +1020,7 @@ __device__ __forceinline__ void rev_col_slot(const WSlot &w, const double *rb, d
         acc = __builtin_fma(widen(w.p0[e]), g[e], acc);
     acc = group_reduce_lg(acc, (int)u.bits(w.info, 13, 3));
     if (u.bits(w.info, 16, 2) == 3u) // head and valid
-        publish64(out + u.bits(w.info, 0, 13), __builtin_bit_cast(uint64_t, old - bl * bl * acc), local);
+        publish64(out + u.bits(w.info, 0, 13), __builtin_bit_cast(uint64_t, old - bl * (bl * acc)), local);
 }
 
 // Row phase of one slot: the pairs' terms, the row's new Rbar = eps r - al^2
@@ -1041,7 +1041,7 @@ __device__ __forceinline__ double rev_row_slot(const WSlot &w, const double2 *cs
         __builtin_amdgcn_sched_barrier(0);
     }
     acc = group_reduce_lg(acc, (int)u.bits(w.info, 13, 3));
-    const double next = eps * r - al * al * acc;
+    const double next = eps * r - al * (al * acc);
     if (u.bits(w.info, 16, 2) == 3u)
         publish64(out + u.bits(w.info, 0, 13), __builtin_bit_cast(uint64_t, next), local);
     return next;
@@ -1536,6 +1536,9 @@ __global__ __launch_bounds__(kLossT) void k_loss_reduce(DevPlan d, const double 
 // follow one another without any per-pair state:
 //   Sbar^l_j     = eps Sbar^(l+1)_j - (beta^l_j)^2 sum_i P0_ij Rbar^l_i
 //   Rbar^(l-1)_i = eps Rbar^l_i - (alpha^(l-1)_i)^2 sum_j P0_ij Sbar^l_j
+// (a factor of a square at a time: with N != M alpha and beta drift by N / M an
+// iteration, and where they pass 1e154 the square itself leaves the range of a
+// double while the terms stay near the other side's scale)
 // from the direct terms of the loss (sum alpha^L P0 beta^L C; k_bwd_direct), and
 //   dLoss/dP0_ij = g alpha^L_i beta^L_j C_ij
 //                  + sum_l (Rbar^l_i beta^l_j + alpha^(l-1)_i Sbar^l_j),
@@ -1576,7 +1579,7 @@ template <bool COL> __device__ __forceinline__ void direct_owner(const DevPlan &
                                  },
                                  [&](const V &v) { return (double)v.p * (v.x * v.c); });
     if (lg == 0) {
-        const double first = -(own * own) * (gl * acc);
+        const double first = -own * (own * (gl * acc));
         if (COL)
             d.cs[o] = make_double2(own, first);
         else
@@ -1622,7 +1625,7 @@ __device__ __forceinline__ void bwd_col(const DevPlan &d, int l, double keep, in
                                  },
                                  [&](const V &v) { return (double)v.p * v.x; });
     if (lg == 0)
-        d.cs[gc] = make_double2(bl, old - bl * bl * acc);
+        d.cs[gc] = make_double2(bl, old - bl * (bl * acc));
 }
 
 template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_cols(DevPlan d, int l, double keep)
@@ -1663,7 +1666,7 @@ __device__ __forceinline__ void bwd_row(const DevPlan &d, int l, double eps, int
                                              return v.c.y * (double)v.p;
                                          });
     if (lg == 0)
-        d.rbar[r] = eps * rb - al * al * acc;
+        d.rbar[r] = eps * rb - al * (al * acc);
 }
 
 template <bool FIRST, int G> __global__ __launch_bounds__(kBlock) void k_bwd_rows(DevPlan d, int l, double eps)
