@@ -288,6 +288,19 @@ __device__ __forceinline__ uint32_t shift_in_hit(uint32_t bits, float ax, float 
         : "vcc");
     return bits;
 }
+// The same of a column in vector registers.
+__device__ __forceinline__ uint32_t shift_in_hit(uint32_t bits, float ax, float ay, float az, float E, float4 yv)
+{
+    const float s = sqdist_f32(ax, ay, az, yv.x, yv.y, yv.z);
+    float m;
+    asm("v_max_f32 %1, %3, %4\n\t"
+        "v_cmp_le_f32 vcc, %2, %1\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, vcc"
+        : "+v"(bits), "=&v"(m)
+        : "v"(s), "v"(yv.w), "v"(E)
+        : "vcc");
+    return bits;
+}
 
 // Calls f(j) for every column j in [j0, j1) whose pair with this lane's row
 // passes the radius test, in increasing j. Blocks of 32 columns: one bit per
@@ -329,7 +342,7 @@ __device__ __forceinline__ void for_each_hit(float ax, float ay, float az, float
 // ---------------------------------------------------------------------------
 //
 // d^2 = |r|^2 + |c|^2 - 2 r c of a row r and a column c, both relative to one
-// point of the sample, as one product of 32 bfloat16 factors a side: every
+// origin of the sample, as one product of 32 bfloat16 factors a side: every
 // coordinate is the exact sum of three bfloat16 (8 bits each), of whose nine
 // cross products the six largest are kept, and the squared norms, likewise in
 // three parts, meet factors of 1. With a row's threshold taken off its norm
@@ -345,14 +358,31 @@ __device__ __forceinline__ void for_each_hit(float ax, float ay, float az, float
 // The product is off by at most kSlack (|r|^2 + |c|^2) + kTiny: 26 additions
 // rounded at 2^-23 of at most 2.02 (|r|^2 + |c|^2) make 6.3e-6, the dropped
 // products, the norms' rounding and the shift of the origin less than 1e-6
-// more, factors below the normal range 1e-36. Both are taken off the norms, so
+// more, factors below the normal range 1e-36. (Against double, over 25 million
+// pairs of points that are random, near each other, opposite or equal: at most
+// 7.6e-7, so the instruction's own additions lose less than assumed.) Both are taken off the norms, so
 // no pair of the exact test is missed, and every hit is tested again with
 // the exact sequence: the scan finds the same pairs as the other one. Points
 // beyond 1e15 from the origin's, or not finite, take that one instead.
+//
+// What the slack costs grows with the square of the distance from the origin:
+// where it passes a row's threshold, the row visits its far neighbours too. So
+// the origin is, per coordinate, the median of three columns, which a stray point
+// doesn't move, and where many rows of a wave lie far out for their thresholds
+// all the same (clusters far apart, which no origin serves) the workgroup takes
+// the exact test alone. 32 x 2048 points, support phase: one column 300 cloud
+// radii away 39 us with nine operations a pair, 67 with that column as the
+// origin, 29 now; two clusters 1000 apart 39, 59 and 40.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr float kSlack = 1e-5f, kTiny = 1e-36f, kFar = 1e30f, kOpen = 1e32f;
 constexpr int kScanCols = 128; // columns staged in LDS at a time
+// A row is far out when twice its slack passes kFarOut times its threshold: it
+// then visits about kFarOut (on a surface) to kFarOut^1.5 times its neighbours.
+// More than kFarRows of a wave's 64 rows decide: with 5% of a cloud 1000 away the
+// products took 32 us, with 10% 59, the exact test alone 42.
+constexpr float kFarOut = 8.0f;
+constexpr int kFarRows = 6;
 
 // The three bfloat16 parts of v, each in the upper half of a word.
 struct Parts {
@@ -426,19 +456,22 @@ __device__ __forceinline__ uint32_t spread_nibbles(uint32_t m)
 
 // Calls f(j) for every column j in [j0, j1) whose pair with this lane's row
 // passes the radius test, in increasing j, as for_each_hit; all waves of the
-// workgroup together (64 rows each, rows r0 + lane of the sample). False, with
-// nothing called, when a point is out of the products' range.
+// workgroup together (64 rows each, rows r0 + lane of the sample).
 template <class F>
-__device__ __forceinline__ bool for_each_hit_mfma(const EmitArgs &a, ScanLds &sh, int b, int r0, float ax, float ay,
+__device__ __forceinline__ void for_each_hit_mfma(const EmitArgs &a, ScanLds &sh, int b, int r0, float ax, float ay,
                                                   float az, float E, int j0, int j1, uint32_t keep, F f)
 {
     const int lane = lane_id(), half = lane >> 5;
     const float4 *yp = a.ypack + (size_t)b * a.M;
-    const float4 o = yp[0]; // the origin
+    const const_ptr<f32x4> q = as_const(reinterpret_cast<const f32x4 *>(yp));
+    const f32x4 p0 = q[0], p1 = q[a.M / 2], p2 = q[a.M - 1];
+    const float3 o = make_float3(__builtin_amdgcn_fmed3f(p0.x, p1.x, p2.x), __builtin_amdgcn_fmed3f(p0.y, p1.y, p2.y),
+                                 __builtin_amdgcn_fmed3f(p0.z, p1.z, p2.z)); // the origin
     // the rows' operands: rows lane % 32 and 32 + lane % 32 of the wave, the
     // groups of this lane's half
     uint4 rg[2][3];
     bool bad = false;
+    float mine = 0.0f; // |r|^2 of this lane's own row
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         const int i = min(r0 + 32 * t + (lane & 31), a.N - 1);
@@ -446,11 +479,13 @@ __device__ __forceinline__ bool for_each_hit_mfma(const EmitArgs &a, ScanLds &sh
         const float x = p[0] - o.x, y = p[1] - o.y, z = p[2] - o.z;
         const float n = x * x + y * y + z * z, base = n * (1.0f - kSlack) - kTiny;
         bad |= !(n < kFar);
+        mine = t == half ? n : mine;
         const Factors w = factors<true>(x, y, z, base, base - fminf(a.E_row[(size_t)b * a.N + i], kOpen));
         rg[t][0] = half ? w.g[1] : w.g[0];
         rg[t][1] = half ? w.norm[1] : w.g[2]; // the row's threshold
         rg[t][2] = half ? w.norm[0] : w.g[2]; // the column's
     }
+    bad |= __popcll(__ballot(keep != 0 && 2.0f * kSlack * mine > kFarOut * E)) > kFarRows;
     for (int s0 = j0; s0 < j1; s0 += kScanCols) {
         const int n = min(kScanCols, j1 - s0);
         if (s0 > j0)
@@ -468,15 +503,24 @@ __device__ __forceinline__ bool for_each_hit_mfma(const EmitArgs &a, ScanLds &sh
             sh.g[4][k] = w.norm[1];
             sh.col[k] = c;
         }
-        if (__syncthreads_or(bad)) {
-            if (s0 == j0)
-                return false;
-            // later columns out of range: theirs are taken one by one (no
-            // barrier follows in this scan)
-            for_each_hit(ax, ay, az, E, as_const(reinterpret_cast<const f32x4 *>(yp)), s0, j1, keep, f);
-            return true;
+        const bool plain = __syncthreads_or(bad); // from here on by the exact test alone
+        for (int jb = 0; plain && jb < n; jb += 32) {
+            uint32_t bits = 0;
+#pragma unroll 8
+            for (int u = 0; u < 32; ++u) {
+                const float4 c = sh.col[jb + u];
+                bits = shift_in_hit(bits, ax, ay, az, E, c);
+            }
+            bits &= keep;
+            if (jb + 32 > n)
+                bits &= ~0u << (32 - (n - jb));
+            while (bits) {
+                const int u = __clz(bits);
+                bits &= ~(0x80000000u >> u);
+                f(s0 + jb + u);
+            }
         }
-        for (int jb = 0; jb < n; jb += 32) {
+        for (int jb = 0; !plain && jb < n; jb += 32) {
             const int k = jb + (lane & 31);
             const uint4 c0 = sh.g[half][k], c1 = sh.g[half ? 3 : 2][k], c2 = sh.g[half ? 4 : 2][k];
             uint32_t m[2];
@@ -509,7 +553,6 @@ __device__ __forceinline__ bool for_each_hit_mfma(const EmitArgs &a, ScanLds &sh
             }
         }
     }
-    return true;
 }
 
 // Staged hit k of (row, chunk) slot: the column's offset within the chunk,
@@ -573,8 +616,7 @@ template <bool WRITE> __global__ __launch_bounds__(kBlock, 4) void k_emit(EmitAr
             }
             ++cnt;
         };
-        if (!for_each_hit_mfma(a, scan, b, ob * kBlock + (int)(threadIdx.x & ~63u), ax, ay, az, E, j0, j1, keep, hit))
-            for_each_hit(ax, ay, az, E, q, j0, j1, keep, hit);
+        for_each_hit_mfma(a, scan, b, ob * kBlock + (int)(threadIdx.x & ~63u), ax, ay, az, E, j0, j1, keep, hit);
         if (valid)
             a.cnt[slot] = cnt;
         const int extra = max(cnt - a.kst, 0);

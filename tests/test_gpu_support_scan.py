@@ -81,3 +81,58 @@ def test_duplicates_and_open_thresholds():
     _same(X, Y, "clamp")
     _same(X, Y, "fallback", gap_mode=1)  # infinite radii
     _same(X, Y, "tau 0", tau=0.0)
+
+
+# The origin of the products is the median of three columns, so that a stray
+# point among them doesn't move it; where two of them are, or clusters lie far
+# apart, the error taken off the thresholds passes them and the workgroups test
+# every column exactly. The same pairs on either way.
+@pytest.mark.parametrize("at", [30.0, 100.0, 300.0, 1000.0])
+@pytest.mark.parametrize("cloud", ["X", "Y", "both", "two of three"])
+def test_stray_points(at, cloud):
+    X, Y = custom(101, 2, 700, 900, sigma=0.05)
+    if cloud in ("X", "both"):
+        X[:, 0] = [at, 0.0, 0.0]
+    if cloud in ("Y", "both"):
+        Y[:, 0] = [at, 0.1, 0.0]
+    if cloud == "two of three":  # of the columns the origin is taken from
+        for k in (0, 450):
+            Y[:, k] = [at, 0.01 * k, 0.0]
+    _same(X, Y, f"stray {cloud} at {at}")
+
+
+@pytest.mark.parametrize("k", [2, 8])
+@pytest.mark.parametrize("N,M", [(600, 1000), (257, 131)])
+def test_clusters_far_apart(k, N, M):
+    rng = np.random.default_rng(102 + k)
+    X, Y = custom(102, 2, N, M, sigma=0.05)
+    centres = rng.uniform(-1000.0, 1000.0, (k, 3)).astype(np.float32)
+    _same(X + centres[rng.integers(0, k, N)], Y + centres[rng.integers(0, k, M)], f"{k} clusters")
+
+
+# One row whose other columns all lie within a few roundings of its threshold:
+# its nearest two at 1 and 1.05 set the radius, each other column has two rows
+# of its own close by, so that only the row's threshold counts.
+@pytest.mark.parametrize("offset", [0.0, 3.0, 40.0])
+def test_pairs_at_the_threshold(offset):
+    m, rng = 1500, np.random.default_rng(103)
+    kappa = np.log(1e8) / np.log((m - 1) * 0.8 / 0.2)
+    edge = (1.0 + 0.05 * kappa) * np.sqrt(1.0 + 1e-5 * (1.0 + kappa))
+    v = rng.standard_normal((m, 3))
+    v /= np.linalg.norm(v, axis=1, keepdims=True)
+    centre = np.array([offset, -0.3 * offset, 0.0])
+
+    def stored(shift, spread):
+        r = edge * (1.0 + shift + spread * rng.uniform(-1.0, 1.0, m))
+        r[:2] = 1.0, 1.05
+        Y = v * r[:, None]
+        X = np.concatenate([np.zeros((1, 3))] + [Y[2:] * s for s in (1.0 + 1e-3, 1.0 + 2.5e-3)])
+        X, Y = (np.ascontiguousarray((c + centre).astype(np.float32)[None]) for c in (X, Y))
+        note(f"pairs at the threshold: offset {offset} shift {shift} spread {spread}")
+        return [_pairs(X, Y, scan)[1] for scan in (1, 2)]
+
+    inside, outside = stored(-1e-3, 0.0), stored(1e-3, 0.0)
+    at = stored(0.0, 3e-6 + 1e-6 * offset)  # float32 coordinates move a point by up to 6e-8 of its offset too
+    for full, skip in (inside, outside, at):
+        assert full == skip
+    assert outside[0] < at[0] < inside[0]
