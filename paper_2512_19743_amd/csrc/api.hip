@@ -832,6 +832,11 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
     for (int b = 0; b < B; ++b)
         plan->max_sample = std::max<int64_t>(plan->max_sample, offsets[b + 1] - offsets[b]);
     dv.nnz = nnz;
+    dv.most_row = dv.most_col = 0;
+    for (int b = 0; b < B; ++b) {
+        dv.most_row = std::max(dv.most_row, kSinkPiece * pieces[4 * b + 2]);
+        dv.most_col = std::max(dv.most_col, kSinkPiece * pieces[4 * b + 3]);
+    }
     const int slots = sinkhorn_slots(N, M, pieces, B);
     plan->sink_fwd = slots > 0;
     const int wslots = plan->sink_fwd ? 0 : sinkhorn_slots_wide(N, M, pieces, B);

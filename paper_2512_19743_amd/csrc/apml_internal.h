@@ -300,6 +300,7 @@ struct WideOrder {
 struct DevPlan {
     int B, N, M, L;
     int64_t nnz;
+    int most_row, most_col;       // no row (column) has more pairs
     const float *x, *y;
     int32_t *row_ptr, *col_ptr;   // [B*N+1], [B*M+1] global offsets
     int32_t *csr_col, *csr_row;   // [nnz] row-major: column j in sample, global row b*N+i

@@ -245,6 +245,33 @@ __device__ __forceinline__ int xcd_contiguous(int bid, int grid)
     return x * q + min(x, r) + bid / kXcds;
 }
 
+// The owners of a launch in two kinds of workgroups of T threads. The first
+// long_blocks take the owners of more than CAP pairs a lane of G, a wave each:
+// wave w of W looks at owners w, w + W, ..., so that long ones that stand
+// together (points repeated at a cloud's end) go to different waves. The others
+// call shorter(owner, lane of the group) for the rest, in groups of G lanes. As
+// two kinds the short owners' code keeps its compile-time lane count and carries
+// none of the loops of the long ones'.
+template <int G, int CAP, int T, class Short, class Long>
+__device__ __forceinline__ void split_owners(int block, int blocks, int long_blocks, int n_own, const int32_t *ptr,
+                                             Short shorter, Long longer)
+{
+    if (block < long_blocks) {
+        const int waves = long_blocks * (T / 64), w = block * (T / 64) + ((int)threadIdx.x >> 6), lane = lane_id();
+        for (int base = w; base < n_own; base += 64 * waves) {
+            const int o = min(base + lane * waves, n_own); // owners stay below 2^29, waves below 2^12
+            uint64_t left = __ballot(o < n_own && ptr[o + 1] - ptr[o] > G * CAP);
+            for (; left; left &= left - 1)
+                longer(base + __builtin_ctzll(left) * waves, lane);
+        }
+        return;
+    }
+    const int gid = xcd_contiguous(block - long_blocks, blocks - long_blocks) * T + (int)threadIdx.x;
+    const int o = gid / G; // a sample's owners share an L2
+    if (o < n_own && ptr[o + 1] - ptr[o] <= G * CAP)
+        shorter(o, gid % G);
+}
+
 inline unsigned blocks_for(int64_t n, int per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 
 } // namespace apml

@@ -18,6 +18,7 @@
 //     of the minimum (-) unless the gap was clamped; plus the direct term
 //     grad_loss * v of loss = sum v C; the row kernel turns Cbar into grad_x
 //     with Eq. 5, k_bwd_grad_y into grad_y.
+#include <algorithm>
 #include <type_traits>
 
 #include "apml_internal.h"
@@ -49,17 +50,21 @@ __host__ inline int softmax_lanes(int64_t owners, int64_t pairs)
 // coordinates and, for columns, P_row and the flags of the pair) and their
 // distances and similarities kept in registers, so the segment is read once.
 // Longer segments read the rest again in each step.
-// Owners with more pairs than that take the whole wave (each_owner). Forward +
-// backward, before and after: 32 x 2048 points 357 -> 321 us, losses
-// of 100 x 1024 points 251 -> 201 us, 6 x 1900 x 1500 with rows that fall back
-// to all pairs 3.10 -> 2.53 ms. The forward kernels and the double-precision
-// row adjoint are held to four waves per SIMD: the bound costs them 40 and 16
-// bytes of scratch in the long-segment loops, without it three waves.
+// Owners with more pairs than that take a wave each, in workgroups of their own
+// (split_owners). Forward + backward, against groups that stride through them:
+// 32 x 2048 points 357 -> 321 us, losses of 100 x 1024 points 251 -> 201 us,
+// 6 x 1900 x 1500 with rows that fall back to all pairs 3.10 -> 2.53 ms. With both
+// kinds in one copy of the code, by a run-time lane count, the short owners paid
+// for the long ones' loops: row and column softmax of 4 x 65536 points 34 + 53 ->
+// 39 + 63 us, now 83 in all; of 64 x 8192 65 + 80, 49 + 79 and now 42 + 69. The
+// bounds of four and five waves per SIMD cost the long owners' code up to 8 bytes of scratch.
 constexpr int kSmCache = 8;
-// Pairs a lane of a long segment takes at a time past those (loads in flight):
-// 6 x 1900 x 1500 with fallback rows 1.73 -> 1.59 ms; with four the registers
-// cost the other owners as much (4 x 65536: row adjoint 72 -> 96 us).
-constexpr int kLongBatch = 2;
+// Such an owner's lanes keep kLongCache of their pairs (more cost the others their
+// waves per SIMD: the registers are those of the larger code) and read the rest in
+// each step, kLongLight at a time where a step takes little of a pair, else
+// kLongBatch (in single precision 2: five waves per SIMD instead of six).
+constexpr int kLongCache = 2;
+constexpr int kLongLight = 4, kLongBatch = 2;
 
 // Pair t (row-major position; row i, column j of sample b, the k-th entry of
 // its column) with P0 into the per-sample Sinkhorn pieces of both orders.
@@ -90,9 +95,10 @@ __device__ __forceinline__ double dist3(float ax, float ay, float az, float bx, 
 // ROWS: owner r = b*N + i over row-major pairs t (the other index is the
 // column j); else owner gc = b*M + j over column-major entries q (the other
 // index is the row i, the row-major position t = csc_perm[q]).
-template <bool ROWS>
-__device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p, int o, int G, int lg)
+template <bool ROWS, int G, bool LONG>
+__device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p, int o, int lg)
 {
+    constexpr int NC = LONG ? kLongCache : kSmCache;
     const int n_own = ROWS ? d.N : d.M, n_oth = ROWS ? d.M : d.N;
     const int b = o / n_own;
     const float *own = (ROWS ? d.x : d.y) + (size_t)o * 3;
@@ -104,17 +110,17 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
     const float2 m = ROWS ? d.m12_row[o] : d.m12_col[o];
     const double lk = ROWS ? p.lk_row : p.lk_col;
 
-    int oi[kSmCache], tt[kSmCache];
-    float ox[kSmCache], oy[kSmCache], oz[kSmCache], prow[kSmCache];
-    uint8_t fl[kSmCache];
+    int oi[NC], tt[NC];
+    float ox[NC], oy[NC], oz[NC], prow[NC];
+    uint8_t fl[NC];
 #pragma unroll
-    for (int c = 0; c < kSmCache; ++c) {
+    for (int c = 0; c < NC; ++c) {
         const int k = lg + G * c;
         oi[c] = k < n ? idx[s0 + k] : 0;
         tt[c] = ROWS ? s0 + k : (k < n ? d.csc_perm[s0 + k] : 0);
     }
 #pragma unroll
-    for (int c = 0; c < kSmCache; ++c) {
+    for (int c = 0; c < NC; ++c) {
         const int k = lg + G * c;
         const float *q = oth + 3 * (size_t)oi[c];
         ox[c] = q[0];
@@ -133,12 +139,13 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
     // minimum and second minimum among the stored pairs (single precision)
     Argmins am;
 #pragma unroll
-    for (int c = 0; c < kSmCache; ++c)
+    for (int c = 0; c < NC; ++c)
         if (lg + G * c < n)
             am.see(s0 + lg + G * c, sqdist_f32(a0, a1, a2, ox[c], oy[c], oz[c]), m);
-    strided<kLongBatch>(lg + G * kSmCache, n, G, other, [&](const float3 &q, int k) {
-        am.see(s0 + k, sqdist_f32(a0, a1, a2, q.x, q.y, q.z), m);
-    });
+    if constexpr (LONG)
+        strided<kLongLight>(lg + G * NC, n, G, other, [&](const float3 &q, int k) {
+            am.see(s0 + k, sqdist_f32(a0, a1, a2, q.x, q.y, q.z), m);
+        });
     int q1, q2;
     am.resolve(&q1, &q2, G);
     if (q1 == INT_MAX || q2 == INT_MAX) { // cannot happen: both minima are always emitted
@@ -167,16 +174,16 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
         }
         return;
     }
-    double dc[kSmCache];
+    double dc[NC];
 #pragma unroll
-    for (int c = 0; c < kSmCache; ++c) // only where the lane holds a pair: slots past the segment cost nothing
+    for (int c = 0; c < NC; ++c) // only where the lane holds a pair: slots past the segment cost nothing
         dc[c] = lg + G * c < n ? dist3(a0, a1, a2, ox[c], oy[c], oz[c]) : 0.0;
     auto dist_at = [&](int q) { // distance of the pair at position q of the segment array
         const int k = q - s0;
-        if (k < G * kSmCache) { // held by one lane of the group
+        if (!LONG || k < G * NC) { // held by one lane of the group
             double v = 0.0;
 #pragma unroll
-            for (int c = 0; c < kSmCache; ++c)
+            for (int c = 0; c < NC; ++c)
                 v += lg + G * c == k ? dc[c] : 0.0;
             return group_sum(v, G);
         }
@@ -194,9 +201,9 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
     const double T = fallback ? 0.0 : lk / g;
 
     // kept similarities and their sum
-    double sv[kSmCache], zsum = 0.0;
+    double sv[NC], zsum = 0.0;
 #pragma unroll
-    for (int c = 0; c < kSmCache; ++c) {
+    for (int c = 0; c < NC; ++c) {
         sv[c] = 0.0;
         if (lg + G * c < n) {
             const double s = exp(-T * (dc[c] - c1));
@@ -205,11 +212,12 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
                 zsum += s;
         }
     }
-    strided<kLongBatch>(lg + G * kSmCache, n, G, other, [&](const float3 &q, int) {
-        const double s = exp(-T * (dist3(a0, a1, a2, q.x, q.y, q.z) - c1));
-        if (s >= p.tau)
-            zsum += s;
-    });
+    if constexpr (LONG)
+        strided<kLongLight>(lg + G * NC, n, G, other, [&](const float3 &q, int) {
+            const double s = exp(-T * (dist3(a0, a1, a2, q.x, q.y, q.z) - c1));
+            if (s >= p.tau)
+                zsum += s;
+        });
     zsum = group_sum(zsum, G);
 
     // P = s / Z on the kept pairs; rows store C, columns P0 = (P_row + P_col)/2
@@ -232,30 +240,32 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
         }
     };
 #pragma unroll
-    for (int c = 0; c < kSmCache; ++c)
+    for (int c = 0; c < NC; ++c)
         if (lg + G * c < n)
             write(lg + G * c, tt[c], dc[c], sv[c], prow[c], fl[c]);
-    struct Far {
-        float3 q;
-        int t;
-        float pr;
-        uint8_t f;
-    };
-    strided<kLongBatch>(
-        lg + G * kSmCache, n, G,
-        [&](int k) {
-            Far v{other(k), s0 + k, 0.0f, 0};
-            if (!ROWS) {
-                v.t = d.csc_perm[s0 + k];
-                v.pr = d.p_row[v.t];
-                v.f = d.flags[v.t];
-            }
-            return v;
-        },
-        [&](const Far &v, int k) {
-            const double c = dist3(a0, a1, a2, v.q.x, v.q.y, v.q.z);
-            write(k, v.t, c, exp(-T * (c - c1)), v.pr, v.f);
-        });
+    if constexpr (LONG) {
+        struct Far {
+            float3 q;
+            int t;
+            float pr;
+            uint8_t f;
+        };
+        strided<kLongBatch>(
+            lg + G * NC, n, G,
+            [&](int k) {
+                Far v{other(k), s0 + k, 0.0f, 0};
+                if (!ROWS) {
+                    v.t = d.csc_perm[s0 + k];
+                    v.pr = d.p_row[v.t];
+                    v.f = d.flags[v.t];
+                }
+                return v;
+            },
+            [&](const Far &v, int k) {
+                const double c = dist3(a0, a1, a2, v.q.x, v.q.y, v.q.z);
+                write(k, v.t, c, exp(-T * (c - c1)), v.pr, v.f);
+            });
+    }
     if (lg == 0) {
         (ROWS ? d.T_row : d.T_col)[o] = T;
         (ROWS ? d.C1_row : d.C1_col)[o] = c1;
@@ -266,20 +276,20 @@ __device__ __forceinline__ void owner_softmax(const DevPlan &d, const Params &p,
     }
 }
 
-template <int G> __global__ __launch_bounds__(kBlock, 4) void k_row_softmax(DevPlan d, Params p)
+template <int G> __global__ __launch_bounds__(kBlock, 5) void k_row_softmax(DevPlan d, Params p, int long_blocks)
 {
-    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<kSmCache>(G, gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
-        owner_softmax<true>(d, p, r, lanes, lg);
-    });
+    split_owners<G, kSmCache, kBlock>(
+        blockIdx.x, gridDim.x, long_blocks, d.B * d.N, d.row_ptr,
+        [&](int r, int lg) { owner_softmax<true, G, false>(d, p, r, lg); },
+        [&](int r, int lane) { owner_softmax<true, 64, true>(d, p, r, lane); });
 }
 
-template <int G> __global__ __launch_bounds__(kBlock, 4) void k_col_softmax(DevPlan d, Params p)
+template <int G> __global__ __launch_bounds__(kBlock, 4) void k_col_softmax(DevPlan d, Params p, int long_blocks)
 {
-    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<kSmCache>(G, gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
-        owner_softmax<false>(d, p, gc, lanes, lg);
-    });
+    split_owners<G, kSmCache, kBlock>(
+        blockIdx.x, gridDim.x, long_blocks, d.B * d.M, d.col_ptr,
+        [&](int gc, int lg) { owner_softmax<false, G, false>(d, p, gc, lg); },
+        [&](int gc, int lane) { owner_softmax<false, 64, true>(d, p, gc, lane); });
 }
 
 // Column-major view of columns [j0, j1) of sample b in one workgroup: every
@@ -339,7 +349,7 @@ __device__ __forceinline__ void csc_sample(const DevPlan &d, int b, int j0, int 
 // column ranges per sample) and the row softmax (the other blocks, kCscT / G
 // rows each): independent work in one launch, so the row softmax runs on the
 // CUs the per-sample blocks leave free.
-template <int G> __global__ __launch_bounds__(kCscT) void k_csc_rows(DevPlan d, Params p, int parts)
+template <int G> __global__ __launch_bounds__(kCscT) void k_csc_rows(DevPlan d, Params p, int parts, int long_blocks)
 {
     extern __shared__ uint32_t lds_csc[];
     if ((int)blockIdx.x < d.B * parts) {
@@ -347,10 +357,10 @@ template <int G> __global__ __launch_bounds__(kCscT) void k_csc_rows(DevPlan d, 
         csc_sample(d, b, (int)((int64_t)d.M * part / parts), (int)((int64_t)d.M * (part + 1) / parts), lds_csc);
         return;
     }
-    const int gid = (blockIdx.x - d.B * parts) * kCscT + threadIdx.x;
-    each_owner<kSmCache>(G, gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
-        owner_softmax<true>(d, p, r, lanes, lg);
-    });
+    split_owners<G, kSmCache, kCscT>(
+        blockIdx.x - d.B * parts, gridDim.x - d.B * parts, long_blocks, d.B * d.N, d.row_ptr,
+        [&](int r, int lg) { owner_softmax<true, G, false>(d, p, r, lg); },
+        [&](int r, int lane) { owner_softmax<true, 64, true>(d, p, r, lane); });
 }
 
 __host__ inline size_t csc_sample_lds(int M, int64_t max_pairs)
@@ -387,16 +397,11 @@ __device__ __forceinline__ double p0bar(const DevPlan &d, int t, double w, doubl
 // 0.0338 -> 0.0331 ms).
 constexpr int kBwdCache = 4;
 
-template <bool DP> struct BwdP {
-    static constexpr int kCache = kBwdCache;
-    using T = std::conditional_t<DP, double, float>; // type of the cached P
-};
-
-template <bool DP>
-__device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p, int gc, int G, int lg)
+template <bool DP, int G, bool LONG>
+__device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p, int gc, int lg)
 {
-    constexpr int NC = BwdP<DP>::kCache;
-    using PT = typename BwdP<DP>::T;
+    constexpr int NC = LONG ? kLongCache : kBwdCache, LB = LONG ? kLongBatch + DP : 1;
+    using PT = std::conditional_t<DP, double, float>; // type of the cached P
     const int b = gc / d.M;
     const double gl = d.grad_loss[b];
     const int s0 = d.col_ptr[gc], n = d.col_ptr[gc + 1] - s0;
@@ -441,7 +446,7 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
             double c;
             uint8_t f;
         };
-        strided<kLongBatch>(
+        strided<LONG ? kLongLight : 1>(
             lg + G * NC, n, G,
             [&](int k) {
                 const int t = d.csc_perm[s0 + k];
@@ -477,13 +482,13 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         sigma += kq[c] ? (double)pq[c] * aq[c] : 0.0;
-    strided<kLongBatch>(lg + G * NC, n, G, far, [&](const Far &v, int) { sigma += far_p(v) * far_a(v); });
+    strided<LB>(lg + G * NC, n, G, far, [&](const Far &v, int) { sigma += far_p(v) * far_a(v); });
     sigma = group_sum(sigma, G);
     double tbar = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         tbar -= kq[c] ? (double)pq[c] * (aq[c] - sigma) * (cq[c] - c1) : 0.0;
-    strided<kLongBatch>(lg + G * NC, n, G, far,
+    strided<LB>(lg + G * NC, n, G, far,
                         [&](const Far &v, int) { tbar -= far_p(v) * (far_a(v) - sigma) * (v.c - c1); });
     tbar = group_sum(tbar, G);
     const double gapbar = gapbar_scale * tbar;
@@ -500,24 +505,24 @@ __device__ __forceinline__ void bwd_col_owner(const DevPlan &d, const Params &p,
         if (k < n)
             d.cbar[tq[c]] = gap_terms(s0 + k, kq[c] ? -T * (double)pq[c] * (aq[c] - sigma) : 0.0);
     }
-    strided<kLongBatch>(lg + G * NC, n, G, far, [&](const Far &v, int k) {
+    strided<LONG ? kLongBatch : 1>(lg + G * NC, n, G, far, [&](const Far &v, int k) {
         d.cbar[v.t] = gap_terms(s0 + k, -T * far_p(v) * (far_a(v) - sigma));
     });
 }
 
-template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_softmax(DevPlan d, Params p)
+template <int G, bool DP> __global__ __launch_bounds__(kBlock) void k_bwd_col_softmax(DevPlan d, Params p, int long_blocks)
 {
-    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<kSmCache>(G, gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
-        bwd_col_owner<DP>(d, p, gc, lanes, lg);
-    });
+    split_owners<G, kSmCache, kBlock>(
+        blockIdx.x, gridDim.x, long_blocks, d.B * d.M, d.col_ptr,
+        [&](int gc, int lg) { bwd_col_owner<DP, G, false>(d, p, gc, lg); },
+        [&](int gc, int lane) { bwd_col_owner<DP, 64, true>(d, p, gc, lane); });
 }
 
-template <bool DP>
-__device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p, int keep_cbar, int r, int G, int lg)
+template <bool DP, int G, bool LONG>
+__device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p, int keep_cbar, int r, int lg)
 {
-    constexpr int NC = BwdP<DP>::kCache;
-    using PT = typename BwdP<DP>::T;
+    constexpr int NC = LONG ? kLongCache : kBwdCache, LB = LONG ? kLongBatch + DP : 1;
+    using PT = std::conditional_t<DP, double, float>; // type of the cached P
     const int b = r / d.N;
     const size_t BN = (size_t)d.B * d.N, BM = (size_t)d.B * d.M;
     const float *xr = d.x + (size_t)r * 3;
@@ -562,7 +567,7 @@ __device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p,
             double c;
             uint8_t f;
         };
-        strided<kLongBatch>(
+        strided<LONG ? kLongLight : 1>(
             lg + G * NC, n, G, [&](int k) { return CF{d.cost[t0 + k], d.flags[t0 + k]}; },
             [&](const CF &v, int) {
                 if (v.f & 1)
@@ -594,13 +599,13 @@ __device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p,
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         sigma += kq[c] ? (double)pq[c] * aq[c] : 0.0;
-    strided<kLongBatch>(lg + G * NC, n, G, far, [&](const Far &v, int) { sigma += far_p(v) * far_a(v); });
+    strided<LB>(lg + G * NC, n, G, far, [&](const Far &v, int) { sigma += far_p(v) * far_a(v); });
     sigma = group_sum(sigma, G);
     double tbar = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         tbar -= kq[c] ? (double)pq[c] * (aq[c] - sigma) * (cq[c] - c1) : 0.0;
-    strided<kLongBatch>(lg + G * NC, n, G, far,
+    strided<LB>(lg + G * NC, n, G, far,
                         [&](const Far &v, int) { tbar -= far_p(v) * (far_a(v) - sigma) * (v.c - c1); });
     tbar = group_sum(tbar, G);
     const double gapbar = gscale * tbar;
@@ -650,15 +655,15 @@ __device__ __forceinline__ void bwd_row_owner(const DevPlan &d, const Params &p,
 }
 
 template <int G, bool DP>
-__global__ __launch_bounds__(kBlock, 4) void k_bwd_row_softmax(DevPlan d, Params p, int keep_cbar)
+__global__ __launch_bounds__(kBlock, 4) void k_bwd_row_softmax(DevPlan d, Params p, int keep_cbar, int long_blocks)
 {
-    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<kSmCache>(G, gid / G, d.B * d.N, d.row_ptr, [&](int lanes, int r, int lg) {
-        bwd_row_owner<DP>(d, p, keep_cbar, r, lanes, lg);
-    });
+    split_owners<G, kSmCache, kBlock>(
+        blockIdx.x, gridDim.x, long_blocks, d.B * d.N, d.row_ptr,
+        [&](int r, int lg) { bwd_row_owner<DP, G, false>(d, p, keep_cbar, r, lg); },
+        [&](int r, int lane) { bwd_row_owner<DP, 64, true>(d, p, keep_cbar, r, lane); });
 }
 
-__device__ __forceinline__ void grad_y_owner(const DevPlan &d, const Params &p, int gc, int G, int lg)
+template <int G> __device__ __forceinline__ void grad_y_owner(const DevPlan &d, const Params &p, int gc, int lg)
 {
     const int b = gc / d.M;
     const float *yc = d.y + (size_t)gc * 3;
@@ -693,12 +698,12 @@ __device__ __forceinline__ void grad_y_owner(const DevPlan &d, const Params &p, 
     }
 }
 
-template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_grad_y(DevPlan d, Params p)
+template <int G> __global__ __launch_bounds__(kBlock) void k_bwd_grad_y(DevPlan d, Params p, int long_blocks)
 {
-    const int gid = xcd_contiguous(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; // a sample's owners share an L2
-    each_owner<kSmCache>(G, gid / G, d.B * d.M, d.col_ptr, [&](int lanes, int gc, int lg) {
-        grad_y_owner(d, p, gc, lanes, lg);
-    });
+    split_owners<G, kSmCache, kBlock>(
+        blockIdx.x, gridDim.x, long_blocks, d.B * d.M, d.col_ptr,
+        [&](int gc, int lg) { grad_y_owner<G>(d, p, gc, lg); },
+        [&](int gc, int lane) { grad_y_owner<64>(d, p, gc, lane); });
 }
 
 } // namespace
@@ -708,81 +713,86 @@ bool csc_sample_fits(int N, int M, int64_t max_pairs)
     return N <= 65536 && max_pairs <= 65536 && csc_sample_lds(M, max_pairs) <= 160 * 1024;
 }
 
-// Launches kernel template K with the lanes per owner of `owners`.
-#define APML_LAUNCH_G(K, owners, pairs, per_block, shmem, s, ...)                                                   \
-    do {                                                                                                           \
-        const int g_ = softmax_lanes(owners, pairs);                                                               \
-        const dim3 grid_(blocks_for((int64_t)(owners) * g_, per_block));                                           \
-        if (g_ == 16)                                                                                              \
-            hipLaunchKernelGGL(K<16>, grid_, dim3(per_block), shmem, s, __VA_ARGS__);                              \
-        else if (g_ == 8)                                                                                          \
-            hipLaunchKernelGGL(K<8>, grid_, dim3(per_block), shmem, s, __VA_ARGS__);                               \
-        else                                                                                                       \
-            hipLaunchKernelGGL(K<kGroup>, grid_, dim3(per_block), shmem, s, __VA_ARGS__);                          \
-    } while (0)
+namespace {
 
-// The same for a kernel template with a second, boolean parameter X.
-#define APML_LAUNCH_GP(K, X, owners, pairs, s, ...)                                                                 \
-    do {                                                                                                           \
-        const int g_ = softmax_lanes(owners, pairs);                                                               \
-        const dim3 grid_(blocks_for((int64_t)(owners) * g_, kBlock));                                              \
-        if (g_ == 16)                                                                                              \
-            hipLaunchKernelGGL((K<16, X>), grid_, dim3(kBlock), 0, s, __VA_ARGS__);                                \
-        else if (g_ == 8)                                                                                          \
-            hipLaunchKernelGGL((K<8, X>), grid_, dim3(kBlock), 0, s, __VA_ARGS__);                                 \
-        else                                                                                                       \
-            hipLaunchKernelGGL((K<kGroup, X>), grid_, dim3(kBlock), 0, s, __VA_ARGS__);                            \
-    } while (0)
+// Workgroups of T threads that look for owners of more than kSmCache pairs a lane
+// (split_owners): none where the host knows of none, else a wave for every four
+// owners, up to 2048 waves (those take more owners each); a multiple of 8, which
+// keeps the other workgroups' mapping to the XCDs. Where an owner has more than
+// kFullOwner pairs, a wave that meets two of them sets the launch's time, so twice
+// the waves (6 x 1900 x 1500 with owners that keep all pairs, forward and adjoint
+// 141 + 309 -> 124 + 254 us; elsewhere the waves cost 1 to 2 us more).
+constexpr int kFullOwner = 1024;
+template <int T> int long_blocks_of(int64_t owners, int most, int lanes)
+{
+    if (most <= lanes * kSmCache)
+        return 0;
+    const bool full = most > kFullOwner;
+    const int waves = (int)(full ? std::min<int64_t>((owners + 1) / 2, 4096) : std::min<int64_t>((owners + 3) / 4, 2048));
+    return (waves + T / 64 * 8 - 1) / (T / 64 * 8) * 8;
+}
+
+// Launches kernel template instance K<lanes> for `owners` with `most` pairs at most.
+template <template <int> class K, class... A>
+void launch_owners(int64_t owners, int64_t pairs, int most, hipStream_t s, A... args)
+{
+    const int g = softmax_lanes(owners, pairs), lb = long_blocks_of<kBlock>(owners, most, g);
+    const dim3 grid(lb + blocks_for(owners * g, kBlock)), block(kBlock);
+    if (g == 16)
+        hipLaunchKernelGGL(K<16>::fn, grid, block, 0, s, args..., lb);
+    else if (g == 8)
+        hipLaunchKernelGGL(K<8>::fn, grid, block, 0, s, args..., lb);
+    else
+        hipLaunchKernelGGL(K<kGroup>::fn, grid, block, 0, s, args..., lb);
+}
+template <int G> struct RowSm { static constexpr auto fn = k_row_softmax<G>; };
+template <int G> struct ColSm { static constexpr auto fn = k_col_softmax<G>; };
+template <int G> struct BwdColSm { static constexpr auto fn = k_bwd_col_softmax<G, false>; };
+template <int G> struct BwdColSmD { static constexpr auto fn = k_bwd_col_softmax<G, true>; };
+template <int G> struct BwdRowSm { static constexpr auto fn = k_bwd_row_softmax<G, false>; };
+template <int G> struct BwdRowSmD { static constexpr auto fn = k_bwd_row_softmax<G, true>; };
+template <int G> struct GradY { static constexpr auto fn = k_bwd_grad_y<G>; };
+
+} // namespace
 
 hipError_t launch_csc_and_softmax(const DevPlan &d, const Params &p, int64_t max_pairs, hipStream_t s)
 {
     const size_t bytes = csc_sample_lds(d.M, max_pairs);
     const int64_t BN = (int64_t)d.B * d.N;
-    const int gr = softmax_lanes(BN, d.nnz);
-    const void *k = gr == 16  ? (const void *)k_csc_rows<16>
-                    : gr == 8 ? (const void *)k_csc_rows<8>
-                              : (const void *)k_csc_rows<kGroup>;
-    hipError_t e = set_dynamic_lds(k, bytes);
+    const int gr = softmax_lanes(BN, d.nnz), lb = long_blocks_of<kCscT>(BN, d.most_row, gr);
+    const auto k = gr == 16 ? k_csc_rows<16> : gr == 8 ? k_csc_rows<8> : k_csc_rows<kGroup>;
+    hipError_t e = set_dynamic_lds((const void *)k, bytes);
     if (e != hipSuccess)
         return e;
-    const unsigned rows = blocks_for(BN * gr, kCscT);
     // Two column ranges per sample while that still leaves CUs for the row
     // softmax: at 32 samples of 2048 points this took this launch and the
     // column softmax together from 44.5 to 42.0 us (four ranges: 42.8); each
     // range reads all of its sample's pairs.
     const int parts = 2 * d.B <= 256 ? 2 : 1;
-    const dim3 grid(d.B * parts + rows);
-    if (gr == 16)
-        hipLaunchKernelGGL(k_csc_rows<16>, grid, dim3(kCscT), bytes, s, d, p, parts);
-    else if (gr == 8)
-        hipLaunchKernelGGL(k_csc_rows<8>, grid, dim3(kCscT), bytes, s, d, p, parts);
-    else
-        hipLaunchKernelGGL(k_csc_rows<kGroup>, grid, dim3(kCscT), bytes, s, d, p, parts);
-    APML_LAUNCH_G(k_col_softmax, (int64_t)d.B * d.M, d.nnz, kBlock, 0, s, d, p);
+    hipLaunchKernelGGL(k, dim3(d.B * parts + lb + blocks_for(BN * gr, kCscT)), dim3(kCscT), bytes, s, d, p, parts, lb);
+    launch_owners<ColSm>((int64_t)d.B * d.M, d.nnz, d.most_col, s, d, p);
     return hipGetLastError();
 }
 
 void launch_softmax(const DevPlan &d, const Params &p, hipStream_t s)
 {
-    APML_LAUNCH_G(k_row_softmax, (int64_t)d.B * d.N, d.nnz, kBlock, 0, s, d, p);
-    APML_LAUNCH_G(k_col_softmax, (int64_t)d.B * d.M, d.nnz, kBlock, 0, s, d, p);
+    launch_owners<RowSm>((int64_t)d.B * d.N, d.nnz, d.most_row, s, d, p);
+    launch_owners<ColSm>((int64_t)d.B * d.M, d.nnz, d.most_col, s, d, p);
 }
 
 void launch_bwd_softmax(const DevPlan &d, const Params &p, bool double_p, hipStream_t s)
 {
+    const int64_t BN = (int64_t)d.B * d.N, BM = (int64_t)d.B * d.M;
     const int keep = d.grad_y != nullptr ? 1 : 0;
     if (double_p) {
-        APML_LAUNCH_GP(k_bwd_col_softmax, true, (int64_t)d.B * d.M, d.nnz, s, d, p);
-        APML_LAUNCH_GP(k_bwd_row_softmax, true, (int64_t)d.B * d.N, d.nnz, s, d, p, keep);
+        launch_owners<BwdColSmD>(BM, d.nnz, d.most_col, s, d, p);
+        launch_owners<BwdRowSmD>(BN, d.nnz, d.most_row, s, d, p, keep);
     } else {
-        APML_LAUNCH_GP(k_bwd_col_softmax, false, (int64_t)d.B * d.M, d.nnz, s, d, p);
-        APML_LAUNCH_GP(k_bwd_row_softmax, false, (int64_t)d.B * d.N, d.nnz, s, d, p, keep);
+        launch_owners<BwdColSm>(BM, d.nnz, d.most_col, s, d, p);
+        launch_owners<BwdRowSm>(BN, d.nnz, d.most_row, s, d, p, keep);
     }
     if (d.grad_y)
-        APML_LAUNCH_G(k_bwd_grad_y, (int64_t)d.B * d.M, d.nnz, kBlock, 0, s, d, p);
+        launch_owners<GradY>(BM, d.nnz, d.most_col, s, d, p);
 }
-
-#undef APML_LAUNCH_G
-#undef APML_LAUNCH_GP
 
 } // namespace apml

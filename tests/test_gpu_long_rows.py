@@ -50,3 +50,12 @@ def test_long_owners(m, swap):
 def test_many_long_owners(far):
     X, Y = clouds(300, 700, far, far)
     _check_batch(X, Y, f"{far} long rows", n_iter=3)
+
+
+# waves that look for long owners: more of them where an owner has more than 1024
+# pairs; column and row owners at that edge, and short owners only beside them
+@pytest.mark.parametrize("m", [1023, 1024, 1025, 1028, 1029])
+def test_owners_at_the_full_edge(m):
+    X, Y = clouds(1500, m, 2, m)
+    _check_batch(X, Y, f"rows of {m}", n_iter=2)
+    _check_batch(Y, X, f"columns of {m}", n_iter=2)
