@@ -601,8 +601,7 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
     SpatialArgs sa{};
     CullDir crows{}, ccols{};
     CullEmitArgs ca{};
-    int32_t *cnt = nullptr; // stored pairs per row (per (row, chunk) for the full scan)
-    int cnt_chunks = 1;
+    int32_t *cnt = nullptr; // stored pairs per row
     if (!skip) {
         choose_pair_scan(ps, B, N, M);
         ps.x = x;
@@ -620,6 +619,7 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
             E_row = c.take<float>(BN);
             ypack = c.take<float4>(BM);
             ea.cnt = c.take<int32_t>((size_t)BN * ea.S);
+            ea.row_cnt = ea.S > 1 ? c.take<int32_t>(BN) : ea.cnt;
             if (ea.chunk <= 65536) {
                 ea.kst = stage_slots(ea.S);
                 ea.stage_narrow = ea.chunk <= 256;
@@ -646,7 +646,8 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
             PhaseTimer pt(PH_STATS, s, timed);
             launch_top2_pairs(ps, s);
             HIP_TRY(hipGetLastError());
-            FinalizeDir fr{ps.row_partial, x, dv.m12_row, E_row, nullptr, nullptr, nullptr, N, ps.S_r, kp.lk_row};
+            FinalizeDir fr{ps.row_partial, x, dv.m12_row, E_row, nullptr, ea.S > 1 ? ea.row_cnt : nullptr, nullptr, N,
+                           ps.S_r, kp.lk_row};
             FinalizeDir fc{ps.col_partial, y, dv.m12_col, nullptr, ypack, col_cnt, ba.col_fill, M, ps.S_c,
                            kp.lk_col};
             launch_finalize(fr, fc, B, kp, dv.ctr, s); // also clears the counters
@@ -664,8 +665,7 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
         ea.owner_blocks = owner_blocks;
         ea.col_cnt = col_cnt; // cleared by the finalize kernel
         ea.ctr = dv.ctr;
-        cnt = ea.cnt;
-        cnt_chunks = ea.S;
+        cnt = ea.row_cnt;
     } else {
         const int pad_x = pad64(N), pad_y = pad64(M);
         sa.x = x;
@@ -798,7 +798,7 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
         pt.stop();
     }
     // row and column offsets, and what the host needs, in one block
-    launch_offsets(cnt, cnt_chunks, col_cnt, dv.ctr, B, N, M, dv.row_ptr, dv.col_ptr, off_tiles,
+    launch_offsets(cnt, col_cnt, dv.ctr, B, N, M, dv.row_ptr, dv.col_ptr, off_tiles,
                    bumped ? (Readback *)rb_dev : (Readback *)pinned().device_ptr(plan->device), s);
     HIP_TRY(hipGetLastError());
     if (bumped)

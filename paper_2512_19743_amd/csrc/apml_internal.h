@@ -81,7 +81,7 @@ struct FinalizeDir {
     float2 *m12;           // out: (m1, m2) per owner
     float *E;              // out (rows): emission threshold on the squared distance
     float4 *packed;        // out (columns): (x, y, z, emission threshold)
-    int32_t *zero_a, *zero_b; // (columns) per-owner counters cleared here
+    int32_t *zero_a, *zero_b; // per-owner counters cleared here (columns both; rows zero_a, or NULL)
     int n_own, S;
     double log_ratio;      // -log((1-p)/((K-1)p)), K = length of the other set
 };
@@ -129,6 +129,7 @@ struct EmitArgs {
     const float *E_row;  // [B*N]
     int B, N, M, S, chunk, owner_blocks;
     int32_t *cnt;        // [B*N][S] stored pairs per (row, column chunk)
+    int32_t *row_cnt;    // [B*N] their sum over the chunks, zero before the first pass; with one chunk cnt itself
     int32_t *col_cnt;    // [B*M] stored pairs per column
     uint16_t *stage;     // [B*N][S][kst] column offsets within the chunk of the first hits, or NULL;
                          // one byte each when stage_narrow (chunks of at most 256 columns)
@@ -384,13 +385,13 @@ __host__ __device__ inline int64_t *readback_totals(Readback *r) { return reinte
 __host__ __device__ inline int32_t *readback_offsets(Readback *r, int B) { return reinterpret_cast<int32_t *>(readback_totals(r) + 2 * B); }
 __host__ __device__ inline int32_t *readback_pieces(Readback *r, int B) { return readback_offsets(r, B) + B + 1; }
 
-// Row and column offsets of all samples (row_ptr [B*N+1] from the per-(row,
-// chunk) counts cnt [B*N][S], col_ptr [B*M+1] from col_cnt) and the read-back
+// Row and column offsets of all samples (row_ptr [B*N+1] from the rows' counts
+// row_cnt, col_ptr [B*M+1] from col_cnt) and the read-back
 // block, in two launches. tiles is device scratch of offsets_scratch_ints
 // ints (per-tile totals); rb_host, mapped pinned host memory, receives the
 // whole block, written by the kernels.
 size_t offsets_scratch_ints(int B, int N, int M);
-void launch_offsets(const int32_t *cnt, int S, const int32_t *col_cnt, const Counters *ctr, int B, int N, int M,
+void launch_offsets(const int32_t *row_cnt, const int32_t *col_cnt, const Counters *ctr, int B, int N, int M,
                     int32_t *row_ptr, int32_t *col_ptr, int32_t *tiles, Readback *rb_host, hipStream_t s);
 // Whether the per-sample kernels take a batch: counts are the host copy of the
 // piece counts of the read-back block, max_pairs the largest sample's stored

@@ -18,25 +18,6 @@ namespace {
 
 constexpr int kOffT = 1024;
 
-// Pair count of owner k of sample b: the sum of a row's chunk counts (in
-// 16-byte loads when the count is a multiple of 4), or a column's count.
-__device__ __forceinline__ int owner_len(bool rows, const int32_t *cnt, int S, const int32_t *col_cnt, int b, int N,
-                                         int M, int k)
-{
-    if (!rows)
-        return col_cnt[(size_t)b * M + k];
-    const int32_t *rc = cnt + ((size_t)b * N + k) * S;
-    int len = 0, c = 0;
-    if (S % 4 == 0)
-        for (; c < S; c += 4) {
-            const int4 v = *reinterpret_cast<const int4 *>(rc + c);
-            len += v.x + v.y + v.z + v.w;
-        }
-    for (; c < S; ++c)
-        len += rc[c];
-    return len;
-}
-
 // Owners are cut into tiles of kOffTile; a workgroup of kOffT threads takes
 // one tile of one sample and direction (grid: tiles x B x 2, blockIdx.z 0 for
 // rows, 1 for columns), thread t owners tile * kOffTile + u * kOffT + t.
@@ -45,8 +26,8 @@ constexpr int kOffTile = kOffT * kOffPer;
 
 // Per tile: the pair total, the lane positions of its owners' piece groups and
 // the largest piece count, into tiles[((dir * B + b) * T + tile) * 3 + 0..2].
-__global__ __launch_bounds__(kOffT) void k_sample_scan(const int32_t *cnt, int S, const int32_t *col_cnt, int N,
-                                                       int M, int32_t *tiles, int T)
+__global__ __launch_bounds__(kOffT) void k_sample_scan(const int32_t *row_cnt, const int32_t *col_cnt, int N, int M,
+                                                       int32_t *tiles, int T)
 {
     __shared__ int red[3][kOffT / 64];
     const int tile = blockIdx.x, b = blockIdx.y, B = gridDim.y, tid = threadIdx.x;
@@ -55,11 +36,12 @@ __global__ __launch_bounds__(kOffT) void k_sample_scan(const int32_t *cnt, int S
     if (tile * kOffTile >= n) // the whole workgroup
         return;
     const int lane = lane_id(), wave = tid >> 6;
+    const int32_t *cnt = (rows ? row_cnt : col_cnt) + (size_t)b * n;
     int len[kOffPer];
 #pragma unroll
     for (int u = 0; u < kOffPer; ++u) {
         const int k = tile * kOffTile + u * kOffT + tid;
-        len[u] = k < n ? owner_len(rows, cnt, S, col_cnt, b, N, M, k) : -1;
+        len[u] = k < n ? cnt[k] : -1;
     }
     int sum = 0, pos = 0, mx = 0;
 #pragma unroll
@@ -100,7 +82,7 @@ __global__ __launch_bounds__(kOffT) void k_sample_scan(const int32_t *cnt, int S
 // owners' counts (one workgroup scan per round u). The first tile of each
 // sample also closes row_ptr / col_ptr and fills the read-back block (totals,
 // offsets, piece counts; the counters from sample 0's row tile).
-__global__ __launch_bounds__(kOffT) void k_sample_base(const int32_t *cnt, int S, const int32_t *col_cnt,
+__global__ __launch_bounds__(kOffT) void k_sample_base(const int32_t *row_cnt, const int32_t *col_cnt,
                                                        const Counters *ctr, int N, int M, int32_t *row_ptr,
                                                        int32_t *col_ptr, const int32_t *tiles, int T,
                                                        Readback *rb_host)
@@ -159,11 +141,12 @@ __global__ __launch_bounds__(kOffT) void k_sample_base(const int32_t *cnt, int S
     if (tile == 0 && b == 0 && rows) // the counters, word by word over the workgroup
         for (int i = tid; i < (int)(sizeof(Counters) / 4); i += kOffT)
             reinterpret_cast<uint32_t *>(&rb_host->ctr)[i] = reinterpret_cast<const uint32_t *>(ctr)[i];
+    const int32_t *cnt = (rows ? row_cnt : col_cnt) + (size_t)b * n;
     int len[kOffPer];
 #pragma unroll
     for (int u = 0; u < kOffPer; ++u) {
         const int k = tile * kOffTile + u * kOffT + tid;
-        len[u] = k < n ? owner_len(rows, cnt, S, col_cnt, b, N, M, k) : 0;
+        len[u] = k < n ? cnt[k] : 0;
     }
     __syncthreads(); // base_s
     int carry = base_s;
@@ -310,12 +293,12 @@ __global__ __launch_bounds__(kBlock) void k_count_support(const int32_t *row_ptr
 
 } // namespace
 
-void launch_offsets(const int32_t *cnt, int S, const int32_t *col_cnt, const Counters *ctr, int B, int N, int M,
+void launch_offsets(const int32_t *row_cnt, const int32_t *col_cnt, const Counters *ctr, int B, int N, int M,
                     int32_t *row_ptr, int32_t *col_ptr, int32_t *tiles, Readback *rb_host, hipStream_t s)
 {
     const int T = (std::max(N, M) + kOffTile - 1) / kOffTile;
-    hipLaunchKernelGGL(k_sample_scan, dim3(T, B, 2), dim3(kOffT), 0, s, cnt, S, col_cnt, N, M, tiles, T);
-    hipLaunchKernelGGL(k_sample_base, dim3(T, B, 2), dim3(kOffT), 0, s, cnt, S, col_cnt, ctr, N, M, row_ptr, col_ptr,
+    hipLaunchKernelGGL(k_sample_scan, dim3(T, B, 2), dim3(kOffT), 0, s, row_cnt, col_cnt, N, M, tiles, T);
+    hipLaunchKernelGGL(k_sample_base, dim3(T, B, 2), dim3(kOffT), 0, s, row_cnt, col_cnt, ctr, N, M, row_ptr, col_ptr,
                        (const int32_t *)tiles, T, rb_host);
 }
 
