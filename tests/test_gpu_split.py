@@ -89,3 +89,18 @@ def test_split_matches_one_workgroup(case, monkeypatch):
         for b in range(X.shape[0]):
             np.testing.assert_array_equal(other["v"][b], one["v"][b])
         assert np.isfinite(other["loss"]).all()
+
+
+# More samples than can have two workgroups each: one workgroup a sample, its
+# pieces in registers (up to four slots) or streamed. The first samples' results
+# are those of a batch of three, which is split.
+@pytest.mark.parametrize("n", [2100, 4096])
+def test_one_workgroup_by_batch_size(n):
+    X, Y = custom(78, 3, n, n - 7, reference="primitives", prediction="perm_noise", sigma=0.03)
+    note(f"one workgroup a sample: 131 x {n} x {n - 7}")
+    few = run_gpu(X, Y, n_iter=4)
+    many = run_gpu(*(np.concatenate([c] * 44)[:131] for c in (X, Y)), n_iter=4)
+    assert np.isfinite(many["loss"]).all() and np.array_equal(many["plan"].nnz()[:3], few["plan"].nnz())
+    for name in ("loss", "gx", "gy"):
+        for b in range(131):
+            np.testing.assert_array_equal(many[name][b], few[name][b % 3])
