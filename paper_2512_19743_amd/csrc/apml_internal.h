@@ -453,7 +453,7 @@ constexpr int kDenseMaxD = 16; // largest point dimension of the dense path
 struct DenseSide {
     int32_t *k1, *k2;          // indices of the minimum and the second minimum
     double *c1, *g, *T, *iZ;   // minimum cost, clamped gap, temperature (Eq. 1), 1 / softmax normaliser (Eq. 2)
-    double *n2;                // -T log2(e)
+    double *n2;                // -T log2(e), no further below 0 than -1e250
     uint8_t *clamped;          // gap clamped: no temperature gradient
     float *pf;                 // coordinates padded to dp, in single
     double *pd;                // and in double precision

@@ -85,7 +85,7 @@ __device__ __forceinline__ double root(double s)
     return __builtin_fma(__builtin_fma(-g, g, s), h, g);
 }
 
-// 2^t for t up to 1024 (below -1100: 0; NaN stays, by f): 2^n (1 + f q(f)), n
+// 2^t for finite t (above 1024 infinity, below -1100: 0; NaN stays, by f): 2^n (1 + f q(f)), n
 // the nearest whole number and |f| <= 1/2, q the polynomial that interpolates (2^f - 1) / f at
 // eleven Chebyshev nodes (relative error 2e-17 of 2^f, exactly 1 at 0). 17
 // operations against the library exponential's 26, which with the root's 8
@@ -276,7 +276,10 @@ __global__ __launch_bounds__(kBlock) void k_dstat(DenseDev D, Split sp, const fl
     s.c1[o] = c1;
     s.g[o] = g;
     s.T[o] = (rows ? lk_row : lk_col) / g;
-    s.n2[o] = -1.4426950408889634 * s.T[o];
+    // a T beyond 1e250 (a clamped gap of a tiny eps_gap) as 1e250: every difference of
+    // costs but 0 gives the same 0 or infinity, and the product stays finite (exp2_of)
+    const double n2 = -1.4426950408889634 * s.T[o];
+    s.n2[o] = n2 < -1e250 && n2 >= -1.7976931348623157e308 ? -1e250 : n2;
     s.clamped[o] = clamped;
     s.sc[o] = 1.0;
 }

@@ -79,3 +79,23 @@ def test_dense_points_that_are_not_finite(value, d):
         for got, ref in zip(run_dense(*bad, gbar=[1.0, 1.0, 1.0], n_iter=3), clean):
             assert np.isnan(got[1]).all()
             assert np.array_equal(got[0], ref[0]) and np.array_equal(got[2], ref[2])
+
+
+# A gap clamped to a tiny eps_gap: the temperature times a difference of costs
+# passes the range of a double, and the softmax is 1 on the nearest points and 0
+# elsewhere, as its limit says.
+@pytest.mark.parametrize("eps_gap", [1e-200, 1e-260, 2e-307])
+def test_dense_temperature_beyond_range(eps_gap):
+    rng = np.random.default_rng(310)
+    X, Y = (rng.uniform(-3.0, 3.0, (2, n, 3)).astype(np.float32) for n in (20, 30))
+    Y[:, 15:] = Y[:, :15]  # every row's two nearest columns coincide
+    loss, gx, gy = run_dense(X, Y, gbar=[1.0, 1.0], n_iter=0, delta=0.0, eps_gap=eps_gap)
+    for b in range(2):
+        x, y = (torch.from_numpy(c[b].astype(np.float64)) for c in (X, Y))
+        D = (x[:, None] - y[None]).square().sum(-1).sqrt()
+        P = (D == D.min(1, keepdim=True)[0]).double() * 0.5
+        gap = torch.sort(D, 0)[0]
+        T = np.log(19 * 0.8 / 0.2) / (gap[1] - gap[0])
+        P = 0.5 * (P + torch.softmax(-T * (D - gap[0]), 0))
+        ref = (P * D).sum().item()
+        assert abs(loss[b] - ref) <= LOSS_RTOL * ref
