@@ -124,6 +124,7 @@ def _check(func: str, status: int):
             detail += f" (PyTorch's allocator: {type(torch_alloc_error).__name__}: {torch_alloc_error})"
         torch_alloc_error = None
         raise ApmlError(func, status, detail)
+    torch_alloc_error = None  # a call may do without memory that was refused
 
 
 def apml_params_default(**overrides) -> apml_params:

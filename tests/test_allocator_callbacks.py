@@ -73,3 +73,10 @@ def test_out_of_memory_error_names_the_allocator_exception():
     else:
         raise AssertionError("no error raised")
     assert _lib.torch_alloc_error is None
+
+
+def test_an_error_of_a_call_that_went_on_without_the_memory_is_not_kept():
+    # the backward pass takes other kernels where its exchange's memory is refused
+    _lib.torch_alloc_error = torch.OutOfMemoryError("device full")
+    _lib._check("apml_backward", 0)
+    assert _lib.torch_alloc_error is None
