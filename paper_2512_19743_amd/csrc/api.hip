@@ -351,6 +351,7 @@ struct apml_plan {
     bool sink_fwd = false;  // per-sample Sinkhorn kernels take this plan
     bool sink_wide = false; // streamed per-sample Sinkhorn kernels (larger samples)
     bool timed = true;  // phases recorded by the profiler (off for the no-alloc entry point)
+    bool with_grad = false; // a backward pass follows in the same bump region
     Arena keep;         // everything backward and export need
     DevPlan dv{};       // device arrays (x, y and the backward fields are set per call)
 };
@@ -533,6 +534,25 @@ namespace {
 // Bytes of the read-back block the no-alloc entry point keeps in host memory
 // of its own (it bounds B there).
 constexpr size_t kStaticReadbackBytes = 64 << 10;
+
+// The scratch of the backward pass of plan, from c into dv. wide: with the
+// exchange of the per-sample kernels of larger samples.
+void lay_backward(const apml_plan &plan, DevPlan &dv, Carve &c, bool wide)
+{
+    const size_t BN = (size_t)plan.B * plan.N, BM = (size_t)plan.B * plan.M;
+    dv.cbar = c.take<double>(plan.stored);
+    if (dv.L == 0)
+        return;
+    dv.adj = c.take<double>(plan.stored);
+    dv.rbar = c.take<double>(BN);
+    dv.cs = c.take<double2>(BM);
+    if (wide) {
+        if (sinkhorn_bwd_streams(dv.wk_row.slots, plan.B))
+            dv.wz = c.take<double>(packed_order_words(plan.B, dv.wk_row.slots));
+        dv.yr = c.take<double>(sinkhorn_exchange_words(dv.L, BN));
+        dv.yc = c.take<double>(sinkhorn_exchange_words(dv.L, BM));
+    }
+}
 
 // The forward pass (Alg. 1) into plan, whose device memory comes from
 // plan->keep: the pool (or the caller's allocator), or a bump region. The
@@ -972,6 +992,16 @@ apml_status run_forward(apml_plan *plan, const float *x, const float *y, int32_t
             return fail(APML_ERR_OUT_OF_MEMORY, "device allocation failed (plan)");
         lay(c);
     }
+    if (bumped && plan->with_grad) { // known here, before a kernel writes the loss
+        Bump &region = *keep.bump;
+        DevPlan none = dv;
+        Carve size;
+        lay_backward(*plan, none, size, false);
+        if (size.off > region.cap - region.used) {
+            region.need = std::max(region.need, region.used + size.off);
+            return fail(APML_ERR_OUT_OF_MEMORY, "device allocation failed (backward)");
+        }
+    }
     // the per-sample Sinkhorn path: the column softmax writes each pair into
     // its pieces (no separate packing launch)
     if (plan->sink_fwd) {
@@ -1070,31 +1100,16 @@ apml_status run_backward(apml_plan *plan, const float *x, const float *y, const 
     dv.grad_x = grad_x;
     dv.grad_y = grad_y;
     dv.yr = dv.yc = nullptr;
-    const size_t BN = (size_t)plan->B * plan->N, BM = (size_t)plan->B * plan->M;
     // The kernels of larger samples exchange the owners' words of every phase
     // in memory; where that does not fit, the per-iteration launches, which
     // keep one word per owner, take the sweeps.
     bool wide = plan->sink_wide && dv.L > 0;
-    auto lay = [&](Carve &c) {
-        dv.cbar = c.take<double>(plan->stored);
-        if (dv.L == 0)
-            return;
-        dv.adj = c.take<double>(plan->stored);
-        dv.rbar = c.take<double>(BN);
-        dv.cs = c.take<double2>(BM);
-        if (wide) {
-            if (sinkhorn_bwd_streams(dv.wk_row.slots, plan->B))
-                dv.wz = c.take<double>(packed_order_words(plan->B, dv.wk_row.slots));
-            dv.yr = c.take<double>(sinkhorn_exchange_words(dv.L, BN));
-            dv.yc = c.take<double>(sinkhorn_exchange_words(dv.L, BM));
-        }
-    };
     for (;;) {
         Carve size;
-        lay(size);
+        lay_backward(*plan, dv, size, wide);
         Carve c{tmp.get<uint8_t>(size.off)};
         if (!tmp.failed) {
-            lay(c);
+            lay_backward(*plan, dv, c, wide);
             break;
         }
         if (!wide)
@@ -1150,9 +1165,8 @@ apml_status apml_backward(apml_plan *plan, const float *x, const float *y, const
 // forward + backward without allocation
 // ---------------------------------------------------------------------------
 
-// Device scratch of apml_forward_backward_noalloc: every array of the plan and
-// every temporary of one forward + backward call is carved from it, front to
-// back. Each device the library runs on holds its own copy until the process
+// Device scratch of apml_forward_backward_noalloc: every array of the plan is
+// carved from its front, the temporaries of a pass from its end. Each device the library runs on holds its own copy until the process
 // ends. Host code never uses this name as an address: the kernels receive the
 // per-device address that hipGetSymbolAddress returns.
 static __device__ __align__(256) unsigned char scratch[APML_NOALLOC_SCRATCH_BYTES];
@@ -1231,6 +1245,7 @@ apml_status apml_forward_backward_noalloc(const float *x, const float *y, int32_
     bump.cap = APML_NOALLOC_SCRATCH_BYTES;
     apml_plan plan; // host state on the stack; its arrays live in the scratch
     plan.timed = false;
+    plan.with_grad = grad_x != nullptr;
     plan.keep.bump = &bump;
     plan.keep.stream = s;
     auto too_large = [&](apml_status r) {

@@ -83,3 +83,31 @@ def test_noalloc_rejects_a_call_beyond_its_scratch():
     ref_loss, ref_gx, _ = _allocating(x1, y1, prm1, torch.ones(w1.B, device="cuda"))
     l1, g1, _ = apml.apml_forward_backward_noalloc(x1, y1, prm1)
     assert np.array_equal(l1.cpu().numpy(), ref_loss) and np.array_equal(g1.cpu().numpy(), ref_gx)
+
+
+def test_noalloc_rejects_before_the_loss_what_has_no_room_for_the_backward_pass():
+    # every pair stored (tau = 0): of the sizes whose forward pass fits, the
+    # largest have no room left for two doubles a pair
+    g = np.random.default_rng(5)
+    fits = refused = 0
+    for n in range(1300, 1801, 50):
+        x, y = (torch.from_numpy(g.standard_normal((1, n, 3)).astype(np.float32)).cuda() for _ in range(2))
+        prm = apml.apml_params_default(tau=0.0, n_iter=1)
+        note(f"no-alloc, every pair stored: {n} x {n}")
+        try:
+            apml.apml_forward_backward_noalloc(x, y, prm, want_grad=False)
+        except apml.ApmlError:
+            break
+        fits += 1
+        lib = apml.load()
+        import ctypes
+        loss, gx, gl = torch.full((1,), 7.0, device="cuda"), torch.full_like(x, 7.0), torch.ones(1, device="cuda")
+        ptr = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+        st = lib.apml_forward_backward_noalloc(ptr(x), ptr(y), 1, n, n, 3, ctypes.byref(prm), ptr(loss), ptr(gl),
+                                               ptr(gx), None, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+        assert st in (0, 3)
+        if st == 3:
+            refused += 1
+            assert (loss == 7.0).all() and (gx == 7.0).all()
+    assert fits > refused > 0
