@@ -34,9 +34,12 @@ HBM_PEAK = 8.0e12
 # support scan, the row's and the column's radius test): 3 subtractions,
 # 3 multiplications, 2 additions = 8 FLOPs per pair. The selects (min, med3,
 # compares) are not floating-point arithmetic and are not counted. The full
-# statistics scan evaluates every pair once for both directions; the VALU
-# issue rate it reaches is measured with counters (VALU instructions per CU
-# and clock), not here.
+# support scan finds its candidates on the matrix cores (bfloat16 products) and
+# evaluates only those in FP32; it is rated by the same 8 FLOPs of a pair
+# against the FP32 vector peak, so that its fraction compares with the
+# statistics scan's. The full statistics scan evaluates every pair once for
+# both directions; the VALU issue rate it reaches is measured with counters
+# (VALU instructions per CU and clock), not here.
 FLOPS_PER_PAIR = 8
 
 
@@ -64,7 +67,8 @@ PHASE_MODEL = {
               {"full": "k_top2_pairs: minimum and second minimum of every row and column, each pair evaluated once",
                "skip": "k_spatial_sort + k_cull_top2: curve order, then the minima over the runs that can matter"}),
     "support": ("alu", _flops(1, 1), "FLOP",
-                {"full": "k_emit: radius test of every pair, counts and staged hits of the candidate support",
+                {"full": "k_emit: radius test of every pair (matrix cores, candidates again in FP32), counts and staged "
+                         "hits of the candidate support",
                  "skip": "k_cull_emit: radius test over the runs that can matter, counts and staged hits"}),
     "build": ("hbm", _bytes(lambda w: 16), "bytes",
               {"full": "k_emit_compact_place: row-major structure from the staged hits, placement of the Sinkhorn pieces",

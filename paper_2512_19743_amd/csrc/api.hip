@@ -1,7 +1,7 @@
 // Host side of libapml: argument validation, device memory (pool or caller
 // allocator), per-phase event timing, and the launch sequence of the forward
 // and backward passes (Algorithm 1 of the paper, redesigned as described at
-// the top of kernels.hip).
+// the top of each kernel file).
 #include <algorithm>
 #include <chrono>
 #include <cmath>

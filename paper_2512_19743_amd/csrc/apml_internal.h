@@ -360,8 +360,8 @@ hipError_t set_dynamic_lds(const void *k, size_t bytes);
 
 void launch_softmax(const DevPlan &d, const Params &p, hipStream_t s);
 // Backward of both softmaxes and the distance gradient. double_p: P formed
-// again in double precision from the stored costs (for plans whose reverse
-// sweeps keep the adjoint in double, or that have none), else read as stored.
+// again in double precision from the stored costs (for plans of the
+// per-iteration sweeps, or of none), else read as stored.
 void launch_bwd_softmax(const DevPlan &d, const Params &p, bool double_p, hipStream_t s);
 
 // Sinkhorn. The per-sample kernels run all iterations in one workgroup per
@@ -423,11 +423,8 @@ hipError_t launch_sinkhorn_bwd_wide(const DevPlan &d, double eps, hipStream_t s)
 bool sinkhorn_bwd_streams(int slots, int B);
 size_t sinkhorn_exchange_words(int L, size_t owners);
 size_t packed_order_words(int B, int slots); // 32-bit words of one PackedOrder's p0 array
-// Lays out the pieces of both orders; place: [B][2][2048] int32 scratch.
-// placed: place[] and the info words are already written (with the compaction).
-void launch_pack(const DevPlan &d, int32_t *place, bool placed, hipStream_t s);
-// Only the placement (place[] and the info words), when the column softmax
-// packs the pairs.
+// Places the pieces of both orders (place: [B][2][2048] int32 scratch, and the
+// info words); the column softmax writes the pairs into them.
 void launch_place(const DevPlan &d, int32_t *place, hipStream_t s);
 hipError_t launch_sinkhorn_fwd(const DevPlan &d, double eps, hipStream_t s);
 // The first adjoints of the row and column sums (rbar, cs) from the loss, then

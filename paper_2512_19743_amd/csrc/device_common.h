@@ -165,13 +165,14 @@ template <bool LDS_ONLY> __device__ __forceinline__ void wg_barrier()
 }
 
 // Calls f(lanes, owner, lane of the group) for the owner of each group of G
-// lanes (a power of two from 4 to 64), then, for the owners whose segment exceeds CAP pairs a lane (what a
-// lane loads at once), with the whole wave, one such owner after another.
+// lanes (a power of two from 4 to 64), then, for the owners whose segment exceeds
+// CAP pairs a lane (what a lane loads at once), with the whole wave, one such
+// owner after another.
 // A group strides through a long segment with two dependent loads a step
 // while the other groups of its wave wait: one point far from the rest keeps
 // hundreds of candidates (its gap sets its radius), and its row alone took
 // most of a launch. The lane count is a run-time value so that both uses
-// share one copy of f (two copies held 166 instead of 126 registers).
+// share one copy of f: for short f (the sweeps); split_owners keeps two.
 template <int CAP, class F> __device__ __forceinline__ void each_owner(int G, int o, int n_own, const int32_t *ptr, F f)
 {
     const int n = o < n_own ? ptr[o + 1] - ptr[o] : 0;

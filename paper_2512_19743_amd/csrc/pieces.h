@@ -1,6 +1,6 @@
 // Layout of the pieces of the per-sample Sinkhorn kernels, and the device
-// routines that place owners and write pairs into it (k_place and
-// k_pack_pairs in sinkhorn.hip).
+// routines that place owners and write pairs into it (k_place in sinkhorn.hip,
+// the column softmax).
 //
 // Each row's (column's) pairs are cut into pieces of kSinkPiece consecutive
 // pairs; an owner with n pieces takes a group of 2^ceil(log2 n) consecutive

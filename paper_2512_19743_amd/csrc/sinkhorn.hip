@@ -10,7 +10,7 @@
 // indices once and writes no per-pair values.
 //
 // Per-sample kernels: one 1024-lane workgroup per sample runs all 2L sweeps
-// with the sample's pairs in registers. k_place and k_pack_pairs cut every
+// with the sample's pairs in registers. k_place and the column softmax cut every
 // row's (column's) pairs into pieces of kP and lay them out so that an
 // owner's pieces are consecutive lanes of one wave (see PackedOrder). In a
 // sweep each lane sums its pieces (gathering the other side's values from
@@ -38,8 +38,6 @@ namespace {
 constexpr int kT = kSinkLanes;
 constexpr int kP = kSinkPiece;
 constexpr int kSL = kSinkOwners / kSinkLanes; // owners per lane in the owner phase
-using pieces::pack_col_pair;
-using pieces::pack_row_pair;
 using pieces::pk_index;
 using pieces::place_order;
 
@@ -47,23 +45,6 @@ __global__ __launch_bounds__(kT) void k_place(DevPlan d, int32_t *place)
 {
     __shared__ int hist[8], base[8];
     place_order(d, place, blockIdx.x, blockIdx.y == 0, hist, base);
-}
-
-// Writes every stored pair into its piece, one thread per pair and order.
-__global__ __launch_bounds__(kBlock) void k_pack_pairs(DevPlan d, const int32_t *place)
-{
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool rows = g < d.nnz;
-    const int64_t t = rows ? g : g - d.nnz;
-    if (t >= d.nnz)
-        return;
-    if (rows) {
-        const int r = d.csr_row[t], b = r / d.N;
-        pack_row_pair(d, place, b, r - b * d.N, (int)(t - d.row_ptr[r]), d.csr_col[t], d.p0r[t]);
-    } else {
-        const int gc = d.csc_col[t], b = gc / d.M, i = d.csc_row[t];
-        pack_col_pair(d, place, b, gc - b * d.M, (int)(t - d.col_ptr[gc]), i, d.p0c[t]);
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -469,7 +450,7 @@ template <int SLP> __global__ __launch_bounds__(kT) void k_sinkhorn_bwd(DevPlan 
                 const double r = rb[i], al = own_a[i];
                 double acc = 0.0;
 #pragma unroll
-                for (int h = 0; h < kP; h += 2) { // two gathers at a time: four would spill at five slots
+                for (int h = 0; h < kP; h += 2) { // two gathers at a time: at five slots 16 bytes of scratch, at six 104; four spill more
                     const double2 g0 = lds_at<double2>(cs, 2 * u.half(pr.gi[s][h / 2], 0));
                     const double2 g1 = lds_at<double2>(cs, 2 * u.half(pr.gi[s][h / 2], 1));
                     z[s][h] = __builtin_fma(r, g0.x, __builtin_fma(al, g0.y, z[s][h]));
@@ -1291,7 +1272,8 @@ template <int SW> __global__ __launch_bounds__(kT) void k_sinkhorn_fwd_wr(DevPla
 }
 
 // The last of four column slots lives in LDS (28 KB beside the 128 KB of the
-// gathered vector): with it the registers would spill.
+// gathered vector): with it too in registers, more than the 48 bytes of scratch that
+// four slots take would spill.
 __host__ __device__ constexpr int bwd_wide_lds_slots(int sw) { return sw == 4 ? 1 : 0; }
 
 template <int SW> __global__ __launch_bounds__(kT) void k_sinkhorn_bwd_wr(DevPlan d, double eps, int K)
@@ -1811,7 +1793,8 @@ hipError_t launch_sinkhorn_fwd_wide(const DevPlan &d, double eps, hipStream_t s)
 {
     // a forward half-sweep over fewer slots is shorter than the meeting that
     // splitting it needs (measured: 3000 to 4096 points per cloud, 4 to 6
-    // slots, 0.09 -> 0.13 ms; large-batch workload, 12 slots, 0.51 -> 0.35 ms)
+    // slots, 0.09 -> 0.13 ms; 10 to 12 slots: 37 x 7000 points 0.185 -> 0.135 ms,
+    // 72 x 8000 0.257 -> 0.236)
     constexpr int kSplitFwdMinSlots = 8;
     int K = d.wk_row.slots >= kSplitFwdMinSlots ? sinkhorn_split_factor(d.B) : 1;
     if (K > 1 && d.split_sync) {
@@ -1860,13 +1843,6 @@ size_t packed_order_words(int B, int slots) { return (size_t)B * slots * kP * kT
 void launch_place(const DevPlan &d, int32_t *place, hipStream_t s)
 {
     hipLaunchKernelGGL(k_place, dim3(d.B, 2), dim3(kT), 0, s, d, place);
-}
-
-void launch_pack(const DevPlan &d, int32_t *place, bool placed, hipStream_t s)
-{
-    if (!placed)
-        hipLaunchKernelGGL(k_place, dim3(d.B, 2), dim3(kT), 0, s, d, place);
-    hipLaunchKernelGGL(k_pack_pairs, dim3(blocks_for(2 * d.nnz, kBlock)), dim3(kBlock), 0, s, d, (const int32_t *)place);
 }
 
 // The kernel instance for the plan's slot count.

@@ -24,8 +24,8 @@ def _gpu():
 
 
 def _run(X, Y, n_iter, mode, monkeypatch):
-    # mode "0": one workgroup per sample; "1": split, pieces (or the reverse
-    # adjoint) in registers where a workgroup's share allows; "streamed":
+    # mode "0": one workgroup per sample; "1": split, pieces (and the reverse
+    # sweeps' sums) in registers where a workgroup's share allows; "streamed":
     # split, streamed variants only
     monkeypatch.setenv("APML_SINKHORN_SPLIT", mode)
     # an untimed call first: the phase times below are of loaded kernels
@@ -60,10 +60,8 @@ CASES = {
     # one sample with enough pieces for the split forward kernel, B N < 8192
     # (and B not a multiple of 8: seven of the grid's eight rounds end at once)
     "b1_n8000": lambda: custom(75, 1, 8000, 7990, reference="primitives", prediction="perm_noise", sigma=0.02),
-    # B = 37 (not a multiple of 8), four workgroups per sample, ragged
-    # clouds of 7000 and 6500 points: about three slots per workgroup, the
-    # reverse kernel that keeps the adjoint in registers and loads its
-    # pieces in every phase
+    # B = 37 (not a multiple of 8), six workgroups per sample, ragged
+    # clouds of 7000 and 6500 points: about two slots per workgroup
     "b37_ragged": lambda: custom(77, 37, 7000, 6500, reference="primitives", prediction="perm_noise", sigma=0.02),
     # B = 72: three workgroups per sample (a grid of 216), a larger share of
     # each sample's pieces per workgroup
