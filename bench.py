@@ -93,13 +93,13 @@ PHASE_MODEL = {
 # workload, traffic is reported as null.
 TRAFFIC_WORKLOAD = 2
 TRAFFIC = {
-    "stats": {"sources": {"paper_2512_19743_amd/csrc/dense.hip": "b8ad8ac7143c0e550506b6e9f041715acbb53afe58979c162835c46acc143f29", "paper_2512_19743_amd/csrc/apml_internal.h": "9de09b22e2bb70db0e738b837406b4c22d17c6c43878bf853591214bca0bb461", "paper_2512_19743_amd/csrc/device_common.h": "03dc51e197a1281c03edf6f18979a0e66674abec0a0da05b91d1f7efd31020c0"}, "kernels": ["k_top2_pairs", "k_finalize"], "bytes_per_launch": 32933544},
-    "support": {"sources": {"paper_2512_19743_amd/csrc/dense.hip": "b8ad8ac7143c0e550506b6e9f041715acbb53afe58979c162835c46acc143f29", "paper_2512_19743_amd/csrc/apml_internal.h": "9de09b22e2bb70db0e738b837406b4c22d17c6c43878bf853591214bca0bb461", "paper_2512_19743_amd/csrc/device_common.h": "03dc51e197a1281c03edf6f18979a0e66674abec0a0da05b91d1f7efd31020c0"}, "kernels": ["k_emit"], "bytes_per_launch": 31271543},
-    "build": {"sources": {"paper_2512_19743_amd/csrc/dense.hip": "b8ad8ac7143c0e550506b6e9f041715acbb53afe58979c162835c46acc143f29", "paper_2512_19743_amd/csrc/pieces.h": "f583f03e18c705c400d730c1898150e41963388a2bc4895a88aca2cb4a0f625b", "paper_2512_19743_amd/csrc/apml_internal.h": "9de09b22e2bb70db0e738b837406b4c22d17c6c43878bf853591214bca0bb461", "paper_2512_19743_amd/csrc/device_common.h": "03dc51e197a1281c03edf6f18979a0e66674abec0a0da05b91d1f7efd31020c0"}, "kernels": ["k_emit_compact_place"], "bytes_per_launch": 19027330},
-    "softmax": {"sources": {"paper_2512_19743_amd/csrc/softmax.hip": "28183ee496ceedff271bcff0dd2c7514af55af7c0c45ec3fb1acfae43e1015fe", "paper_2512_19743_amd/csrc/apml_internal.h": "9de09b22e2bb70db0e738b837406b4c22d17c6c43878bf853591214bca0bb461", "paper_2512_19743_amd/csrc/device_common.h": "03dc51e197a1281c03edf6f18979a0e66674abec0a0da05b91d1f7efd31020c0"}, "kernels": ["k_csc_rows", "k_col_softmax"], "bytes_per_launch": 47747018},
-    "sinkhorn": {"sources": {"paper_2512_19743_amd/csrc/sinkhorn.hip": "6a3a219f06db8722ed82302bacadd7d5d9a8d94492632d4a1c2cf2fc4b99ff33", "paper_2512_19743_amd/csrc/pieces.h": "f583f03e18c705c400d730c1898150e41963388a2bc4895a88aca2cb4a0f625b", "paper_2512_19743_amd/csrc/apml_internal.h": "9de09b22e2bb70db0e738b837406b4c22d17c6c43878bf853591214bca0bb461", "paper_2512_19743_amd/csrc/device_common.h": "03dc51e197a1281c03edf6f18979a0e66674abec0a0da05b91d1f7efd31020c0"}, "kernels": ["k_sinkhorn_fwd"], "bytes_per_launch": 26089219},
-    "bwd_sinkhorn": {"sources": {"paper_2512_19743_amd/csrc/sinkhorn.hip": "6a3a219f06db8722ed82302bacadd7d5d9a8d94492632d4a1c2cf2fc4b99ff33", "paper_2512_19743_amd/csrc/pieces.h": "f583f03e18c705c400d730c1898150e41963388a2bc4895a88aca2cb4a0f625b", "paper_2512_19743_amd/csrc/apml_internal.h": "9de09b22e2bb70db0e738b837406b4c22d17c6c43878bf853591214bca0bb461", "paper_2512_19743_amd/csrc/device_common.h": "03dc51e197a1281c03edf6f18979a0e66674abec0a0da05b91d1f7efd31020c0"}, "kernels": ["k_sinkhorn_bwd"], "bytes_per_launch": 26059848},
-    "bwd_softmax": {"sources": {"paper_2512_19743_amd/csrc/softmax.hip": "28183ee496ceedff271bcff0dd2c7514af55af7c0c45ec3fb1acfae43e1015fe", "paper_2512_19743_amd/csrc/apml_internal.h": "9de09b22e2bb70db0e738b837406b4c22d17c6c43878bf853591214bca0bb461", "paper_2512_19743_amd/csrc/device_common.h": "03dc51e197a1281c03edf6f18979a0e66674abec0a0da05b91d1f7efd31020c0"}, "kernels": ["k_bwd_col_softmax", "k_bwd_row_softmax"], "bytes_per_launch": 33406536},
+    "stats": {"sources": {"paper_2512_19743_amd/csrc/dense.hip": "9b9199fe92e6f698fbd280bd320a26819ff31ed49c5fa5454c0055a2f21a5b08", "paper_2512_19743_amd/csrc/apml_internal.h": "ea7d10d8785ab7d28e4550f7099e2997702359f3135c01a477c3b8266b15dd7a", "paper_2512_19743_amd/csrc/device_common.h": "c363a8b2c961bc347ed60c7f40974015b979ad6f661edf37453e67a02cd4b254"}, "kernels": ["k_top2_pairs", "k_finalize"], "bytes_per_launch": 33205992},
+    "support": {"sources": {"paper_2512_19743_amd/csrc/dense.hip": "9b9199fe92e6f698fbd280bd320a26819ff31ed49c5fa5454c0055a2f21a5b08", "paper_2512_19743_amd/csrc/apml_internal.h": "ea7d10d8785ab7d28e4550f7099e2997702359f3135c01a477c3b8266b15dd7a", "paper_2512_19743_amd/csrc/device_common.h": "c363a8b2c961bc347ed60c7f40974015b979ad6f661edf37453e67a02cd4b254"}, "kernels": ["k_emit"], "bytes_per_launch": 25129301},
+    "build": {"sources": {"paper_2512_19743_amd/csrc/dense.hip": "9b9199fe92e6f698fbd280bd320a26819ff31ed49c5fa5454c0055a2f21a5b08", "paper_2512_19743_amd/csrc/pieces.h": "f23151f6549a77f730628a1bade974fba9ae636f38d633eea41934fc70f2d392", "paper_2512_19743_amd/csrc/apml_internal.h": "ea7d10d8785ab7d28e4550f7099e2997702359f3135c01a477c3b8266b15dd7a", "paper_2512_19743_amd/csrc/device_common.h": "c363a8b2c961bc347ed60c7f40974015b979ad6f661edf37453e67a02cd4b254"}, "kernels": ["k_emit_compact_place"], "bytes_per_launch": 17988417},
+    "softmax": {"sources": {"paper_2512_19743_amd/csrc/softmax.hip": "623bf06d899673103c3205702aaee835cd2a03af83d7eac471c9183cdc7876ee", "paper_2512_19743_amd/csrc/pieces.h": "f23151f6549a77f730628a1bade974fba9ae636f38d633eea41934fc70f2d392", "paper_2512_19743_amd/csrc/apml_internal.h": "ea7d10d8785ab7d28e4550f7099e2997702359f3135c01a477c3b8266b15dd7a", "paper_2512_19743_amd/csrc/device_common.h": "c363a8b2c961bc347ed60c7f40974015b979ad6f661edf37453e67a02cd4b254"}, "kernels": ["k_csc_rows", "k_col_softmax"], "bytes_per_launch": 43775271},
+    "sinkhorn": {"sources": {"paper_2512_19743_amd/csrc/sinkhorn.hip": "3fa3c091de247b94ff060e6e6c8dbedf9c0c63d11b8984a17203a4ceb20ae9ac", "paper_2512_19743_amd/csrc/pieces.h": "f23151f6549a77f730628a1bade974fba9ae636f38d633eea41934fc70f2d392", "paper_2512_19743_amd/csrc/apml_internal.h": "ea7d10d8785ab7d28e4550f7099e2997702359f3135c01a477c3b8266b15dd7a", "paper_2512_19743_amd/csrc/device_common.h": "c363a8b2c961bc347ed60c7f40974015b979ad6f661edf37453e67a02cd4b254"}, "kernels": ["k_sinkhorn_fwd"], "bytes_per_launch": 26091267},
+    "bwd_sinkhorn": {"sources": {"paper_2512_19743_amd/csrc/sinkhorn.hip": "3fa3c091de247b94ff060e6e6c8dbedf9c0c63d11b8984a17203a4ceb20ae9ac", "paper_2512_19743_amd/csrc/pieces.h": "f23151f6549a77f730628a1bade974fba9ae636f38d633eea41934fc70f2d392", "paper_2512_19743_amd/csrc/apml_internal.h": "ea7d10d8785ab7d28e4550f7099e2997702359f3135c01a477c3b8266b15dd7a", "paper_2512_19743_amd/csrc/device_common.h": "c363a8b2c961bc347ed60c7f40974015b979ad6f661edf37453e67a02cd4b254"}, "kernels": ["k_bwd_direct", "k_sinkhorn_bwd"], "bytes_per_launch": 36252756},
+    "bwd_softmax": {"sources": {"paper_2512_19743_amd/csrc/softmax.hip": "623bf06d899673103c3205702aaee835cd2a03af83d7eac471c9183cdc7876ee", "paper_2512_19743_amd/csrc/apml_internal.h": "ea7d10d8785ab7d28e4550f7099e2997702359f3135c01a477c3b8266b15dd7a", "paper_2512_19743_amd/csrc/device_common.h": "c363a8b2c961bc347ed60c7f40974015b979ad6f661edf37453e67a02cd4b254"}, "kernels": ["k_bwd_col_softmax", "k_bwd_row_softmax"], "bytes_per_launch": 38318618},
 }
 
 
